@@ -168,11 +168,11 @@ void* static_scratch_ptr(hipError_t* err) {
 sa_status hip_status(hipError_t e) { return e == hipSuccess ? SA_OK : (e == hipErrorNotSupported ? SA_ERR_UNSUPPORTED : SA_ERR_HIP); }
 
 hipError_t run_fwd(const sa_desc* c, const Pass& p, hipStream_t st) {
-  return c->dtype == SA_F32 ? sa::launch_fwd_rowwise_f32(p, st) : sa::launch_fwd_mfma_bf16(p, st);
+  return c->dtype == SA_F32 ? sa::launch_fwd_f32(p, st) : sa::launch_fwd_mfma_bf16(p, st);
 }
 
 hipError_t run_bwd(const sa_desc* c, const Pass& p, hipStream_t st) {
-  return c->dtype == SA_F32 ? sa::launch_bwd_rowwise_f32(p, st) : sa::launch_bwd_mfma_bf16(p, st);
+  return c->dtype == SA_F32 ? sa::launch_bwd_f32(p, st) : sa::launch_bwd_mfma_bf16(p, st);
 }
 
 }  // namespace
@@ -554,8 +554,8 @@ sa_status sa_bwd(const sa_desc* sa_d, const sa_desc* swa_d, const void* Q, const
   pr.lse_a = LSE_sa; pr.lse_b = LSE_swa;
   pr.L_a = fold ? reinterpret_cast<float*>(base + w.off_dOa) : nullptr;
   pr.L_b = fold ? pr.L_a + (size_t)pr.rows : nullptr;
-  // ungated bf16: no separate pass, the dQ kernel forms rowsum(dY o Y) from the rows it holds
-  const bool rowsum_in_dq = !gated && sa_d->dtype == SA_BF16;
+  // ungated: no separate pass, the dQ kernel forms rowsum(dY o Y) from the rows it holds
+  const bool rowsum_in_dq = !gated;
   hipError_t e = rowsum_in_dq ? hipSuccess : sa::launch_bwd_prepare(pr, st);
   if (e != hipSuccess) return hip_status(e);
 

@@ -62,8 +62,8 @@ __host__ __device__ inline int perm_slice_index(int perm_B, int perm_H, int b, i
 }
 
 // kernels (each file checks its own launch geometry against the Pass on the host)
-hipError_t launch_fwd_rowwise_f32(const Pass& p, hipStream_t st);
-hipError_t launch_bwd_rowwise_f32(const Pass& p, hipStream_t st);
+hipError_t launch_fwd_f32(const Pass& p, hipStream_t st);
+hipError_t launch_bwd_f32(const Pass& p, hipStream_t st);
 hipError_t launch_fwd_mfma_bf16(const Pass& p, hipStream_t st);
 hipError_t launch_bwd_mfma_bf16(const Pass& p, hipStream_t st);
 
