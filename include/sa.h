@@ -111,10 +111,10 @@ sa_status sa_fwd(const sa_desc* desc, const void* Q, const void* K, const void* 
  * by p (44 random bits, ties - probability < n^2/2^45 per slice - go to the smaller p), and perm = the
  * argsort of the keys.  Deterministic in (seed, layer, slice, n); no host round trip.  layer >= 0;
  * n <= 2^20 (SA_ERR_UNSUPPORTED beyond); at most 65535 slices.
- * ws = NULL: the rank of every key is counted against all keys, O(n^2) compares per slice, no workspace.
- * ws = sa_workspace_bytes(desc, SA_OP_SAMPLE_PERM) bytes of device memory: the keys are first spread over
- * buckets by their top bits and ranked inside their bucket, O(n) work in five small launches (taken for
- * n >= 16384, where it is the faster one); the same permutation, bit for bit. */
+ * ws = NULL: one launch, no workspace; every bucket of keys is gathered by a pass over all of them (O(n^2 / 64)
+ * hashes up to n = 32768, O(n^2 / 256) beyond).
+ * ws = sa_workspace_bytes(desc, SA_OP_SAMPLE_PERM) bytes of device memory: longer requests form every key once, in
+ * two launches (O(n) work); the same permutation, bit for bit. */
 sa_status sa_sample_perm(const sa_desc* desc, uint64_t seed, int32_t layer, int32_t* perm, void* ws,
                          size_t ws_bytes, void* stream);
 

@@ -89,10 +89,15 @@ __global__ __launch_bounds__(256) void permuted_copy_bf16_kernel(const Pass p, c
 // ---- permutation sampler (Sec. 3.3: sigma ~ Uniform(S_n), fresh per layer): sort by random key.
 // Slot p of slice s gets the 64-bit sort key  (r(p) with its low 20 bits replaced by p),  r(p) = the
 // (p+1)-th output of SplitMix64 started at a per-(seed, layer, slice) stream value: 44 random bits,
-// ties broken by p, all keys distinct.  perm = argsort of the keys, computed as a rank: the thread of
-// slot p counts the keys below its own and writes perm[rank] = p.  All keys of the slice stream
-// through LDS in tiles of 1024; 16 lanes share one slot (each takes every 16th pair of keys of a
-// tile, the partial counts are added with shuffles), so even a short slice fills the chip.
+// ties broken by p, all keys distinct.  perm = argsort of the keys.  The keys are uniform 64-bit numbers, so their top
+// bits spread them evenly over buckets; a workgroup owns one bucket of one slice, gathers its keys in LDS together with
+// the number of keys in lower buckets, ranks them among themselves and writes perm[lower + rank] = p.  The result
+// depends on no order of arrival.  Two ways to gather:
+//   scan    one launch, no workspace: every workgroup forms all n keys (a hash of p, 150 cycles per 64 of them) and
+//           keeps its own;
+//   binned  two launches, with a workspace: a first kernel forms each key once, in pieces of consecutive slots, and
+//           leaves every piece ordered by bucket with the bucket boundaries beside it; the owner of a bucket then
+//           reads one boundary pair and a few keys per piece, and the boundaries' sum is the number of lower keys.
 __device__ __forceinline__ uint64_t splitmix_mix(uint64_t z) {
   z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
   z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
@@ -100,111 +105,148 @@ __device__ __forceinline__ uint64_t splitmix_mix(uint64_t z) {
 }
 constexpr uint64_t kGamma = 0x9E3779B97F4A7C15ull;
 constexpr uint64_t kIndexMask = 0xFFFFFull;  // n <= 2^20
-constexpr int SAMPLE_TILE = 1024;
 
 __device__ __forceinline__ uint64_t sort_key(uint64_t stream, int p) {
   return (splitmix_mix(stream + kGamma * (uint64_t)(p + 1)) & ~kIndexMask) | (uint64_t)p;
 }
 
-constexpr int SAMPLE_LPP = 16;  // lanes that share the rank count of one slot
-
-__global__ __launch_bounds__(256) void sample_perm_kernel(int32_t* __restrict__ perm, const int n, const uint64_t seed,
-                                                           const int layer) {
-  __shared__ __attribute__((aligned(16))) uint64_t tile[SAMPLE_TILE];
-  const int slice = blockIdx.y;
-  const uint64_t stream = splitmix_mix(splitmix_mix(seed) + kGamma * (((uint64_t)(uint32_t)layer << 32) | (uint32_t)slice));
-  const int p = blockIdx.x * (256 / SAMPLE_LPP) + threadIdx.x / SAMPLE_LPP;
-  const int sub = threadIdx.x % SAMPLE_LPP;
-  const uint64_t mine = sort_key(stream, p);
-  int rank = 0;
-  for (int q0 = 0; q0 < n; q0 += SAMPLE_TILE) {
-    __syncthreads();
-    // keys past the end of the slice are set above every real key
-    for (int j = threadIdx.x; j < SAMPLE_TILE; j += 256) tile[j] = q0 + j < n ? sort_key(stream, q0 + j) : ~0ull;
-    __syncthreads();
-#pragma unroll 8
-    for (int j = 2 * sub; j < SAMPLE_TILE; j += 2 * SAMPLE_LPP) {  // two keys per 16-byte read
-      const ulonglong2 k = *reinterpret_cast<const ulonglong2*>(tile + j);
-      rank += (k.x < mine) ? 1 : 0;
-      rank += (k.y < mine) ? 1 : 0;
-    }
-  }
-#pragma unroll
-  for (int o = SAMPLE_LPP / 2; o > 0; o >>= 1) rank += __shfl_xor(rank, o);
-  if (sub == 0 && p < n) perm[(size_t)slice * n + rank] = p;
-}
-
-// ---- the same permutation in O(n) work, with a workspace: the keys are uniform 64-bit numbers, so their
-// top bits spread them evenly over NB buckets (64 keys each on average).  Count per bucket, exclusive scan,
-// scatter the keys into their buckets (in any order), then rank every key inside its bucket: the slot of
-// key k goes to perm[start(bucket) + #{keys of the bucket below k}].  The result does not depend on the
-// order in which the atomic counters hand out places.
 __device__ __forceinline__ uint64_t slice_stream(uint64_t seed, int layer, int slice) {
   return splitmix_mix(splitmix_mix(seed) + kGamma * (((uint64_t)(uint32_t)layer << 32) | (uint32_t)slice));
 }
 
-struct SampleWs {
-  uint64_t* keys;  // [slices][n]
-  int* count;      // [slices][NB]
-  int* cursor;     // [slices][NB]: first free place of the bucket while scattering, its end afterwards
-  int NB, shift;   // bucket of key k = k >> shift (shift = 64: one bucket)
-};
+constexpr int SAMPLE_CAP = 1024;  // keys of a bucket held in LDS (at most 256 expected: 1024 is 48 standard deviations off)
 
-__device__ __forceinline__ int bucket_of(uint64_t k, int shift) { return shift >= 64 ? 0 : (int)(k >> shift); }
-
-__global__ __launch_bounds__(256) void sample_count_kernel(SampleWs w, const int n, const uint64_t seed, const int layer) {
-  const int slice = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= n) return;
-  const uint64_t k = sort_key(slice_stream(seed, layer, slice), p);
-  atomicAdd(w.count + (size_t)slice * w.NB + bucket_of(k, w.shift), 1);
+// perm[lower + rank of the key in its bucket] = slot, for the cnt keys in LDS: four lanes share a key
+__device__ __forceinline__ void rank_bucket(const uint64_t* keys, int cnt, int lower, int32_t* __restrict__ perm_slice) {
+  const int sub = threadIdx.x & 3;
+  for (int e0 = 0; e0 < cnt; e0 += 64) {
+    const int e = e0 + (threadIdx.x >> 2);
+    const uint64_t mine = keys[min(e, cnt - 1)];
+    int rank = 0;
+#pragma unroll 4
+    for (int j = sub; j < cnt; j += 4) rank += keys[j] < mine ? 1 : 0;
+    rank += __shfl_xor(rank, 1);
+    rank += __shfl_xor(rank, 2);
+    if (sub == 0 && e < cnt) perm_slice[lower + rank] = (int32_t)(mine & kIndexMask);
+  }
 }
 
-// one workgroup per slice: cursor = exclusive prefix sum of count
-__global__ __launch_bounds__(256) void sample_scan_kernel(SampleWs w) {
-  __shared__ int part[256];
-  const int slice = blockIdx.x, t = threadIdx.x;
-  const int* cnt = w.count + (size_t)slice * w.NB;
-  int* cur = w.cursor + (size_t)slice * w.NB;
-  const int per = (w.NB + 255) / 256, b0 = t * per, b1 = min(b0 + per, w.NB);
-  int sum = 0;
-  for (int b = b0; b < b1; ++b) sum += cnt[b];
-  part[t] = sum;
+// A bucket that does not fit in LDS (never seen): its keys are ranked against all keys of the slice, one after another.
+__device__ void rank_oversized(uint64_t stream, int bucket, int shift, int n, int32_t* __restrict__ perm_slice) {
+  for (int p = threadIdx.x; p < n; p += 256) {
+    const uint64_t mine = sort_key(stream, p);
+    if ((int)(mine >> shift) != bucket) continue;
+    int rank = 0;
+    for (int q = 0; q < n; ++q) rank += sort_key(stream, q) < mine ? 1 : 0;
+    perm_slice[rank] = p;
+  }
+}
+
+// grid (buckets, slices); bucket of key k = k >> shift, shift <= 63
+__global__ __launch_bounds__(256) void sample_scan_kernel(int32_t* __restrict__ perm, const int n, const uint64_t seed, const int layer,
+                                                          const int shift) {
+  __shared__ uint64_t keys[SAMPLE_CAP];
+  __shared__ int counters[2];  // keys in the bucket, keys below it
+  const int bucket = blockIdx.x, slice = blockIdx.y;
+  const uint64_t stream = slice_stream(seed, layer, slice);
+  if (threadIdx.x < 2) counters[threadIdx.x] = 0;
   __syncthreads();
-  if (t == 0) {
-    int run = 0;
-    for (int i = 0; i < 256; ++i) {
-      const int v = part[i];
-      part[i] = run;
-      run += v;
+  int lower = 0;
+#pragma unroll 4
+  for (int p = threadIdx.x; p < n; p += 256) {
+    const uint64_t k = sort_key(stream, p);
+    const int b = (int)(k >> shift);
+    lower += b < bucket ? 1 : 0;
+    if (b == bucket) {
+      const int at = atomicAdd(&counters[0], 1);
+      if (at < SAMPLE_CAP) keys[at] = k;
     }
   }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) lower += __shfl_xor(lower, o);
+  if ((threadIdx.x & 63) == 0) atomicAdd(&counters[1], lower);
   __syncthreads();
-  int run = part[t];
+  const int cnt = counters[0];
+  int32_t* out = perm + (size_t)slice * n;
+  if (cnt > SAMPLE_CAP) rank_oversized(stream, bucket, shift, n, out);
+  else rank_bucket(keys, cnt, counters[1], out);
+}
+
+struct SampleWs {
+  uint64_t* keys;    // [slices][n]: pieces of `piece` slots, each ordered by bucket
+  uint16_t* bounds;  // [slices][pieces][buckets + 1]: where each bucket starts in its piece
+  int buckets, shift, piece, pieces;
+};
+
+constexpr int SAMPLE_MAX_BUCKETS = 4096;
+
+// grid (pieces, slices)
+__global__ __launch_bounds__(256) void sample_bin_kernel(const SampleWs w, const int n, const uint64_t seed, const int layer) {
+  __shared__ int place[SAMPLE_MAX_BUCKETS];
+  __shared__ int wave_sum[4];
+  const int piece = blockIdx.x, slice = blockIdx.y, t = threadIdx.x;
+  const uint64_t stream = slice_stream(seed, layer, slice);
+  const int p0 = piece * w.piece, p1 = min(p0 + w.piece, n);
+  for (int b = t; b < w.buckets; b += 256) place[b] = 0;
+  __syncthreads();
+  for (int p = p0 + t; p < p1; p += 256) atomicAdd(&place[(int)(sort_key(stream, p) >> w.shift)], 1);
+  __syncthreads();
+  // exclusive prefix sum: a thread sums its run of buckets, the runs are scanned over the workgroup
+  const int run = (w.buckets + 255) / 256, b0 = t * run, b1 = min(b0 + run, w.buckets);
+  int sum = 0;
+  for (int b = b0; b < b1; ++b) sum += place[b];
+  int incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o);
+    if ((t & 63) >= o) incl += v;
+  }
+  if ((t & 63) == 63) wave_sum[t >> 6] = incl;
+  __syncthreads();
+  int at = incl - sum;
+  for (int v = 0; v < (t >> 6); ++v) at += wave_sum[v];
   for (int b = b0; b < b1; ++b) {
-    cur[b] = run;
-    run += cnt[b];
+    const int c = place[b];
+    place[b] = at;
+    at += c;
+  }
+  __syncthreads();
+  uint16_t* bounds = w.bounds + ((size_t)slice * w.pieces + piece) * (w.buckets + 1);
+  for (int b = t; b <= w.buckets; b += 256) bounds[b] = (uint16_t)(b < w.buckets ? place[b] : p1 - p0);
+  __syncthreads();
+  uint64_t* keys = w.keys + (size_t)slice * n + p0;
+  for (int p = p0 + t; p < p1; p += 256) {
+    const uint64_t k = sort_key(stream, p);
+    keys[atomicAdd(&place[(int)(k >> w.shift)], 1)] = k;
   }
 }
 
-__global__ __launch_bounds__(256) void sample_scatter_kernel(SampleWs w, const int n, const uint64_t seed, const int layer) {
-  const int slice = blockIdx.y, p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= n) return;
-  const uint64_t k = sort_key(slice_stream(seed, layer, slice), p);
-  const int place = atomicAdd(w.cursor + (size_t)slice * w.NB + bucket_of(k, w.shift), 1);
-  w.keys[(size_t)slice * n + place] = k;
-}
-
-__global__ __launch_bounds__(256) void sample_rank_kernel(SampleWs w, int32_t* __restrict__ perm, const int n) {
-  const int slice = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= n) return;
-  const uint64_t* keys = w.keys + (size_t)slice * n;
-  const uint64_t k = keys[e];
-  const int b = bucket_of(k, w.shift);
-  const int cnt = w.count[(size_t)slice * w.NB + b];
-  const int start = w.cursor[(size_t)slice * w.NB + b] - cnt;  // the cursor ended at the bucket's end
-  int rank = 0;
-  for (int j = 0; j < cnt; ++j) rank += keys[start + j] < k ? 1 : 0;
-  perm[(size_t)slice * n + start + rank] = (int32_t)(k & kIndexMask);
+// grid (buckets, slices)
+__global__ __launch_bounds__(256) void sample_merge_kernel(const SampleWs w, int32_t* __restrict__ perm, const int n, const uint64_t seed,
+                                                           const int layer) {
+  __shared__ uint64_t keys[SAMPLE_CAP];
+  __shared__ int counters[2];
+  const int bucket = blockIdx.x, slice = blockIdx.y;
+  if (threadIdx.x < 2) counters[threadIdx.x] = 0;
+  __syncthreads();
+  int lower = 0;
+  for (int c = threadIdx.x; c < w.pieces; c += 256) {
+    const uint16_t* bounds = w.bounds + ((size_t)slice * w.pieces + c) * (w.buckets + 1) + bucket;
+    const int i0 = bounds[0], i1 = bounds[1];
+    const uint64_t* src = w.keys + (size_t)slice * n + (size_t)c * w.piece;
+    lower += i0;
+    int at = i1 > i0 ? atomicAdd(&counters[0], i1 - i0) : 0;
+    for (int i = i0; i < i1; ++i, ++at)
+      if (at < SAMPLE_CAP) keys[at] = src[i];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) lower += __shfl_xor(lower, o);
+  if ((threadIdx.x & 63) == 0) atomicAdd(&counters[1], lower);
+  __syncthreads();
+  const int cnt = counters[0];
+  int32_t* out = perm + (size_t)slice * n;
+  if (cnt > SAMPLE_CAP) rank_oversized(slice_stream(seed, layer, slice), bucket, w.shift, n, out);
+  else rank_bucket(keys, cnt, counters[1], out);
 }
 
 template <int LPR>  // lanes per row, each lane owns 16 bytes of the row
@@ -375,45 +417,49 @@ hipError_t launch_check_perm(const int32_t* perm, int slices, int n, int* seen, 
   return hipGetLastError();
 }
 
-// buckets for the workspace path: a power of two, 64 keys per bucket on average
-static int sample_buckets(int n) {
-  int nb = 1;
-  while ((long)nb * 64 < n) nb *= 2;
-  return nb;
+// log2 of the number of buckets: `per_bucket` keys each on average, at least two buckets (a shift by 64 is undefined)
+static int sample_bits(int n, int per_bucket) {
+  int bits = 1;
+  while (((long)per_bucket << bits) < n) ++bits;
+  return bits;
+}
+
+// Binned form: 128 keys a bucket (256 from 2^19 slots on: SAMPLE_MAX_BUCKETS), pieces of at least as many slots as there
+// are buckets, so that the boundaries stay smaller than the keys.
+static SampleWs sample_layout(int n) {
+  SampleWs w = {};
+  int bits = sample_bits(n, 128);
+  while ((1 << bits) > SAMPLE_MAX_BUCKETS) --bits;
+  w.buckets = 1 << bits;
+  w.shift = 64 - bits;
+  w.piece = w.buckets < 512 ? 512 : w.buckets;
+  w.pieces = (n + w.piece - 1) / w.piece;
+  return w;
 }
 
 size_t sample_perm_workspace_bytes(int slices, int n) {
-  const size_t nb = (size_t)sample_buckets(n);
-  return (size_t)slices * ((size_t)n * 8 + 2 * nb * 4) + 512;
+  const SampleWs w = sample_layout(n);
+  return (size_t)slices * ((size_t)n * 8 + (size_t)w.pieces * (w.buckets + 1) * 2) + 512;
 }
 
 hipError_t launch_sample_perm(int32_t* perm, int slices, int n, uint64_t seed, int layer, void* ws, hipStream_t st) {
   if (!perm || slices < 1 || slices > 65535 || n < 1) return hipErrorInvalidValue;
   if (n > (1 << 20)) return hipErrorNotSupported;  // the slot index takes the low 20 bits of the sort key
-  // five small launches: below ~16K slots the single O(n^2) launch is faster (0.017 against 0.037 ms at
-  // n = 8192; 0.135 against 0.045 ms at n = 32768)
-  if (ws && n >= 16384) {
-    SampleWs w;
-    w.NB = sample_buckets(n);
-    int bits = 0;
-    while ((1 << bits) < w.NB) ++bits;
-    w.shift = 64 - bits;
+  const int bits = sample_bits(n, n <= 32768 ? 64 : 256);
+  // The scan forms n keys in every workgroup, 6 million of them in about the time of the second launch of the binned form
+  // (event times, both forms: 1 slice of 16 384 12.6 / 15.4 us, of 24 000 17.7 / 15.6 us, of 131 072 78 / 16.8 us;
+  // 12 slices of 8192 19.2 / 16.8 us).  Sorting by counting every key against every other took 38 us at n = 16 384, and
+  // five launches over global counters 44 us at 32 768 (now 15.8) and 60 us at 131 072.
+  if (ws && (double)slices * n * (1 << bits) > 6e6) {
+    SampleWs w = sample_layout(n);
     char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~(uintptr_t)255);
     w.keys = reinterpret_cast<uint64_t*>(base);
-    w.count = reinterpret_cast<int*>(base + (size_t)slices * n * 8);
-    w.cursor = w.count + (size_t)slices * w.NB;
-    hipError_t e = launch_fill_zero(w.count, (size_t)slices * w.NB * 4, st);
-    if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)((n + 255) / 256), (unsigned)slices);
-    hipLaunchKernelGGL(sample_count_kernel, grid, dim3(256), 0, st, w, n, seed, layer);
-    hipLaunchKernelGGL(sample_scan_kernel, dim3((unsigned)slices), dim3(256), 0, st, w);
-    hipLaunchKernelGGL(sample_scatter_kernel, grid, dim3(256), 0, st, w, n, seed, layer);
-    hipLaunchKernelGGL(sample_rank_kernel, grid, dim3(256), 0, st, w, perm, n);
+    w.bounds = reinterpret_cast<uint16_t*>(base + (size_t)slices * n * 8);
+    hipLaunchKernelGGL(sample_bin_kernel, dim3((unsigned)w.pieces, (unsigned)slices), dim3(256), 0, st, w, n, seed, layer);
+    hipLaunchKernelGGL(sample_merge_kernel, dim3((unsigned)w.buckets, (unsigned)slices), dim3(256), 0, st, w, perm, n, seed, layer);
     return hipGetLastError();
   }
-  const int per_block = 256 / SAMPLE_LPP;
-  hipLaunchKernelGGL(sample_perm_kernel, dim3((unsigned)((n + per_block - 1) / per_block), (unsigned)slices), dim3(256), 0, st,
-                     perm, n, seed, layer);
+  hipLaunchKernelGGL(sample_scan_kernel, dim3(1u << bits, (unsigned)slices), dim3(256), 0, st, perm, n, seed, layer, 64 - bits);
   return hipGetLastError();
 }
 

@@ -82,3 +82,16 @@ def test_sample_perm_rejects_bad_arguments():
     with pytest.raises(sa.SaError) as e:
         sa.sa_sample_perm(big, 1, 0, perm, ws)
     assert e.value.status == sa.SA_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("slices,n", [(1, 2), (1, 65), (3, 257), (1, 19999), (1, 23439), (12, 5700), (12, 6500), (2, 32769),
+                                      (1, 65537), (1, (1 << 17) + 1), (1, 1 << 20)])
+def test_sample_perm_gathering_forms(slices, n):
+    """Both ways of gathering a bucket, on both sides of the line between them (6 million keys formed by the scan) and at
+    odd piece, bucket and slice counts: bit for bit the oracle's argsort."""
+    from oracle import perm_sampler as ps
+    print(f"case sample_perm {slices} x {n}", flush=True)
+    ref = ps.sample_perm(31, 4, 1, slices, n)
+    for workspace in (False, True):
+        _, perm = sample(1, slices, 1, slices, n, 31, 4, workspace)
+        assert np.array_equal(perm.cpu().numpy(), ref), f"workspace={workspace}"
