@@ -153,3 +153,16 @@ def test_full_size_caches(Hq, Hkv, n, length):
     """The cache of the headline prefill shape (Qwen3-8B heads, 32K rows) and of the long one (32/4 heads, 128K
     rows), every output checked against the oracle."""
     run_decode(1, Hq, Hkv, n, 128, length, poison=False)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,d,length", [
+    (1, 8, 2, 16384, 128, 64),     # one chunk, two of them, and the longest run of 64-row chunks the capacity allows
+    (1, 8, 2, 16384, 128, 65),
+    (1, 8, 2, 16384, 64, 8191),
+    (1, 8, 2, 16384, 64, 16384),
+    (2, 4, 1, 5000, 128, 2049),    # chunks of 64 x 1 .. 64 x 8 rows, the last one partly filled
+    (70, 8, 8, 700, 64, 699),      # more head groups than wanted workgroups: chunks of 512 rows
+    (1, 2, 1, 130000, 128, 129999),  # more chunks than one round of the merge takes
+])
+def test_chunks_follow_the_rows_in_use(B, Hq, Hkv, n, d, length):
+    run_decode(B, Hq, Hkv, n, d, length, seed=length)
