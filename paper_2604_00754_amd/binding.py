@@ -109,11 +109,18 @@ def _ptr(t):
     if t is None:
         return None
     assert t.is_contiguous(), "libsa takes contiguous tensors"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_raw_stream, _device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream) if torch.cuda.is_available() else None
+    """The current stream of the current device as the integer ctypes passes on.  Asked of torch's C layer: the Stream
+    object that torch.cuda.current_stream() builds takes 2.8 us, as long as a launch, against 0.2."""
+    if torch.cuda.is_initialized():
+        return _raw_stream(_device())
+    return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
 
 
 def _check(status, what):
