@@ -65,6 +65,8 @@ __host__ __device__ inline int perm_slice_index(int perm_B, int perm_H, int b, i
 hipError_t launch_fwd_f32(const Pass& p, hipStream_t st);
 hipError_t launch_bwd_f32(const Pass& p, hipStream_t st);
 hipError_t launch_fwd_mfma_bf16(const Pass& p, hipStream_t st);
+bool fwd_sorted_serves(const Pass& p);  // sa_fwd_sorted.hip: can it, and is it the faster one
+hipError_t launch_fwd_sorted_bf16(const Pass& p, hipStream_t st);
 hipError_t launch_bwd_mfma_bf16(const Pass& p, hipStream_t st);
 
 hipError_t launch_permuted_copy_bf16(const Pass& p, hipStream_t st);

@@ -588,6 +588,7 @@ hipError_t launch_fwd_mfma_bf16(const Pass& p, hipStream_t st) {
   if (p.win.circular && p.win.L + p.win.R + 1 > p.n) return hipErrorInvalidValue;
   if ((long)p.n * p.d * 2 >= (1L << 31)) return hipErrorNotSupported;  // 32-bit row offsets inside a head
   if (p.gate_mode && (!p.gate_this || !p.gate_other || !p.Y_other || !p.Yout)) return hipErrorInvalidValue;
+  if (fwd_sorted_serves(p)) return launch_fwd_sorted_bf16(p, st);
   if (p.d == 64) return launch_t<64>(p, st);
   if (p.d == 128) return launch_t<128>(p, st);
   return hipErrorNotSupported;

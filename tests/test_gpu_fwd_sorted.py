@@ -1,0 +1,77 @@
+"""sa_fwd where the sorted-list kernel serves (d = 128, causal, four query heads of a KV group on one permutation, windows of
+448 slots and more): groups of 128 slots cut into quarters, lists of the band, their sections and the fallbacks, against the
+fp64 oracle.  Bars: the 2e-2 / 5e-3 of the bf16 configuration (the arithmetic of a score and of a sum is the same as in the
+kernel for short calls)."""
+import numpy as np
+import pytest
+import torch
+
+from tests import gpu_util as U
+from tests.test_gpu_fwd import run_fwd
+
+pytestmark = pytest.mark.gpu
+
+CIRC, LIN, ONE = 0, 1, 2
+
+CASES = [
+    # B, Hq, Hkv, n, w, window, perm_B
+    (4, 8, 2, 1024, 512, CIRC, 1),    # 256 workgroups: the fewest it is taken for
+    (4, 8, 2, 1025, 449, CIRC, 4),    # a group of one slot
+    (4, 8, 2, 1055, 640, ONE, 1),     # of 31
+    (4, 8, 2, 1057, 700, LIN, 1),     # of 33: a quarter of one query
+    (4, 8, 1, 1151, 511, CIRC, 4),    # of 127; two head sets of one KV head
+    (5, 4, 1, 1700, 1023, CIRC, 1),   # five band slots per thread
+    (5, 4, 1, 1700, 1800, CIRC, 1),   # the band wraps around the ring: every slot twice in a group's band
+    (4, 8, 2, 2100, 1920, LIN, 1),    # the longest band (2047 slots of 2048, clipped at both ends)
+    (4, 8, 2, 2100, 1921, ONE, 1),    # one slot over what a list holds: the other kernel
+    (9, 12, 3, 300, 600, CIRC, 1),    # window longer than the sequence
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"B{c[0]}H{c[1]}-{c[2]}n{c[3]}w{c[4]}win{c[5]}pb{c[6]}")
+def test_sorted_forward(case):
+    B, Hq, Hkv, n, w, window, perm_B = case
+    run_fwd(B, Hq, Hkv, n, 128, w, window, 1, "bf16", perm_B=perm_B, seed=n + w)
+
+
+def test_sorted_forward_scores_outside_fp32_exponentials():
+    """Logits of about +-150 in some rows send their workgroup through its list again in the online form; later keys that
+    outscore the visible ones (K grows with the position) must not show in either form."""
+    run_fwd(4, 8, 2, 1100, 128, 500, CIRC, 1, "bf16", seed=3, k_growth=10.0)
+    from oracle import binding as orc
+    from paper_2604_00754_amd import binding as sa
+    wl, x = U.make_case(4, 8, 2, 1030, 128, 480, seed=8)
+    from paper_2604_00754_amd import synth
+    scale = np.ones((1, 1, 1030, 1), np.float32)
+    scale[:, :, 100:400] = 40.0
+    x["Q"] = synth.round_to_bf16(x["Q"] * scale)
+    Yr, Lr = orc.sa_fwd(U.orc_desc(wl, CIRC, 1), x["Q"], x["K"], x["V"], x["perm"])
+    Q, K, V = (U.to_dev(x[k], "bf16") for k in "QKV")
+    Y, L = torch.empty_like(Q), torch.empty(Q.shape[:3], device=U.DEV, dtype=torch.float32)
+    sa.sa_fwd(U.sa_desc(wl, CIRC, 1), Q, K, V, torch.from_numpy(x["perm"]).to(U.DEV), Y, L)
+    torch.cuda.synchronize()
+    U.assert_close(U.to_np64(Y), Yr, "bf16", "Y")
+    # |LSE| reaches 150: fp32 keeps 1e-5 of it beside the 4e-3 of the bf16 row sums
+    assert np.abs(U.to_np64(L) - Lr).max() <= 4e-3 + 1e-5 * np.abs(Lr).max()
+
+
+@pytest.mark.parametrize("interleaved", [0, 1])
+def test_sorted_forward_with_rotation(interleaved):
+    """The rotation of Q inside the kernel (table rows through LDS) against the pass over Q in memory.  The two may contract
+    a c - b s into a multiply-add on either side, which moves a product by half an ulp of fp32; where the sum lies that close to the
+    middle of two bf16 values (about one value in 2^15) it rounds to the other one.  A score is a sum of 128 products of such
+    values, so the outputs agree far inside the bars of the bf16 configuration: a tenth of them is asked for."""
+    from paper_2604_00754_amd import binding as sa
+    wl, x = U.make_case(4, 8, 2, 1100, 128, 512, seed=5)
+    Q, K, V = (U.to_dev(x[k], "bf16") for k in "QKV")
+    perm = torch.from_numpy(x["perm"]).to(U.DEV)
+    d = U.sa_desc(wl, CIRC, 1)
+    table = torch.empty(wl.n, 64, 2, device=U.DEV)
+    sa.sa_rope_table(wl.n, 128, 1e4, 7, table)
+    Y0, Y1, Qr = torch.empty_like(Q), torch.empty_like(Q), torch.empty_like(Q)
+    sa.sa_rope(d, Q, None, table, Qr, None, interleaved=interleaved)
+    sa.sa_fwd(d, Qr, K, V, perm, Y0)
+    sa.sa_fwd_rope(d, Q, K, V, perm, table, Y1, interleaved=interleaved)
+    torch.cuda.synchronize()
+    max_abs, rel = U.errors(U.to_np64(Y1), U.to_np64(Y0))
+    assert max_abs <= 2e-2 and rel <= 5e-4, (max_abs, rel)
