@@ -328,23 +328,6 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(Prep p) {
     ra = fmaf(dy[k], ya[k], ra);
     rb = fmaf(dy[k], yb[k], rb);
   }
-  if (p.fold) {  // one gate per row: E_x, LSE_x - ln g_x, dgamma_x; no copy of dY
-    ra = group_sum<LPR>(ra);
-    rb = group_sum<LPR>(rb);
-    if (valid && sub == 0) {
-      const float xa = load_gate(p.gate_a, r, p.gate_f32), xb = load_gate(p.gate_b, r, p.gate_f32);
-      // -ln sigmoid(x) = ln(1 + e^-x), evaluated without cancellation on either side
-      const float na = xa > 0.f ? log1pf(__expf(-xa)) : -xa + log1pf(__expf(xa));
-      const float nb = xb > 0.f ? log1pf(__expf(-xb)) : -xb + log1pf(__expf(xb));
-      p.D_a[r] = ra;
-      p.D_b[r] = rb;
-      p.L_a[r] = p.lse_a[r] + na;
-      p.L_b[r] = p.lse_b[r] + nb;
-      store_gate(p.dgate_a, r, p.gate_f32, ga[0] * (1.f - ga[0]) * ra);
-      store_gate(p.dgate_b, r, p.gate_f32, gb[0] * (1.f - gb[0]) * rb);
-    }
-    return;
-  }
   sa = group_sum<LPR>(sa);
   sb = group_sum<LPR>(sb);
   if (valid && sub == 0) {
@@ -387,8 +370,66 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(Prep p) {
   }
 }
 
+// The same for bf16 and one gate per row with the gate folded into the per-row scalars: E_x = rowsum(dY o Y_x),
+// LSE_x - ln g_x, dgamma_x; no copy of dY.  Reads three rows and writes six scalars a row: bound by memory.  A lane group takes
+// U rows (12 loads of 16 bytes in flight a lane at U = 4) and its lanes share the logarithms and the stores, one (row, branch)
+// each, so that a wave stores 32 neighbouring scalars of both branches with one instruction; with one row per group and one
+// lane in eight storing, B4 H16 n8192 d64 took 66 us (3.3 TB/s), now 37 us (5.8 TB/s).
+template <int LPR>
+__global__ __launch_bounds__(256) void bwd_fold_kernel(const Prep p) {
+  constexpr int U = LPR / 2;      // rows per group: two branches x U rows = its lanes
+  constexpr int GPW = 64 / LPR;   // groups per wave
+  const int lane = threadIdx.x & 63, sub = lane % LPR, grp = lane / LPR;
+  const long wave_row0 = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * (U * GPW);
+  u32x4 dy[U], ya[U], yb[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {  // rows past the last one: the last one again, never stored
+    const long row = wave_row0 + u * GPW + grp;
+    const size_t off = (size_t)(row < p.rows ? row : p.rows - 1) * p.d + (size_t)sub * 8;
+    dy[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(p.dY) + off);
+    ya[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(p.Y_a) + off);
+    yb[u] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(p.Y_b) + off);
+  }
+  // this lane's share of the rest: branch a or b of row `mine`
+  const bool is_b = sub >= U;
+  const int own = sub % U;
+  const long mine = wave_row0 + own * GPW + grp;
+  const bool valid = mine < p.rows;
+  const size_t r = valid ? (size_t)mine : 0;
+  const float x = load_gate(is_b ? p.gate_b : p.gate_a, r, p.gate_f32);
+  const float lse = (is_b ? p.lse_b : p.lse_a)[r];
+  float e = 0.f;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    float ra = 0.f, rb = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      ra = fmaf(bf16hi(dy[u][k]), bf16hi(ya[u][k]), fmaf(bf16lo(dy[u][k]), bf16lo(ya[u][k]), ra));
+      rb = fmaf(bf16hi(dy[u][k]), bf16hi(yb[u][k]), fmaf(bf16lo(dy[u][k]), bf16lo(yb[u][k]), rb));
+    }
+    ra = group_sum<LPR>(ra);
+    rb = group_sum<LPR>(rb);
+    if (own == u) e = is_b ? rb : ra;
+  }
+  if (!valid) return;
+  const float g = sigmoidf_exact(x);
+  // -ln sigmoid(x) = ln(1 + e^-x), evaluated without cancellation on either side
+  const float nl = x > 0.f ? log1pf(__expf(-x)) : -x + log1pf(__expf(x));
+  (is_b ? p.D_b : p.D_a)[r] = e;
+  (is_b ? p.L_b : p.L_a)[r] = lse + nl;
+  store_gate(is_b ? p.dgate_b : p.dgate_a, r, p.gate_f32, g * (1.f - g) * e);
+}
+
 template <bool BF16, int LPR>
 hipError_t launch_prepare_t(const Prep& p, hipStream_t st) {
+  if (p.fold) {
+    if constexpr (BF16) {
+      const long per_block = 4 * 32;  // rows: LPR / 2 rows of 64 / LPR groups in each of 4 waves
+      hipLaunchKernelGGL(bwd_fold_kernel<LPR>, dim3((unsigned)((p.rows + per_block - 1) / per_block)), dim3(256), 0, st, p);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+  }
   const long threads = (long)p.rows * LPR;
   const unsigned blocks = (unsigned)((threads + 255) / 256);
   hipLaunchKernelGGL((bwd_prepare_kernel<BF16, LPR>), dim3(blocks), dim3(256), 0, st, p);

@@ -142,6 +142,14 @@ def test_gated_bwd_bf16(per_dim, gate_dtype):
     run_gated_bwd(2, 4, 2, 700, 64, 128, "bf16", per_dim=per_dim, gate_dtype=gate_dtype, seed=40)
 
 
+@pytest.mark.parametrize("n", [1, 3, 33, 127, 129])
+def test_gated_bwd_bf16_row_counts_around_workgroup_edges(n):
+    """One gate per row: rows (heads x n) below, at and past the 32 rows of a wave and the 128 of a workgroup of the
+    pass that folds the gates into the per-row scalars."""
+    run_gated_bwd(1, 1, 1, n, 64, 16, "bf16", seed=42)
+    run_gated_bwd(1, 3, 3, n, 128, 16, "bf16", gate_dtype="bf16", seed=43)
+
+
 def test_gated_bwd_bf16_d128():
     run_gated_bwd(1, 4, 1, 500, 128, 96, "bf16", seed=41)
 
