@@ -90,11 +90,12 @@ __device__ __forceinline__ u32x4 load_row_chunk_once(const bf16_t* head, int row
 enum { CAUSAL_NONE = 0, CAUSAL_I32 = 1, CAUSAL_I16 = 2 };
 
 // PERM = false: identity permutation (plain windowed attention); no index loads are generated.
-// GATED = true: the second branch of the gated forward, with the gated sum of Eq. 5 in the epilogue; it needs
-// more registers after the tile loop, so at d = 64 it runs three workgroups per CU where the plain kernel
-// runs four.
+// GATED = true: the second branch of the gated forward, with the gated sum of Eq. 5 in the epilogue.  At d = 64 that fits
+// the four workgroups per CU of the plain kernel because the epilogue takes its lane numbers from copies the optimiser cannot
+// trace (131 -> 123 registers; three workgroups per CU: 110 against 99 us at B4 H16 n8192 w256); at d = 128 three
+// workgroups per CU spill 62 registers, so it runs two.
 template <int D, bool PERM, int CAUSAL, bool GATED>
-__global__ __launch_bounds__(NT, D == 64 ? (GATED ? 3 : FWD_WGS64) : (GATED ? 2 : FWD_WGS128)) void fwd_mfma_bf16_kernel(const Pass p, const int num_qt, const long total_work,
+__global__ __launch_bounds__(NT, D == 64 ? FWD_WGS64 : (GATED ? 2 : FWD_WGS128)) void fwd_mfma_bf16_kernel(const Pass p, const int num_qt, const long total_work,
                                                               const int hshift) {
   using C = Cfg<D>;
   constexpr int BN = C::BN, NB = C::NB;
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(NT, D == 64 ? (GATED ? 3 : FWD_WGS64) : (GATED ? 2 
   bf16_t* Os = reinterpret_cast<bf16_t*>(smem) + wave * 32 * C::QSTR;
   bool area_free = true;  // the barrier that ended the tile loop has freed the staging area for its first use
   auto stage_and_store = [&](const f32x16* acc, void* dst_tensor) {
-    if (!area_free) __syncthreads();  // the previous staging pass is stored
+    if (!area_free) wave_lds_sync();  // the previous staging pass is stored (the rows are this wave's own)
     area_free = false;
     int le = lane;  // the lane's staging address is formed here, from a copy the optimiser cannot trace back to
     asm volatile("" : "+v"(le));  // the prologue's (equal) one, which it would otherwise keep across the tile loop
@@ -484,6 +485,7 @@ __global__ __launch_bounds__(NT, D == 64 ? (GATED ? 3 : FWD_WGS64) : (GATED ? 2 
         *reinterpret_cast<u32x2*>(mine + 32 * db + 8 * mq) = w;
       }
     wave_lds_sync();  // the staging rows are this wave's own
+    const int lane = le, chunk16 = le % C::CPR;
     int dst[NP];
 #pragma unroll
     for (int pass = 0; pass < NP; ++pass) dst[pass] = rowstash[wave * 32 + pass * C::WRPP + lane / C::CPR];
@@ -502,6 +504,9 @@ __global__ __launch_bounds__(NT, D == 64 ? (GATED ? 3 : FWD_WGS64) : (GATED ? 2 
   if (GATED && p.gate_mode) {
     // Eq. 5: Y = sig(gamma_this) * Y_this + sig(gamma_other) * Y_other, formed in fp32: this branch enters
     // with its fp32 accumulators, the other one as the bf16 tensor it was stored as
+    int lg = lane;  // lane numbers from a copy the optimiser cannot trace to the prologue's, as in the staging above
+    asm volatile("" : "+v"(lg));
+    const int c32 = lg & 31, g2 = lg >> 5, chunk16 = lg % C::CPR, lane = lg;
     const size_t r = s_w0 + c32 < n ? my_row : head_row0;
     float ga = 0.f, gb = 0.f;
     if (!p.gate_per_dim) {
