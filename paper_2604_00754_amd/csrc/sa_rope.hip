@@ -5,8 +5,8 @@
 //
 // Two kernels.  The table kernel evaluates (cos, sin) of every (position, pair) once, in fp64 (the
 // angle reaches 10^5 rad at long prefill, beyond what an fp32 product resolves), and stores them as
-// fp32.  The apply kernel streams rows: one thread owns the same 8 pairs of one position for several
-// heads, keeps their 16 table values in registers, and reads / writes 2 x 16 B (bf16) per head.
+// fp32.  The apply kernel streams rows: one thread owns the same 8 elements of one position for several
+// heads, keeps the table values of their pairs in registers, and reads / writes 16 B (bf16) per head.
 // HBM-bound: 2 * sizeof(T) bytes per element, the table stays in cache.
 #include "sa_common.h"
 #include "sa_device.h"
@@ -62,65 +62,63 @@ struct Row8<float> {
   }
 };
 
-// X, Xout: [heads][n][d].  Thread (m, c) owns pairs 8c .. 8c+7 of position m:
-//   split halves: elements 8c..8c+7 (first of each pair) and d/2 + 8c .. +7 (second),
-//   adjacent pairs: elements 16c .. 16c+15, pair 8c+j = (16c+2j, 16c+2j+1).
+// X, Xout: [heads][n][d].  Thread (m, c) owns elements 8c .. 8c+7 of position m, so that the threads of a row read and write it as
+// one contiguous piece (a thread that owned both halves of its pairs touched half rows, 128-byte lines asked for twice: 16 x 16
+// heads, n = 4096, d = 64 59 against 47 us = 5.8 TB/s; 4 heads, n = 131 072, d = 128 58 against 52 us).
+//   adjacent pairs: they are pairs 4c .. 4c+3;
+//   split halves: the other members of their pairs are the 8 elements of the thread half a row away in the wave.
 template <typename T, bool INTERLEAVED>
 __global__ __launch_bounds__(ROPE_THREADS) void rope_apply_kernel(const T* __restrict__ X, T* __restrict__ Xout,
                                                                    const float2* __restrict__ table, int heads, int n,
                                                                    int d, int inverse) {
-  const int cpr = d / 16;  // threads per row
+  const int cpr = d / 8;  // threads per row: 8 or 16, whole rows to a wave
   const long t = (long)blockIdx.x * ROPE_THREADS + threadIdx.x;
-  if (t >= (long)n * cpr) return;
-  const int m = (int)(t / cpr), c = (int)(t % cpr);
-  float cs[8], sn[8];
+  const bool live = t < (long)n * cpr;  // (every lane takes part in the exchange)
+  const int m = live ? (int)(t / cpr) : n - 1, c = (int)(t % cpr);
+  constexpr int NPAIR = INTERLEAVED ? 4 : 8;
+  const bool second = !INTERLEAVED && c >= cpr / 2;  // holds the second members of its pairs
+  float cs[NPAIR], sn[NPAIR];
   {
-    const float4* tp = reinterpret_cast<const float4*>(table + (size_t)m * (d / 2) + 8 * c);
+    const float4* tp = reinterpret_cast<const float4*>(table + (size_t)m * (d / 2) + NPAIR * (second ? c - cpr / 2 : c));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NPAIR / 2; ++j) {
       const float4 v = tp[j];
       cs[2 * j] = v.x; sn[2 * j] = v.y;
       cs[2 * j + 1] = v.z; sn[2 * j + 1] = v.w;
     }
-    if (inverse) {
+    if ((inverse != 0) != second) {  // first members: u cos - v sin; second: v cos + u sin; the inverse turns the signs
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sn[j] = -sn[j];
+      for (int j = 0; j < NPAIR; ++j) sn[j] = -sn[j];
     }
   }
   const int h0 = blockIdx.y * ROPE_HEADS_PER_BLOCK;
   const int h1 = min(h0 + ROPE_HEADS_PER_BLOCK, heads);
-  const int off_a = INTERLEAVED ? 16 * c : 8 * c;
-  const int off_b = INTERLEAVED ? 16 * c + 8 : d / 2 + 8 * c;
+#pragma unroll 4
   for (int h = h0; h < h1; ++h) {
-    const size_t row = ((size_t)h * n + m) * d;
-    float u[8], v[8], ou[8], ov[8];
-    Row8<T>::load(X + row + off_a, u);
-    Row8<T>::load(X + row + off_b, v);
+    const size_t at = ((size_t)h * n + m) * d + 8 * c;
+    float x[8], o[8];
+    Row8<T>::load(X + at, x);
     if (INTERLEAVED) {
-      // u = elements 16c..16c+7 = pairs 8c..8c+3, v = pairs 8c+4..8c+7
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        ou[2 * j] = u[2 * j] * cs[j] - u[2 * j + 1] * sn[j];
-        ou[2 * j + 1] = u[2 * j] * sn[j] + u[2 * j + 1] * cs[j];
-        ov[2 * j] = v[2 * j] * cs[4 + j] - v[2 * j + 1] * sn[4 + j];
-        ov[2 * j + 1] = v[2 * j] * sn[4 + j] + v[2 * j + 1] * cs[4 + j];
+        o[2 * j] = x[2 * j] * cs[j] - x[2 * j + 1] * sn[j];
+        o[2 * j + 1] = x[2 * j] * sn[j] + x[2 * j + 1] * cs[j];
       }
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        ou[j] = u[j] * cs[j] - v[j] * sn[j];
-        ov[j] = u[j] * sn[j] + v[j] * cs[j];
+        const float other = __shfl_xor(x[j], cpr / 2);
+        o[j] = x[j] * cs[j] - other * sn[j];
       }
     }
-    Row8<T>::store(Xout + row + off_a, ou);
-    Row8<T>::store(Xout + row + off_b, ov);
+    if (live) Row8<T>::store(Xout + at, o);
   }
 }
 
 template <typename T>
 hipError_t launch_apply(const void* X, void* Xout, const float* table, int heads, int n, int d, int interleaved,
                         int inverse, hipStream_t st) {
-  const long threads = (long)n * (d / 16);
+  const long threads = (long)n * (d / 8);
   dim3 grid((unsigned)((threads + ROPE_THREADS - 1) / ROPE_THREADS),
             (unsigned)((heads + ROPE_HEADS_PER_BLOCK - 1) / ROPE_HEADS_PER_BLOCK));
   const float2* tb = reinterpret_cast<const float2*>(table);

@@ -64,6 +64,15 @@ def test_rope_apply(dtype, d, interleaved):
     run_apply(2, 4, 2, 301, d, dtype, interleaved, seed=d + interleaved)   # ragged last block, GQA
 
 
+@pytest.mark.parametrize("n", [3, 15, 17, 31, 33])
+@pytest.mark.parametrize("interleaved", [0, 1])
+def test_rope_row_counts_around_workgroup_edges(n, interleaved):
+    """A workgroup holds 32 (d = 64) or 16 (d = 128) whole rows, a row's halves in lanes of one wave; in place, so that a
+    lane must have its partner's elements before either is overwritten."""
+    for d, dtype in ((64, "bf16"), (128, "bf16"), (64, "f32"), (128, "f32")):
+        run_apply(1, 5, 1, n, d, dtype, interleaved, in_place=True, seed=20 + n)
+
+
 def test_rope_in_place_many_heads_and_late_positions():
     run_apply(1, 9, 3, 130, 64, "bf16", 0, in_place=True, seed=3)          # head count not a multiple of 4
     run_apply(1, 2, 1, 200, 128, "bf16", 0, base=1e6, pos0=131072 - 200, seed=4)
