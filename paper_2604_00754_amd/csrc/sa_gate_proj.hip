@@ -43,8 +43,11 @@ struct GateProj {
   const void* W_x[2];  // [dm, dm] row-major, row = output feature
   void* G_x[2];        // optional: gate values sigmoid(logit) [B,Hq,n,d]
   void* Y;             // [B,Hq,n,d]
-  const void* E1;      // backward-input mode: Y = acc + E1 * E2 (E1 = dY, E2 = g_x), both [B,Hq,n,d]
-  const void* E2;
+  // backward-input mode: the branches are independent parts of the work list, Y_out[x] = acc + E1 * E2[x] (E1 = dY,
+  // E2[x] = g_x), all [B,Hq,n,d]
+  void* Y_out[2];
+  const void* E1;
+  const void* E2[2];
   int B, Hq, n, d;
 };
 
@@ -60,7 +63,9 @@ __global__ __launch_bounds__(GNT, 2) void gate_proj_fwd_bf16_kernel(const GatePr
   const int ft = (int)(work % num_ft);
   long rest = work / num_ft;
   const int tt = (int)(rest % num_tt);
-  const int b = (int)(rest / num_tt);
+  rest /= num_tt;
+  const int b = (int)(rest % p.B);
+  const int only = MODE == GP_BWD_INPUT ? (int)(rest / p.B) : 0;  // backward-input mode: this workgroup's branch
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -159,8 +164,9 @@ __global__ __launch_bounds__(GNT, 2) void gate_proj_fwd_bf16_kernel(const GatePr
     return *reinterpret_cast<const u32x2*>(ostage + (32 * ti + c32) * OSTR + 32 * fi + 8 * q + 4 * g2);
   };
 
-  const int branches = p.Y_x[1] ? 2 : 1;
-  for (int x = 0; x < branches; ++x) {
+  const int first = MODE == GP_BWD_INPUT ? only : 0;
+  const int last = MODE == GP_BWD_INPUT ? only : (p.Y_x[1] ? 1 : 0);
+  for (int x = first; x <= last; ++x) {
     const bf16_t* Yx = reinterpret_cast<const bf16_t*>(p.Y_x[x]);
     const bf16_t* Wx = reinterpret_cast<const bf16_t*>(p.W_x[x]);
     f32x16 acc[2][2];
@@ -202,7 +208,7 @@ __global__ __launch_bounds__(GNT, 2) void gate_proj_fwd_bf16_kernel(const GatePr
     // (backward-input mode: out = product + dY * g_x)
     bf16_t* Gx = reinterpret_cast<bf16_t*>(p.G_x[x]);
     const bf16_t* E1 = reinterpret_cast<const bf16_t*>(p.E1);
-    const bf16_t* E2 = reinterpret_cast<const bf16_t*>(p.E2);
+    const bf16_t* E2 = reinterpret_cast<const bf16_t*>(p.E2[x]);
     // step nk-2 left features o0 .. o0+63 of the token tile in its buffer, step nk-1 the next 64: this wave's 64
     // features are in the buffer of step nk-2+wn (the output staging area below lies on the weight tiles only)
     const bf16_t* Ay = reinterpret_cast<const bf16_t*>(smem + ((nk - 2 + wn) & 1) * GBUF_BYTES) + (64 * wm + c32) * GSTR + 4 * g2;
@@ -227,15 +233,10 @@ __global__ __launch_bounds__(GNT, 2) void gate_proj_fwd_bf16_kernel(const GatePr
     }
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti) {
-      const int token = i0 + 64 * wm + 32 * ti + c32;
-      const bool live = token < n;
-      const int tk = live ? token : n - 1;
 #pragma unroll
       for (int fi = 0; fi < 2; ++fi)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int o = o0 + 64 * wn + 32 * fi + 8 * q + 4 * g2;  // first of four consecutive features
-          const size_t at = (((size_t)b * H + o / D) * n + tk) * D + o % D;
           if (MODE == GP_FORWARD) {
             const u32x2 y = *reinterpret_cast<const u32x2*>(Ay + 32 * ti * GSTR + 32 * fi + 8 * q);
             const float yv[4] = {bf16lo(y[0]), bf16hi(y[0]), bf16lo(y[1]), bf16hi(y[1])};
@@ -275,14 +276,29 @@ __global__ __launch_bounds__(GNT, 2) void gate_proj_fwd_bf16_kernel(const GatePr
         w[1] = pack_bf16(out[fi][ti][4 * q + 2], out[fi][ti][4 * q + 3]);
         stage_put(fi, ti, q, w);
       }
-  stage_flush(reinterpret_cast<bf16_t*>(p.Y));
+  stage_flush(reinterpret_cast<bf16_t*>(MODE == GP_BWD_INPUT ? p.Y_out[only] : p.Y));
 }
 
 
-// dz = dY * y * g * (1 - g), rounded to bf16; 8 elements per thread.
-__global__ __launch_bounds__(256) void gate_dz_bf16_kernel(const uint16_t* __restrict__ dY, const uint16_t* __restrict__ Yx,
-                                                            const uint16_t* __restrict__ Gx, uint16_t* __restrict__ dz,
-                                                            const size_t vecs) {
+// The backward's launches serve both branches at once (blockIdx.y, .z or a part of the work list): per branch the three small
+// passes cost a launch of 5 us each, and short calls leave the chip idle in the products.
+struct GateBwd {
+  const uint16_t* Y_x[2];
+  const uint16_t* W_x[2];
+  const uint16_t* G_x[2];
+  const uint16_t* dY;
+  uint16_t* dz[2];
+  uint16_t* Wt[2];
+  float* dWf[2];
+  uint16_t* dW[2];
+};
+
+// dz = dY * y * g * (1 - g), rounded to bf16; 8 elements per thread.  blockIdx.y = branch.
+__global__ __launch_bounds__(256) void gate_dz_bf16_kernel(const GateBwd p, const size_t vecs) {
+  const uint16_t* __restrict__ dY = p.dY;
+  const uint16_t* __restrict__ Yx = p.Y_x[blockIdx.y];
+  const uint16_t* __restrict__ Gx = p.G_x[blockIdx.y];
+  uint16_t* __restrict__ dz = p.dz[blockIdx.y];
   size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * 256;
   for (; i < vecs; i += stride) {
@@ -298,11 +314,17 @@ __global__ __launch_bounds__(256) void gate_dz_bf16_kernel(const uint16_t* __res
   }
 }
 
-// Wt[k][o] = W[o][k] for a square bf16 matrix (dm a multiple of 64): 64 x 64 tiles through LDS.
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __restrict__ W, uint16_t* __restrict__ Wt, const int dm) {
+// Wt[k][o] = W[o][k] for a square bf16 matrix (dm a multiple of 64): 64 x 64 tiles through LDS; the same tile of the fp32 sums
+// for dW is set to zero.  blockIdx.z = branch.
+__global__ __launch_bounds__(256) void gate_bwd_setup_kernel(const GateBwd p, const int dm) {
   __shared__ uint16_t tile[64][66];
+  const uint16_t* __restrict__ W = p.W_x[blockIdx.z];
+  uint16_t* __restrict__ Wt = p.Wt[blockIdx.z];
+  float* __restrict__ sums = p.dWf[blockIdx.z];
   const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
   for (int e = threadIdx.x; e < 64 * 64; e += 256) tile[e / 64][e % 64] = W[(size_t)(r0 + e / 64) * dm + c0 + e % 64];
+  for (int e = threadIdx.x; e < 64 * 16; e += 256)
+    *reinterpret_cast<f32x4*>(sums + (size_t)(r0 + e / 16) * dm + c0 + 4 * (e % 16)) = f32x4{0.f, 0.f, 0.f, 0.f};
   __syncthreads();
   for (int e = threadIdx.x; e < 64 * 64; e += 256) Wt[(size_t)(c0 + e / 64) * dm + r0 + e % 64] = tile[e % 64][e / 64];
 }
@@ -314,7 +336,10 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __r
 // gets the same 8 tokens of one feature column for the A operand (dz^T) and the B operand (y).
 // Steps of 32 tokens, four buffers, three steps in flight.  Tokens past the chunk's end are zeroed in
 // the dz tile after it has landed.
-constexpr int WCHUNK = 4096;  // tokens per workgroup
+// Tokens per workgroup: WCHUNK, halved down to WCHUNK_LEAST until the launch has WTARGET workgroups (two per
+// CU): 4096 tokens of 12 heads were 36 workgroups a branch (layer forward + backward, with the branches in one launch, 267 -> 214 us).
+constexpr int WCHUNK = 4096, WCHUNK_LEAST = 256;
+constexpr long WTARGET = 512;
 constexpr int WSTEP = 32;
 constexpr int WSTAGES = 4;
 constexpr int WTILE_BYTES = WSTEP * 128 * 2;  // one operand, one step
@@ -322,9 +347,8 @@ constexpr int WSTAGE_BYTES = 2 * WTILE_BYTES;
 constexpr int WLOADS_PER_STAGE = 4;           // instructions per thread: 2 rows of 16 tokens x 2 operands
 
 template <int D>
-__global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const bf16_t* __restrict__ dz, const bf16_t* __restrict__ Yx,
-                                                               float* __restrict__ dW, const int B, const int H, const int n,
-                                                               const int num_ft, const int chunks_per_b, const long total_work) {
+__global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, const int B, const int H, const int n, const int num_ft,
+                                                               const int chunk, const int chunks_per_b, const long total_work) {
   __shared__ __attribute__((aligned(16))) char smem[WSTAGES * WSTAGE_BYTES];
   const long work = xcd_work_index(total_work);
   if (work < 0) return;
@@ -333,14 +357,18 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const bf16_t* __re
   const int ot = (int)(rest % num_ft);  // output-feature tile (rows of dW)
   rest /= num_ft;
   const int ch = (int)(rest % chunks_per_b);
-  const int b = (int)(rest / chunks_per_b);
+  rest /= chunks_per_b;
+  const int b = (int)(rest % B), x = (int)(rest / B);  // x = branch
+  const bf16_t* __restrict__ dz = reinterpret_cast<const bf16_t*>(p.dz[x]);
+  const bf16_t* __restrict__ Yx = reinterpret_cast<const bf16_t*>(p.Y_x[x]);
+  float* __restrict__ dW = p.dWf[x];
   const int dm = H * D;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wo = wave & 1, wk = wave >> 1;
   const int g2 = lane >> 5, c32 = lane & 31;
-  const int t_begin = ch * WCHUNK, t_end = min(t_begin + WCHUNK, n);
+  const int t_begin = ch * chunk, t_end = min(t_begin + chunk, n);
   const int nsteps = (t_end - t_begin + WSTEP - 1) / WSTEP;
 
   // loader: one instruction of a wave fills 4 token rows (256 bytes each) of a tile; the lane delivers
@@ -426,7 +454,10 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const bf16_t* __re
       }
 }
 
-__global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float* __restrict__ src, uint16_t* __restrict__ dst, const size_t pairs) {
+// dW in bf16 from its fp32 sums.  blockIdx.y = branch.
+__global__ __launch_bounds__(256) void gate_dw_round_kernel(const GateBwd p, const size_t pairs) {
+  const float* __restrict__ src = p.dWf[blockIdx.y];
+  uint16_t* __restrict__ dst = p.dW[blockIdx.y];
   size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * 256;
   for (; i < pairs; i += stride) {
@@ -439,7 +470,7 @@ template <int MODE>
 hipError_t launch_gemm(const GateProj& p, hipStream_t st) {
   const long dm = (long)p.Hq * p.d;
   const int num_tt = (p.n + TM - 1) / TM, num_ft = (int)(dm / TN);
-  const long total = (long)num_tt * num_ft * p.B;
+  const long total = (long)num_tt * num_ft * p.B * (MODE == GP_BWD_INPUT && p.Y_x[1] ? 2 : 1);
   const long blocks = xcd_grid_blocks(total);
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
   if (p.d == 64) hipLaunchKernelGGL((gate_proj_fwd_bf16_kernel<64, MODE>), dim3((unsigned)blocks), dim3(GNT), 0, st, p, num_tt, num_ft, total);
@@ -476,42 +507,49 @@ size_t gate_proj_bwd_workspace_bytes(int B, int Hq, int n, int d, bool dual) {
   return (dual ? 2 : 1) * ((per_branch + 255) / 256 * 256);
 }
 
-// One branch: dz, W^T, dy_x = dY * g_x + dz W_x, dW_x = dz^T y_x.
-static hipError_t gate_proj_bwd_branch(int B, int Hq, int n, int d, const void* Yx, const void* Wx, const void* Gx,
-                                       const void* dY, void* dYx, void* dWx, char* ws, hipStream_t st) {
-  const size_t dm = (size_t)Hq * d, act = (size_t)B * Hq * n * d;
-  uint16_t* dz = reinterpret_cast<uint16_t*>(ws);
-  uint16_t* Wt = reinterpret_cast<uint16_t*>(ws + act * 2);
-  float* dWf = reinterpret_cast<float*>(ws + act * 2 + dm * dm * 2);
-  hipLaunchKernelGGL(gate_dz_bf16_kernel, dim3(capped_blocks(act / 8, 256)), dim3(256), 0, st,
-                     reinterpret_cast<const uint16_t*>(dY), reinterpret_cast<const uint16_t*>(Yx),
-                     reinterpret_cast<const uint16_t*>(Gx), dz, act / 8);
+// `branches` branches at once: dz, W^T, dy_x = dY * g_x + dz W_x, dW_x = dz^T y_x.
+static hipError_t gate_proj_bwd_branches(int branches, int B, int Hq, int n, int d, const void* const* Y_x, const void* const* W_x,
+                                         const void* const* G_x, const void* dY, void* const* dY_x, void* const* dW_x, char* ws,
+                                         hipStream_t st) {
+  const size_t dm = (size_t)Hq * d, act = (size_t)B * Hq * n * d, per_branch = gate_proj_bwd_workspace_bytes(B, Hq, n, d, false);
+  GateBwd p = {};
+  GateProj g = {};
+  p.dY = reinterpret_cast<const uint16_t*>(dY);
+  g.E1 = dY;
+  g.B = B; g.Hq = Hq; g.n = n; g.d = d;
+  for (int x = 0; x < branches; ++x) {
+    char* base = ws + x * per_branch;
+    p.Y_x[x] = reinterpret_cast<const uint16_t*>(Y_x[x]);
+    p.W_x[x] = reinterpret_cast<const uint16_t*>(W_x[x]);
+    p.G_x[x] = reinterpret_cast<const uint16_t*>(G_x[x]);
+    p.dz[x] = reinterpret_cast<uint16_t*>(base);
+    p.Wt[x] = reinterpret_cast<uint16_t*>(base + act * 2);
+    p.dWf[x] = reinterpret_cast<float*>(base + act * 2 + dm * dm * 2);
+    p.dW[x] = reinterpret_cast<uint16_t*>(dW_x[x]);
+    g.Y_x[x] = p.dz[x]; g.W_x[x] = p.Wt[x];
+    g.Y_out[x] = dY_x[x]; g.E2[x] = G_x[x];
+  }
+  const unsigned tiles = (unsigned)(dm / 64);
+  hipLaunchKernelGGL(gate_bwd_setup_kernel, dim3(tiles, tiles, branches), dim3(256), 0, st, p, (int)dm);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(transpose_bf16_kernel, dim3((unsigned)(dm / 64), (unsigned)(dm / 64)), dim3(256), 0, st,
-                     reinterpret_cast<const uint16_t*>(Wx), Wt, (int)dm);
+  hipLaunchKernelGGL(gate_dz_bf16_kernel, dim3(capped_blocks(act / 8, 256), branches), dim3(256), 0, st, p, act / 8);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  GateProj p = {};
-  p.Y_x[0] = dz; p.W_x[0] = Wt;
-  p.Y = dYx; p.E1 = dY; p.E2 = Gx;
-  p.B = B; p.Hq = Hq; p.n = n; p.d = d;
-  e = launch_gemm<GP_BWD_INPUT>(p, st);
+  e = launch_gemm<GP_BWD_INPUT>(g, st);
   if (e != hipSuccess) return e;
-  e = launch_fill_zero(dWf, dm * dm * 4, st);
-  if (e != hipSuccess) return e;
-  const int num_ft = (int)(dm / 128), chunks = (n + WCHUNK - 1) / WCHUNK;
-  const long total = (long)num_ft * num_ft * chunks * B;
-  const long blocks = xcd_grid_blocks(total);
+  const int num_ft = (int)(dm / 128);
+  int chunk = WCHUNK;
+  auto workgroups = [&]() -> long { return (long)num_ft * num_ft * ((n + chunk - 1) / chunk) * B * branches; };
+  while (chunk > WCHUNK_LEAST && workgroups() < WTARGET) chunk /= 2;
+  const int chunks = (n + chunk - 1) / chunk;
+  const long total = workgroups(), blocks = xcd_grid_blocks(total);
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  if (d == 64) hipLaunchKernelGGL(gate_dw_bf16_kernel<64>, dim3((unsigned)blocks), dim3(GNT), 0, st, reinterpret_cast<const bf16_t*>(dz),
-                                  reinterpret_cast<const bf16_t*>(Yx), dWf, B, Hq, n, num_ft, chunks, total);
-  else hipLaunchKernelGGL(gate_dw_bf16_kernel<128>, dim3((unsigned)blocks), dim3(GNT), 0, st, reinterpret_cast<const bf16_t*>(dz),
-                          reinterpret_cast<const bf16_t*>(Yx), dWf, B, Hq, n, num_ft, chunks, total);
+  if (d == 64) hipLaunchKernelGGL(gate_dw_bf16_kernel<64>, dim3((unsigned)blocks), dim3(GNT), 0, st, p, B, Hq, n, num_ft, chunk, chunks, total);
+  else hipLaunchKernelGGL(gate_dw_bf16_kernel<128>, dim3((unsigned)blocks), dim3(GNT), 0, st, p, B, Hq, n, num_ft, chunk, chunks, total);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(f32_to_bf16_kernel, dim3(capped_blocks(dm * dm / 2, 256)), dim3(256), 0, st, dWf,
-                     reinterpret_cast<uint16_t*>(dWx), dm * dm / 2);
+  hipLaunchKernelGGL(gate_dw_round_kernel, dim3(capped_blocks((size_t)dm * dm / 2, 256), branches), dim3(256), 0, st, p, (size_t)dm * dm / 2);
   return hipGetLastError();
 }
 
@@ -526,11 +564,25 @@ hipError_t launch_gate_proj_bwd_bf16(int B, int Hq, int n, int d, const void* Y_
   const long dm = (long)Hq * d;
   if (dm % 128 != 0) return hipErrorNotSupported;
   if ((size_t)dm * n * 2 >= ((size_t)1 << 32)) return hipErrorNotSupported;  // 32-bit byte offsets inside a batch
+  const void *const Y_x[2] = {Y_sa, Y_swa}, *const W_x[2] = {W_sa, W_swa}, *const G_x[2] = {G_sa, G_swa};
+  void *const dY_x[2] = {dY_sa, dY_swa}, *const dW_x[2] = {dW_sa, dW_swa};
+  // Both at once unless an output of one shares memory with what the other still reads (the second branch's gradient in the
+  // place of dY, for instance): then one after the other.
+  const size_t bytes = (size_t)B * Hq * n * d * 2;
+  auto overlap = [&](const void* a, const void* b) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + bytes && y < x + bytes;
+  };
+  bool apart = true;
+  if (dual)
+    for (int x = 0; x < 2; ++x)
+      apart = apart && !overlap(dY_x[x], dY) && !overlap(dY_x[x], Y_x[1 - x]) && !overlap(dY_x[x], G_x[1 - x]) && !overlap(dY_x[x], dY_x[1 - x]);
   char* base = reinterpret_cast<char*>(ws);
-  hipError_t e = gate_proj_bwd_branch(B, Hq, n, d, Y_sa, W_sa, G_sa, dY, dY_sa, dW_sa, base, st);
+  if (dual && apart) return gate_proj_bwd_branches(2, B, Hq, n, d, Y_x, W_x, G_x, dY, dY_x, dW_x, base, st);
+  hipError_t e = gate_proj_bwd_branches(1, B, Hq, n, d, Y_x, W_x, G_x, dY, dY_x, dW_x, base, st);
   if (e != hipSuccess || !dual) return e;
-  const size_t half = gate_proj_bwd_workspace_bytes(B, Hq, n, d, false);
-  return gate_proj_bwd_branch(B, Hq, n, d, Y_swa, W_swa, G_swa, dY, dY_swa, dW_swa, base + half, st);
+  return gate_proj_bwd_branches(1, B, Hq, n, d, Y_x + 1, W_x + 1, G_x + 1, dY, dY_x + 1, dW_x + 1,
+                                base + gate_proj_bwd_workspace_bytes(B, Hq, n, d, false), st);
 }
 
 }  // namespace sa

@@ -123,3 +123,38 @@ def test_gate_proj_bwd_dual_path(d, H):
 def test_gate_proj_bwd_single_path_and_several_token_chunks():
     run_bwd_case(1, 2, 9000, 64, seed=5, dual=False)   # 3 token chunks of the dW kernel, ragged tail
     run_bwd_case(2, 2, 1100, 64, seed=6, dual=True)
+
+
+@pytest.mark.parametrize("B,n", [(1, 255), (1, 256), (2, 257), (1, 1100), (3, 2049)])
+def test_backward_branches_together_and_one_after_the_other(B, n):
+    """The launches of the backward serve both branches, with token chunks of dW cut down for short calls; a second-branch
+    gradient in the place of dY sends the branches through one after the other.  Both must agree: dY_x to the bit, dW up to
+    the order of its fp32 sums (one bf16 rounding: 2^-8 of the largest entry)."""
+    from paper_2604_00754_amd import binding as sa
+    H, d = 4, 64
+    print(f"case gate_proj_bwd together B{B} H{H} n{n} d{d}", flush=True)
+    gen = torch.Generator(device=U.DEV)
+    gen.manual_seed(n)
+    rnd = lambda *s: torch.randn(s, device=U.DEV, generator=gen).to(torch.bfloat16)
+    Ya, Yb, dY, Wa, Wb = rnd(B, H, n, d), rnd(B, H, n, d), rnd(B, H, n, d), rnd(H * d, H * d) * 0.06, rnd(H * d, H * d) * 0.06
+    Ga, Gb = torch.sigmoid(rnd(B, H, n, d)), torch.sigmoid(rnd(B, H, n, d))
+    desc = sa.make_desc(B, H, H, n, d, 4)
+    ws = torch.empty(sa.sa_workspace_bytes(desc, sa.SA_OP_GATE_PROJ_BWD), device=U.DEV, dtype=torch.uint8)
+    got = []
+    for in_place in (False, True):
+        g = dY.clone()
+        dYa, dYb = torch.full_like(dY, float("nan")), g if in_place else torch.full_like(dY, float("nan"))
+        dWa, dWb = torch.full_like(Wa, float("nan")), torch.full_like(Wb, float("nan"))
+        ws.fill_(255)
+        sa.sa_gate_proj_bwd(desc, Ya, Yb, Wa, Wb, Ga, Gb, g, dYa, dYb, dWa, dWb, ws)
+        torch.cuda.synchronize()
+        got.append((dYa, dYb, dWa, dWb))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    for x in (2, 3):
+        a, b = got[0][x].float(), got[1][x].float()
+        assert torch.isfinite(a).all() and (a - b).abs().max() <= 2 ** -8 * b.abs().max()
+    # against fp64: dW_x = dz^T y with dz rounded to bf16 (2^-9 a term, averaged out over the sum; stored with 2^-9 more)
+    tok = lambda t: t.double().permute(0, 2, 1, 3).reshape(B * n, H * d)
+    dz = tok(dY) * tok(Ya) * tok(Ga) * (1 - tok(Ga))
+    ref = dz.T @ tok(Ya)
+    assert (got[0][2].double() - ref).norm() <= 5e-3 * ref.norm()
