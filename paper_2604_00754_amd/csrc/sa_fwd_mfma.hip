@@ -485,16 +485,17 @@ __global__ __launch_bounds__(NT, D == 64 ? FWD_WGS64 : (GATED ? 2 : FWD_WGS128))
         *reinterpret_cast<u32x2*>(mine + 32 * db + 8 * mq) = w;
       }
     wave_lds_sync();  // the staging rows are this wave's own
-    const int lane = le, chunk16 = le % C::CPR;
+    // (at d = 128 the prologue's numbers are kept: formed anew there they move registers of the tile loop)
+    const int ls = D == 64 ? le : lane, chunk = D == 64 ? le % C::CPR : chunk16;
     int dst[NP];
 #pragma unroll
-    for (int pass = 0; pass < NP; ++pass) dst[pass] = rowstash[wave * 32 + pass * C::WRPP + lane / C::CPR];
+    for (int pass = 0; pass < NP; ++pass) dst[pass] = rowstash[wave * 32 + pass * C::WRPP + ls / C::CPR];
 #pragma unroll
     for (int pass = 0; pass < NP; ++pass) {
-      const int row = pass * C::WRPP + lane / C::CPR;
+      const int row = pass * C::WRPP + ls / C::CPR;
       if (s_w0 + row < n) {
-        const size_t eoff = (head_row0 + dst[pass]) * D + chunk16 * 8;
-        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(Os + row * C::QSTR + chunk16 * 8),
+        const size_t eoff = (head_row0 + dst[pass]) * D + chunk * 8;
+        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(Os + row * C::QSTR + chunk * 8),
                                     reinterpret_cast<u32x4*>(reinterpret_cast<bf16_t*>(dst_tensor) + eoff));
       }
     }
