@@ -568,10 +568,13 @@ hipError_t launch_t(const Pass& p, hipStream_t st) {
   const int mode = (!p.causal || window_is_causal) ? CAUSAL_NONE : (p.n <= 65535 ? CAUSAL_I16 : CAUSAL_I32);
 #define SA_LAUNCH_FWD(PERM_, MODE_)                                                                              \
   do {                                                                                                            \
-    if (gated) hipLaunchKernelGGL((fwd_mfma_bf16_kernel<D, PERM_, MODE_, true>), grid, block, 0, st, p, num_qt, total, hshift); \
+    if (gated) hipLaunchKernelGGL((fwd_mfma_bf16_kernel<D, PERM_, MODE_, true>), grid, block, pad, st, p, num_qt, total, hshift); \
     else hipLaunchKernelGGL((fwd_mfma_bf16_kernel<D, PERM_, MODE_, false>), grid, block, 0, st, p, num_qt, total, hshift);      \
   } while (0)
   const bool gated = p.gate_mode != 0;
+  // Gates per dimension are read in the accumulator layout, 32 rows an instruction: with four workgroups per CU at d = 64 they push each
+  // other's lines out of the cache (calls 3 - 7 % slower than with three), so unused LDS keeps it at three.
+  const unsigned pad = D == 64 && p.gate_per_dim ? 16384 : 0;
   if (p.perm) {
     if (mode == CAUSAL_NONE) SA_LAUNCH_FWD(true, CAUSAL_NONE);
     else if (mode == CAUSAL_I16) SA_LAUNCH_FWD(true, CAUSAL_I16);
