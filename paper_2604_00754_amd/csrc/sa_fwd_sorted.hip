@@ -105,10 +105,13 @@ __global__ __launch_bounds__(NT, 3) void fwd_sorted_bf16_kernel(const Pass p, co
 #pragma unroll
     for (int j = 0; j < J; ++j) kp[j] = perm[wrap_slot(min(t_lo + j * NT + tid, t_hi), n)];
 
-    // rank of every query of the group: two threads per query with half of the comparisons each
+    // rank of every query of the group: two threads per query with half of the comparisons each.  Positions (below 2^23, the
+    // host bounds n * D * 2) are compared together with the slot, so that every place is taken once even where a
+    // caller's index tensor names a position twice (undefined rows, but rows of the tensors)
+    const int qk = (tid & 127) < nq ? (int)((unsigned)qp * GROUP + (tid & 127)) : 0x7fffffff;
     int* const all_q = reinterpret_cast<int*>(smem);
     int* const half_rank = all_q + GROUP;
-    if (tid < GROUP) all_q[tid] = qp;
+    if (tid < GROUP) all_q[tid] = qk;
     if (tid < 32) own_pos[tid] = 0x7fffffff;
     __syncthreads();
     int rank = 0;
@@ -116,7 +119,7 @@ __global__ __launch_bounds__(NT, 3) void fwd_sorted_bf16_kernel(const Pass p, co
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int4 o = other[j];
-      rank += (o.x < qp ? 1 : 0) + (o.y < qp ? 1 : 0) + (o.z < qp ? 1 : 0) + (o.w < qp ? 1 : 0);
+      rank += (o.x < qk ? 1 : 0) + (o.y < qk ? 1 : 0) + (o.z < qk ? 1 : 0) + (o.w < qk ? 1 : 0);
     }
     half_rank[tid] = rank;
     __syncthreads();

@@ -75,3 +75,33 @@ def test_sorted_forward_with_rotation(interleaved):
     torch.cuda.synchronize()
     max_abs, rel = U.errors(U.to_np64(Y1), U.to_np64(Y0))
     assert max_abs <= 2e-2 and rel <= 5e-4, (max_abs, rel)
+
+
+def test_index_tensor_that_names_positions_twice_stays_inside_the_tensors():
+    """Entries of perm that are in range but no bijection: the rows of the positions named more than once are undefined, every
+    other row is attention over the slots as they are named, and nothing is read or written outside the tensors (Y lies
+    between guard rows).  Twins in one quarter, in two quarters of a group, in two groups, and a group of one position."""
+    from paper_2604_00754_amd import binding as sa
+    B, Hq, Hkv, n, d, w = 4, 8, 2, 1100, 128, 700
+    gen = torch.Generator(device=U.DEV)
+    gen.manual_seed(11)
+    perm = torch.randperm(n, device=U.DEV, generator=gen)
+    perm[1], perm[70], perm[900] = perm[0], perm[2], perm[3]
+    perm[256:384] = 5
+    Q, K, V = (torch.randn(s, device=U.DEV, generator=gen).to(torch.bfloat16) for s in ((B, Hq, n, d), (B, Hkv, n, d), (B, Hkv, n, d)))
+    guard = 64 * d
+    store = torch.full((Q.numel() + 2 * guard,), 7.0, device=U.DEV, dtype=torch.bfloat16)
+    Y = store[guard:guard + Q.numel()].view_as(Q)
+    sa.sa_fwd(sa.make_desc(B, Hq, Hkv, n, d, w), Q, K, V, perm.to(torch.int32).view(1, 1, n).contiguous(), Y)
+    torch.cuda.synchronize()
+    assert (store[:guard] == 7).all() and (store[-guard:] == 7).all()
+    s = torch.arange(n, device=U.DEV)
+    dist = (s[:, None] - s[None, :]).abs()
+    seen = (2 * torch.minimum(dist, n - dist) < w) & (perm[None, :] <= perm[:, None])
+    once = torch.bincount(perm, minlength=n)[perm] == 1
+    for b in range(B):
+        for h in range(Hq):
+            k, v = K[b, h // (Hq // Hkv)].float()[perm], V[b, h // (Hq // Hkv)].float()[perm]
+            z = (Q[b, h].float()[perm] @ k.T.contiguous()) * d ** -0.5
+            ref = torch.softmax(z.masked_fill(~seen, -float("inf")), -1) @ v
+            U.assert_close(U.to_np64(Y[b, h][perm][once]), U.to_np64(ref[once]), "bf16", f"Y[{b},{h}]")
