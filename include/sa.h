@@ -28,6 +28,9 @@
  *     identity.  Each slice must be a bijection of 0..n-1; otherwise results are undefined (use
  *     sa_check_perm to verify).
  *   - LSE is the natural-log sum of exp(scale * <q,k>) over the visible keys, in ORIGINAL order.
+ *   - dtype SA_F32: what a query does not see does not enter its results, whatever it holds.  dtype SA_BF16: tokens are
+ *     taken in blocks and those not seen with a weight of zero, so an infinity or NaN in any row of a block can make
+ *     the results of the whole block NaN.
  *   - The library allocates no device memory and keeps no state; work is only enqueued on `stream`
  *     (a hipStream_t passed as void*, NULL = the default stream).  Outputs are overwritten.
  *   - Every function returns an sa_status.  Argument errors are found on the host before anything

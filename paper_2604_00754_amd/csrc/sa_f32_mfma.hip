@@ -69,9 +69,9 @@ __device__ __forceinline__ void get_rows(const float* stage, int g, int c, f32x4
   for (int j = 0; j < D / 16; ++j) f[j] = *reinterpret_cast<const f32x4*>(stage + c * Stage<D>::STR + 16 * j + 4 * g);
 }
 
-// The 16 stationary rows of a workgroup in "rows" layout.
+// Rows to the staging area and into the "rows" layout.
 template <int D>
-__device__ __forceinline__ void stationary_rows(float* stage, int g, int c, const f32x4* cols, f32x4* f) {
+__device__ __forceinline__ void stage_rows(float* stage, int g, int c, const f32x4* cols, f32x4* f) {
   wave_lds_sync();
   put_columns<D>(stage, g, c, cols);
   wave_lds_sync();
@@ -100,6 +100,46 @@ __device__ __forceinline__ void product_columns(f32x4* acc, const f32x4* cols, c
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int b = 0; b < D / 16; ++b) acc[b] = mfma_f32(cols[i * (D / 64) + b / 4][b % 4], w[i], acc[b]);
+}
+
+// The same sum over the staged rows of a block with the rows of weight zero left out.  A matrix instruction multiplies them as
+// well, and zero times an infinity or NaN in a row that query (or key) c does not see would be a NaN in its sum: a band whose
+// sums are not finite is walked again with this form, so that only what is seen can make them so.
+template <int D>
+__device__ __forceinline__ void add_weighted_rows(f32x4* acc, const float* stage, const f32x4 w, int g, int c) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll 1
+    for (int from = 0; from < 4; ++from) {
+      const float wr = __shfl(w[i], 16 * from + c);
+      const float* row = stage + (4 * from + i) * Stage<D>::STR + 16 * g;
+#pragma unroll
+      for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(row + 64 * h + 4 * x);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[4 * h + e][x] = wr != 0.f ? fmaf(wr, v[e], acc[4 * h + e][x]) : acc[4 * h + e][x];
+        }
+    }
+}
+
+// A copy of the lane number that the optimiser cannot trace: what follows from it is formed where it is used and not kept in
+// registers across the tile loop.
+__device__ __forceinline__ int fresh(int lane) {
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// Is one of the sums of a lane that counts infinite or NaN?  The same answer in every lane.
+template <int D>
+__device__ __forceinline__ bool any_not_finite(const f32x4* acc, bool counts) {
+  float t = 0.f;
+#pragma unroll
+  for (int b = 0; b < D / 16; ++b)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) t = fmaf(acc[b][x], 0.f, t);
+  return __any(counts & (t != 0.f));  // (NaN != 0)
 }
 
 // The slot tile of a workgroup and the band it streams.
@@ -206,25 +246,13 @@ __global__ __launch_bounds__(64 * FW, D == 64 ? 4 : 2) void fwd_f32_kernel(const
   load_columns<D>(reinterpret_cast<const float*>(p.Q) + head_row0 * D, orig_q, g, c, qf);
   load_columns<D>(Kh, pos, g, c, kn);
   load_columns<D>(Vh, pos, g, c, vn);
-  stationary_rows<D>(stage, g, c, qf, qf);
+  stage_rows<D>(stage, g, c, qf, qf);
 #pragma unroll
   for (int b = 0; b < D / 16; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float cs = p.scale * kLog2e;  // exp(scale * x) = exp2(cs * x)
   float m = -INFINITY, l = 0.f;
-  for (int blk = wave; blk < t.nblocks; blk += FW) {
-    wave_lds_sync();
-    put_columns<D>(stage, g, c, kn);
-    wave_lds_sync();
-    int kpos[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) kpos[i] = __shfl(pos, 4 * g + i);
-    pos = pos1;
-    load_columns<D>(Kh, pos, g, c, kn);
-    pos1 = streamed_row<PERM>(t, perm, blk + 2 * FW, c, n);
-    f32x4 kf[D / 16];
-    get_rows<D>(stage, g, c, kf);
-    __builtin_amdgcn_sched_barrier(0);
-    const f32x4 st = product_rows<D>(kf, qf);  // S^T: keys 4g + i, query c
+  // weights of a block (keys 4g + i, query c) from its scores; the sums so far follow the running maximum
+  auto weigh = [&](int blk, const f32x4 st, const int* kpos) -> f32x4 {
     const int t0 = t.lo + FT * blk + 4 * g - s + Ll;
     f32x4 z, pe;
 #pragma unroll
@@ -245,10 +273,47 @@ __global__ __launch_bounds__(64 * FW, D == 64 ? 4 : 2) void fwd_f32_kernel(const
 #pragma unroll
     for (int i = 0; i < 4; ++i) pe[i] = __builtin_amdgcn_exp2f((z[i] - ms) * cs);
     l += (pe[0] + pe[1]) + (pe[2] + pe[3]);  // this lane group's keys; the groups are added at the end
+    return pe;
+  };
+  for (int blk = wave; blk < t.nblocks; blk += FW) {
+    wave_lds_sync();
+    put_columns<D>(stage, g, c, kn);
+    wave_lds_sync();
+    int kpos[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) kpos[i] = __shfl(pos, 4 * g + i);
+    pos = pos1;
+    load_columns<D>(Kh, pos, g, c, kn);
+    pos1 = streamed_row<PERM>(t, perm, blk + 2 * FW, c, n);
+    f32x4 kf[D / 16];
+    get_rows<D>(stage, g, c, kf);
+    __builtin_amdgcn_sched_barrier(0);
+    const f32x4 st = product_rows<D>(kf, qf);  // S^T: keys 4g + i, query c
+    const f32x4 pe = weigh(blk, st, kpos);
     product_columns<D>(o, vn, pe);
     __builtin_amdgcn_sched_barrier(0);
     load_columns<D>(Vh, pos, g, c, vn);
     __builtin_amdgcn_sched_barrier(0);
+  }
+  if (any_not_finite<D>(o, s < n)) {
+    const int le = fresh(lane), g = le >> 4, c = le & 15;
+    m = -INFINITY;
+    l = 0.f;
+#pragma unroll
+    for (int b = 0; b < D / 16; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int blk = wave; blk < t.nblocks; blk += FW) {
+      pos = streamed_row<PERM>(t, perm, blk, c, n);
+      load_columns<D>(Kh, pos, g, c, kn);
+      load_columns<D>(Vh, pos, g, c, vn);
+      stage_rows<D>(stage, g, c, kn, kn);
+      int kpos[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kpos[i] = __shfl(pos, 4 * g + i);
+      const f32x4 pe = weigh(blk, product_rows<D>(kn, qf), kpos);
+      stage_rows<D>(stage, g, c, vn, kn);
+      add_weighted_rows<D>(o, stage, pe, g, c);
+    }
   }
   l = group_sum4(l);
   if (g == 0) {
@@ -261,7 +326,7 @@ __global__ __launch_bounds__(64 * FW, D == 64 ? 4 : 2) void fwd_f32_kernel(const
   for (int w = 1; w < FW; ++w) M = fmaxf(M, lds_m[w][c]);
 #pragma unroll
   for (int w = 0; w < FW; ++w) {
-    scale[w] = __builtin_amdgcn_exp2f((lds_m[w][c] - M) * cs);
+    scale[w] = __builtin_amdgcn_exp2f((lds_m[w][c] - (M == -INFINITY ? 0.f : M)) * cs);
     L = fmaf(scale[w], lds_l[w][c], L);
   }
   const float inv_l = 1.f / L;
@@ -342,10 +407,21 @@ __global__ __launch_bounds__(64 * FW, D == 64 ? 3 : 2) void bwd_dq_f32_kernel(co
   }
   load_columns<D>(Kh, pos, g, c, kn);
   load_columns<D>(Vh, pos, g, c, vn);
-  stationary_rows<D>(stage_k, g, c, qf, qf);
-  stationary_rows<D>(stage_v, g, c, gf, gf);
+  stage_rows<D>(stage_k, g, c, qf, qf);
+  stage_rows<D>(stage_v, g, c, gf, gf);
 #pragma unroll
   for (int b = 0; b < D / 16; ++b) dq[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto weigh = [&](int blk, const f32x4 st, const f32x4 dp, const int* kpos) -> f32x4 {  // dS of keys 4g + i, query c
+    const int t0 = t.lo + FT * blk + 4 * g - s + Ll;
+    f32x4 ds;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool seen = ((unsigned)(t0 + i) <= LRl) & (kpos[i] <= last_q);
+      const float pr = __builtin_amdgcn_exp2f(fmaf(st[i], cs, -lse2));
+      ds[i] = seen ? pr * (dp[i] - Dq) : 0.f;
+    }
+    return ds;
+  };
   for (int blk = wave; blk < t.nblocks; blk += FW) {
     wave_lds_sync();
     put_columns<D>(stage_k, g, c, kn);
@@ -365,15 +441,27 @@ __global__ __launch_bounds__(64 * FW, D == 64 ? 3 : 2) void bwd_dq_f32_kernel(co
     get_rows<D>(stage_v, g, c, x);
     const f32x4 dp = product_rows<D>(x, gf);
     get_columns<D>(stage_k, g, c, x);
-    const int t0 = t.lo + FT * blk + 4 * g - s + Ll;
-    f32x4 ds;
+    product_columns<D>(dq, x, weigh(blk, st, dp, kpos));
+  }
+  if (any_not_finite<D>(dq, s < n)) {
+    const int le = fresh(lane), g = le >> 4, c = le & 15;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool seen = ((unsigned)(t0 + i) <= LRl) & (kpos[i] <= last_q);
-      const float pr = __builtin_amdgcn_exp2f(fmaf(st[i], cs, -lse2));
-      ds[i] = seen ? pr * (dp[i] - Dq) : 0.f;
+    for (int b = 0; b < D / 16; ++b) dq[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int blk = wave; blk < t.nblocks; blk += FW) {
+      pos = streamed_row<PERM>(t, perm, blk, c, n);
+      f32x4 x[D / 16];
+      load_columns<D>(Kh, pos, g, c, x);
+      stage_rows<D>(stage_k, g, c, x, x);
+      const f32x4 st = product_rows<D>(x, qf);
+      load_columns<D>(Vh, pos, g, c, x);
+      stage_rows<D>(stage_v, g, c, x, x);
+      const f32x4 dp = product_rows<D>(x, gf);
+      int kpos[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kpos[i] = __shfl(pos, 4 * g + i);
+      add_weighted_rows<D>(dq, stage_k, weigh(blk, st, dp, kpos), g, c);
     }
-    product_columns<D>(dq, x, ds);
   }
   float ones[FW];
 #pragma unroll
@@ -429,10 +517,21 @@ __global__ __launch_bounds__(64 * FW, 2) void bwd_dkv_f32_kernel(const Pass p, c
   const float* __restrict__ dO = reinterpret_cast<const float*>(p.dO);
   int pos = unit_row(wave), pos1 = unit_row(wave + FW);
   f32x4 qn[D / 16], gn[D / 16];
+  auto probabilities = [&](int u, const f32x4 st, const int* qpos, const float* lse2) -> f32x4 {  // of queries 4g + i for key c
+    const int s0 = t.lo + FT * (u % t.nblocks) + 4 * g - k + Rl;
+    f32x4 pr;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool seen = ((unsigned)(s0 + i) <= LRl) & (first_q <= qpos[i]);
+      const float pe = __builtin_amdgcn_exp2f(fmaf(st[i], cs, -lse2[i]));
+      pr[i] = seen ? pe : 0.f;
+    }
+    return pr;
+  };
   load_columns<D>(Q + unit_row0(wave) * D, pos, g, c, qn);
   load_columns<D>(dO + unit_row0(wave) * D, pos, g, c, gn);
-  stationary_rows<D>(stage_q, g, c, kf, kf);
-  stationary_rows<D>(stage_g, g, c, vf, vf);
+  stage_rows<D>(stage_q, g, c, kf, kf);
+  stage_rows<D>(stage_g, g, c, vf, vf);
   for (int u = wave; u < units; u += FW) {
     const size_t head_row0 = unit_row0(u), next_row0 = unit_row0(u + FW);
     wave_lds_sync();
@@ -456,14 +555,7 @@ __global__ __launch_bounds__(64 * FW, 2) void bwd_dkv_f32_kernel(const Pass p, c
     get_rows<D>(stage_q, g, c, x);
     __builtin_amdgcn_sched_barrier(0);
     const f32x4 st = product_rows<D>(x, kf);  // S: queries 4g + i, key c
-    const int s0 = t.lo + FT * (u % t.nblocks) + 4 * g - k + Rl;
-    f32x4 pr;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const bool seen = ((unsigned)(s0 + i) <= LRl) & (first_q <= qpos[i]);
-      const float pe = __builtin_amdgcn_exp2f(fmaf(st[i], cs, -lse2[i]));
-      pr[i] = seen ? pe : 0.f;
-    }
+    const f32x4 pr = probabilities(u, st, qpos, lse2);
     get_columns<D>(stage_g, g, c, x);
     product_columns<D>(dv, x, pr);
     get_rows<D>(stage_g, g, c, x);
@@ -474,18 +566,50 @@ __global__ __launch_bounds__(64 * FW, 2) void bwd_dkv_f32_kernel(const Pass p, c
     for (int i = 0; i < 4; ++i) ds[i] = pr[i] == 0.f ? 0.f : pr[i] * (dp[i] - dd[i]);
     product_columns<D>(dk, x, ds);
   }
+  if (any_not_finite<D>(dk, k < n) || any_not_finite<D>(dv, k < n)) {
+    const int le = fresh(lane), g = le >> 4, c = le & 15;
+#pragma unroll
+    for (int b = 0; b < D / 16; ++b) dk[b] = dv[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int u = wave; u < units; u += FW) {
+      const size_t head_row0 = unit_row0(u);
+      pos = unit_row(u);
+      int qpos[4];
+      float lse2[4], dd[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        qpos[i] = __shfl(pos, 4 * g + i);
+        lse2[i] = p.lse_in[head_row0 + qpos[i]] * kLog2e;
+        dd[i] = p.Dsum[head_row0 + qpos[i]];
+      }
+      f32x4 x[D / 16];
+      load_columns<D>(Q + head_row0 * D, pos, g, c, x);
+      stage_rows<D>(stage_q, g, c, x, x);
+      const f32x4 pr = probabilities(u, product_rows<D>(x, kf), qpos, lse2);
+      load_columns<D>(dO + head_row0 * D, pos, g, c, x);
+      stage_rows<D>(stage_g, g, c, x, x);
+      const f32x4 dp = product_rows<D>(x, vf);
+      f32x4 ds;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ds[i] = pr[i] == 0.f ? 0.f : pr[i] * (dp[i] - dd[i]);
+      add_weighted_rows<D>(dv, stage_g, pr, g, c);
+      add_weighted_rows<D>(dk, stage_q, ds, g, c);
+    }
+  }
+  // (lane numbers from a fresh copy: with them 167 or 168 registers at d = 64, three wavefronts per SIMD)
+  const int le = fresh(lane), ge = le >> 4, ke = t.s0 + (le & 15);
   float ones[FW];
 #pragma unroll
   for (int w = 0; w < FW; ++w) ones[w] = 1.f;
   f32x4 yk[4 / FW][D / 64], yv[4 / FW][D / 64];
-  merge_waves<D, FW>(area, 2 * Stage<D>::FLOATS, dk, ones, wave, lane, yk);
+  merge_waves<D, FW>(area, 2 * Stage<D>::FLOATS, dk, ones, wave, le, yk);
   __syncthreads();
-  merge_waves<D, FW>(area, 2 * Stage<D>::FLOATS, dv, ones, wave, lane, yv);
-  if (k >= n) return;
+  merge_waves<D, FW>(area, 2 * Stage<D>::FLOATS, dv, ones, wave, le, yv);
+  if (ke >= n) return;
 #pragma unroll
   for (int qh = 0; qh < 4 / FW * (D / 64); ++qh) {
-    const int q = qh / (D / 64), h = qh % (D / 64), col = 64 * h + 16 * g + 4 * (wave + FW * q);
-    const size_t at = (kv_row0 + orig_k) * D + col;
+    const int q = qh / (D / 64), h = qh % (D / 64), col = 64 * h + 16 * ge + 4 * (wave + FW * q);
+    const size_t at = (kv_row0 + (PERM ? orig_k : ke)) * D + col;
     float* dK = reinterpret_cast<float*>(p.dK) + at;
     float* dV = reinterpret_cast<float*>(p.dV) + at;
     yk[q][h] *= p.scale;

@@ -1,8 +1,11 @@
 """fp32 kernels at the edges of their 16-slot tiles and on both sides of the lines where the number of wavefronts per tile
 changes (1024 and 2048 tiles of query heads), against the fp64 oracle.  Bar: the 1e-5 of the fp32 configuration; a sum of W
 products of N(0,1) values in any order is off by about sqrt(W) 2^-24 of its size, 2e-6 at most here."""
+import numpy as np
 import pytest
+import torch
 
+from tests import gpu_util as U
 from tests.test_gpu_bwd import run_bwd
 from tests.test_gpu_fwd import run_fwd
 
@@ -30,3 +33,70 @@ def test_f32_tiles(case):
     kw = dict(perm_H=perm_H, identity=identity, seed=n)
     run_fwd(B, Hq, Hkv, n, d, w, window, causal, "f32", **kw)
     run_bwd(B, Hq, Hkv, n, d, w, window, causal, "f32", **kw)
+
+
+UNSEEN = [
+    # B, Hq, Hkv, n, d, w, window, causal, perm_H
+    (1, 1, 1, 17, 64, 5, ONE, 1, 1),
+    (1, 2, 1, 200, 64, 40, CIRC, 1, 1),             # four wavefronts a tile
+    (1, 4, 2, 333, 128, 37, CIRC, 0, 4),            # not causal: tokens outside the window
+    (1, 16, 4, 1009, 128, 48, CIRC, 1, 1),          # two
+    (2, 16, 16, 1023, 64, 33, LIN, 1, 16),          # one
+    (2, 16, 8, 1025, 128, 15, CIRC, 1, 16),
+]
+
+
+@pytest.mark.parametrize("case", UNSEEN, ids=lambda c: f"B{c[0]}H{c[1]}-{c[2]}n{c[3]}d{c[4]}w{c[5]}")
+def test_f32_non_finite_rows_reach_only_the_rows_that_see_them(case):
+    """K and V of the last token and Q and dY of the first one are infinite or NaN.  Every row of Y, LSE and dQ whose query does
+    not see the last token, and every row of dK and dV whose key no such query sees, is what the same call gives without them
+    (the definition sums over visible pairs only), within the 1e-5 of the fp32 configuration."""
+    from oracle import binding as orc
+    from paper_2604_00754_amd import binding as sa
+    B, Hq, Hkv, n, d, w, window, causal, perm_H = case
+    wl, x = U.make_case(B, Hq, Hkv, n, d, w, "f32", 1, perm_H, seed=n, grads=True)
+    print(f"case f32 non-finite rows {case}", flush=True)
+    od, desc = U.orc_desc(wl, window, causal), U.sa_desc(wl, window, causal)
+    Yr, Lr = orc.sa_fwd(od, x["Q"], x["K"], x["V"], x["perm"])
+    ref = orc.sa_bwd(od, x["Q"], x["K"], x["V"], x["perm"], x["dY"])
+    s, t = np.arange(n)[:, None], np.arange(n)[None, :]
+    near = {CIRC: 2 * np.minimum(abs(s - t), n - abs(s - t)) < w, LIN: 2 * abs(s - t) < w, ONE: (s - t >= 0) & (s - t < w)}[window]
+    hit_q, hit_k = np.zeros((Hq, n), bool), np.zeros((Hkv, n), bool)
+    for h in range(Hq):
+        p = x["perm"][0, h if perm_H > 1 else 0]
+        seen = np.zeros((n, n), bool)  # by original positions
+        seen[np.ix_(p, p)] = near & ((p[None, :] <= p[:, None]) if causal else True)
+        hit_q[h] = seen[:, n - 1]
+        hit_q[h, 0] = True
+        hit_k[h // (Hq // Hkv)] |= seen[hit_q[h]].any(0)
+    hit_k[:, n - 1] = True
+    assert not hit_q.all() and not hit_k.all()
+    x["K"][:, :, n - 1, :3], x["V"][:, :, n - 1, 1:4] = [np.inf, np.nan, -np.inf], [np.nan, np.inf, -np.inf]
+    x["Q"][:, :, 0, :3], x["dY"][:, :, 0, 1:4] = [np.nan, np.inf, -np.inf], [-np.inf, np.nan, np.inf]
+    Q, K, V, dY = (torch.from_numpy(x[k]).to(U.DEV).contiguous() for k in ("Q", "K", "V", "dY"))
+    perm = torch.from_numpy(x["perm"]).to(U.DEV)
+    Y, L = torch.empty_like(Q), torch.empty(Q.shape[:3], device=U.DEV)
+    got = [torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)]
+    ws = torch.full((max(sa.sa_workspace_bytes(desc, sa.SA_OP_BWD), 16),), 255, device=U.DEV, dtype=torch.uint8)
+    sa.sa_fwd(desc, Q, K, V, perm, Y, L)
+    sa.sa_bwd(desc, None, Q, K, V, perm, None, None, Y, None, L, None, dY, *got, None, None, ws)
+    torch.cuda.synchronize()
+    ok_q, ok_k = np.broadcast_to(~hit_q, (B, Hq, n)), np.broadcast_to(~hit_k, (B, Hkv, n))
+    assert not np.isfinite(U.to_np64(Y)[:, :, n - 1]).all()
+    U.assert_close(U.to_np64(Y)[ok_q], Yr[ok_q], "f32", "Y")
+    assert np.abs(U.to_np64(L)[ok_q] - Lr[ok_q]).max() <= 1e-5
+    for name, g, r, ok in zip(("dQ", "dK", "dV"), got, ref, (ok_q, ok_k, ok_k)):
+        U.assert_close(U.to_np64(g)[ok], r[ok], "f32", name, scale_abs=max(1.0, np.abs(r).max()))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_rows_whose_scores_are_all_minus_infinity(d):
+    """The log of an empty sum is minus infinity, whatever the number of wavefronts that share the row."""
+    from paper_2604_00754_amd import binding as sa
+    for n in (5, 70):
+        Q, K = torch.ones(1, 1, n, d, device=U.DEV), torch.zeros(1, 1, n, d, device=U.DEV)
+        K[..., 0] = -float("inf")
+        Y, L = torch.zeros_like(Q), torch.zeros(1, 1, n, device=U.DEV)
+        sa.sa_fwd(sa.make_desc(1, 1, 1, n, d, 4, dtype=sa.SA_F32), Q, K, torch.ones_like(K), None, Y, L)
+        torch.cuda.synchronize()
+        assert (L == -float("inf")).all() and torch.isnan(Y).all()
