@@ -149,8 +149,9 @@ sa_status sa_gate_proj_fwd(const sa_desc* desc, const void* Y_sa, const void* Y_
  * dY_sa, dY_swa: [B,Hq,n,d]; dW_sa, dW_swa: [dm, dm] like the weights; all overwritten.  The *_swa
  * arguments are all NULL for the single path.  ws: sa_workspace_bytes(desc, SA_OP_GATE_PROJ_BWD or
  * SA_OP_GATE_PROJ_BWD_SINGLE) bytes.  dz_x is rounded to the tensor dtype before the two products;
- * dW_x is accumulated in fp32 (order of the additions not fixed) and rounded once.  Same support as
- * the forward. */
+ * dW_x is accumulated in fp32 and rounded once.  Calls of at most two pieces of 4096 tokens of a sequence
+ * (ceil(n / 4096) * B <= 2) give the same bits every time; in larger ones the order of the additions to dW_x is not
+ * fixed.  Same support as the forward. */
 sa_status sa_gate_proj_bwd(const sa_desc* desc, const void* Y_sa, const void* Y_swa, const void* W_sa,
                            const void* W_swa, const void* G_sa, const void* G_swa, const void* dY,
                            void* dY_sa, void* dY_swa, void* dW_sa, void* dW_swa,

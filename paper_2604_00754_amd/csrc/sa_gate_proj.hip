@@ -336,8 +336,11 @@ __global__ __launch_bounds__(256) void gate_bwd_setup_kernel(const GateBwd p, co
 // gets the same 8 tokens of one feature column for the A operand (dz^T) and the B operand (y).
 // Steps of 32 tokens, four buffers, three steps in flight.  Tokens past the chunk's end are zeroed in
 // the dz tile after it has landed.
-// Tokens per workgroup: WCHUNK, halved down to WCHUNK_LEAST until the launch has WTARGET workgroups (two per
-// CU): 4096 tokens of 12 heads were 36 workgroups a branch (layer forward + backward, with the branches in one launch, 267 -> 214 us).
+// Tokens per workgroup.  A call that pieces of WCHUNK tokens cut into one or two is cut into two at most: two additions to
+// zero give the same bits in either order, so dW repeats itself.  (It is the faster cut as well for 12 and 16 heads of 64:
+// every further piece adds its 64 KB per tile in memory; the whole backward of the gates with 4 and 8 pieces, as many as fill the chip,
+// and with two: n = 1100 51.6 / 44.3 us, 2048 65.4 / 48.3, 4096 78.5 / 64.6; with two heads, one tile, n = 8192 28.6 / 56.4.)
+// Longer calls add in no fixed order: WCHUNK, halved down to WCHUNK_LEAST until the launch has WTARGET workgroups, two per CU.
 constexpr int WCHUNK = 4096, WCHUNK_LEAST = 256;
 constexpr long WTARGET = 512;
 constexpr int WSTEP = 32;
@@ -541,7 +544,11 @@ static hipError_t gate_proj_bwd_branches(int branches, int B, int Hq, int n, int
   const int num_ft = (int)(dm / 128);
   int chunk = WCHUNK;
   auto workgroups = [&]() -> long { return (long)num_ft * num_ft * ((n + chunk - 1) / chunk) * B * branches; };
-  while (chunk > WCHUNK_LEAST && workgroups() < WTARGET) chunk /= 2;
+  if ((long)((n + WCHUNK - 1) / WCHUNK) * B <= 2) {
+    if (B == 1 && n > WCHUNK_LEAST && workgroups() < WTARGET) chunk = ((n + 1) / 2 + WSTEP - 1) / WSTEP * WSTEP;
+  } else {
+    while (chunk > WCHUNK_LEAST && workgroups() < WTARGET) chunk /= 2;
+  }
   const int chunks = (n + chunk - 1) / chunk;
   const long total = workgroups(), blocks = xcd_grid_blocks(total);
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
