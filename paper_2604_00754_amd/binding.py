@@ -83,6 +83,8 @@ def _load():
     lib.sa_decode_fwd_static.argtypes = [dp, vp, vp, vp, C.c_int32, vp, vp, vp]
     lib.sa_decode_fwd_varlen.restype = C.c_int
     lib.sa_decode_fwd_varlen.argtypes = [dp, vp, vp, vp, ip, C.c_int32, vp, vp, vp, sz, vp]
+    lib.sa_internal_fwd_kernel.restype = C.c_char_p
+    lib.sa_internal_fwd_kernel.argtypes = [dp, C.c_int, C.c_int]
     lib.swa_fwd.restype = C.c_int
     lib.swa_fwd.argtypes = [dp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.gated_sa_swa_fwd.restype = C.c_int
@@ -240,6 +242,11 @@ def sa_bwd(sa, swa, Q, K, V, perm, gate_sa, gate_swa, Y_sa, Y_swa, LSE_sa, LSE_s
                        _ptr(dY), _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(dgate_sa), _ptr(dgate_swa),
                        _ptr(ws), (ws.numel() * ws.element_size()) if ws is not None else 0,
                        _stream()), "sa_bwd")
+
+
+def fwd_kernel(desc, permuted=True, rotated=False) -> str:
+    """Name of the kernel that sa_fwd (rotated: sa_fwd_rope) runs on for this descriptor."""
+    return _lib.sa_internal_fwd_kernel(C.byref(desc), int(permuted), int(rotated)).decode()
 
 
 def raw():

@@ -131,3 +131,7 @@ hipError_t launch_bwd_prepare(const Prep& p, hipStream_t st);
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st);
 
 }  // namespace sa
+
+// The kernel that an ungated forward of this descriptor runs on (with an index tensor; with sa_fwd_rope's rotation), for tests
+// and measurements.  No part of include/sa.h.
+extern "C" const char* sa_internal_fwd_kernel(const sa_desc* desc, int permuted, int rotated);

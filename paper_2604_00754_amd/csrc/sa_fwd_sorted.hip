@@ -459,18 +459,32 @@ __global__ __launch_bounds__(NT, 3) void fwd_sorted_bf16_kernel(const Pass p, co
 static long quarters_of(const Pass& p) { return (long)((p.n + GROUP - 1) / GROUP) * (GROUP / 32); }
 
 // Where the shorter walk pays for the list (a workgroup spends about six tiles' time on its prologue, hidden the better the
-// more workgroups a CU goes through).  Measured against the kernel of sa_fwd_mfma.hip, 32 query heads, 8 KV heads, without
-// rotation, us (there / here):
-//   w \ n     2048         4096         8192          32 768       65 536
-//   128       13.6/17.2    24.7/30.2    48.4/53.5     155/165      333/322
-//   256       18.7/20.6    31.7/35.2    61.2/60.5     216/203      437/393
-//   512       27.6/26.7    47.1/46.1    90.6/78.6     330/275      686/535
-//   1024      43.8/39.2    78.1/69.2    147/118       572/422      1162/820
+// more workgroups a CU goes through).  Items: quarters x sets of four heads; window: its slots.  Time here over time of the
+// kernel of sa_fwd_mfma.hip at the line and at the next smaller window measured, 32 query heads on 8 KV heads (4 to 48
+// heads in groups of 4 to 12 are within 0.02 of it), without rotation:
+//   items                256    512    1024   1536   2048   4096   8192   16 384
+//   window at the line   767    639    575    448    383    287    256    192
+//   here / there         0.98   0.98   0.99   0.96   0.95   0.97   0.94   0.99
+//   smaller window       703    575    511    383    351    255    223    159
+//   here / there         1.01   1.00   1.02   1.02   0.98   0.99   0.98   1.02
+// With rotation the other kernel reads the table row of every lane by itself and the lines lie lower: 447 slots 1.00 at 256 items and
+// 0.94 at 768 (383 slots: 1.01, 0.96), 255 slots 0.94 at 2048, 191 slots 0.90 at 8192.
+struct Line {
+  long items;
+  int window;
+};
+constexpr Line kLines[] = {{256, 767}, {512, 639}, {1024, 575}, {1536, 448}, {2048, 383}, {4096, 287}, {8192, 256}, {16384, 192}};
+constexpr Line kLinesRotated[] = {{256, 448}, {2048, 256}, {8192, 192}};
+
 bool fwd_sorted_serves(const Pass& p) {
   const int w = p.win.L + p.win.R + 1;
   if (!(p.d == D && p.perm && p.perm_H == 1 && p.causal && p.g % 4 == 0 && !p.gate_mode && w - 1 + GROUP <= CAP)) return false;
   const long items = quarters_of(p) * (p.Hq >> 2) * p.B;
-  return items >= (w >= 448 ? 256 : (w >= 256 ? 2048 : (w >= 192 ? 8192 : 0x7fffffff)));
+  int least = 0x7fffffff;
+  auto lower = [&](const Line& l) { least = items >= l.items ? l.window : least; };
+  if (p.rope_table) for (const Line& l : kLinesRotated) lower(l);
+  else for (const Line& l : kLines) lower(l);
+  return w >= least;
 }
 
 hipError_t launch_fwd_sorted_bf16(const Pass& p, hipStream_t st) {

@@ -229,3 +229,21 @@ def test_bwd_rope_arguments():
     assert call(desc=f32) == sa.SA_ERR_UNSUPPORTED
     big = sa.make_desc(1, 1, 1, 1 << 23, 128, 512)
     assert call(desc=big, nb=1 << 40) == sa.SA_ERR_UNSUPPORTED
+
+
+def test_forward_kernel_that_each_case_of_its_gpu_test_expects():
+    """The dispatch rule of the forward, asked of the library without a GPU: the cases that test the sorted kernel reach it."""
+    from tests import test_gpu_fwd_sorted as S
+    for *shape, served in S.CASES:
+        assert S.kernel_of(*shape) == ("fwd_sorted_bf16_kernel" if served else "fwd_mfma_bf16_kernel"), shape
+    for case in S.LARGE:
+        assert S.kernel_of(*case) == "fwd_sorted_bf16_kernel", case
+    mk = sa.make_desc
+    assert sa.fwd_kernel(mk(1, 32, 8, 32768, 128, 512)) == "fwd_sorted_bf16_kernel"
+    # no index tensor, another one per head, another head size, groups of two, no causal test, fp32: the general kernels
+    assert sa.fwd_kernel(mk(1, 32, 8, 32768, 128, 512), permuted=False) == "fwd_mfma_bf16_kernel"
+    for d in (mk(1, 32, 8, 32768, 128, 512, perm_H=32), mk(1, 32, 8, 32768, 64, 512), mk(1, 16, 8, 32768, 128, 512),
+              mk(1, 32, 8, 32768, 128, 512, causal_orig=0)):
+        assert sa.fwd_kernel(d) == "fwd_mfma_bf16_kernel"
+    assert sa.fwd_kernel(mk(1, 32, 8, 32768, 128, 512, dtype=sa.SA_F32)) == "fwd_f32_kernel"
+    assert sa.fwd_kernel(mk(1, 32, 8, 0, 128, 512)) == ""
