@@ -295,7 +295,7 @@ __global__ __launch_bounds__(64 * FW, D == 64 ? 4 : 2) void fwd_f32_kernel(const
     load_columns<D>(Vh, pos, g, c, vn);
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (any_not_finite<D>(o, s < n)) {
+  if (__builtin_expect(any_not_finite<D>(o, s < n), 0)) {
     const int le = fresh(lane), g = le >> 4, c = le & 15;
     m = -INFINITY;
     l = 0.f;
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(64 * FW, D == 64 ? 3 : 2) void bwd_dq_f32_kernel(co
     get_columns<D>(stage_k, g, c, x);
     product_columns<D>(dq, x, weigh(blk, st, dp, kpos));
   }
-  if (any_not_finite<D>(dq, s < n)) {
+  if (__builtin_expect(any_not_finite<D>(dq, s < n), 0)) {
     const int le = fresh(lane), g = le >> 4, c = le & 15;
 #pragma unroll
     for (int b = 0; b < D / 16; ++b) dq[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(64 * FW, 2) void bwd_dkv_f32_kernel(const Pass p, c
     for (int i = 0; i < 4; ++i) ds[i] = pr[i] == 0.f ? 0.f : pr[i] * (dp[i] - dd[i]);
     product_columns<D>(dk, x, ds);
   }
-  if (any_not_finite<D>(dk, k < n) || any_not_finite<D>(dv, k < n)) {
+  if (__builtin_expect(any_not_finite<D>(dk, k < n) | any_not_finite<D>(dv, k < n), 0)) {
     const int le = fresh(lane), g = le >> 4, c = le & 15;
 #pragma unroll
     for (int b = 0; b < D / 16; ++b) dk[b] = dv[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -630,12 +630,24 @@ bool f32_shape_ok(const Pass& p) {
 
 }  // namespace
 
-// Wavefronts that share a tile's band.  A call with few tiles needs the split to occupy the chip and to shorten the
-// chain of one tile (B1 H2 n1024 d64 w64, 128 tiles: forward 9.2 / 7.2 / 6.4 us with 1 / 2 / 4); with two tiles per
-// SIMD everything is resident unsplit, and every wavefront that shares a tile repeats its index and row round trips
-// (B2 H8 n2039 d64 w128, 2048 tiles: forward + dQ + dK/dV 87 / 95 / 98 us with 1 / 2 / 4; 711 us with one wavefront per
-// row on vector FMAs, whose lanes each read a row of their own).
-static int wavefronts_per_tile(long tiles) { return tiles < 1024 ? 4 : (tiles < 2048 ? 2 : 1); }
+// Wavefronts that share a tile's band: the most that are all resident at once.  A call with few tiles needs the split to
+// occupy the chip and to shorten the chain of one tile (B1 H2 n1024 d64 w64, 128 tiles: forward 9.2 / 7.2 / 6.4 us with 1 / 2 / 4);
+// past one round of workgroups every wavefront that shares a tile repeats its index and row round trips for nothing.  8 heads,
+// w = 128, us with 1 / 2 / 4, on both sides of the lines:
+//   tiles                  512                640                768                1000               1280               1536               2000
+//   forward d = 64         13.0/10.8/8.6      13.8/11.8/10.6     14.0/12.0/10.6     14.7/13.0/13.7     18.6/15.8/17.4     19.4/18.6/19.8     21.5/20.9/22.8
+//   dQ d = 64              13.7/12.4/11.8     15.4/13.9/13.5     15.8/14.1/14.1     16.4/15.5/18.0     22.3/19.4/22.9     22.9/20.4/23.9     26.2/29.6/30.0
+//   dK, dV d = 64          18.8/16.5/13.4     20.0/17.6/17.0     20.8/18.5/17.5     22.1/20.3/24.6     29.6/25.5/28.3     29.8/27.9/29.4     33.9/38.9/37.6
+//   forward d = 128        18.4/16.2/13.4     19.1/17.8/19.8     20.0/18.7/23.4     21.7/21.3/24.7     30.1/31.5/32.9     31.4/35.6/35.0     36.9/38.2/44.4
+//   dQ d = 128             22.0/20.6/16.4     23.7/22.4/24.6     24.6/23.2/28.8     27.2/26.8/30.4     40.7/38.1/40.7     42.4/46.2/43.8     47.9/50.6/55.7
+//   dK, dV d = 128         32.2/29.2/23.9     34.0/31.4/35.1     35.5/32.7/41.2     39.2/38.6/44.1     53.6/59.7/60.6     56.9/67.5/63.9     69.4/73.6/83.0
+// `resident`: wavefronts that the registers let the 1024 SIMDs hold.  Four to a tile do not pay for a fourth on a SIMD.
+static int wavefronts_per_tile(long tiles, int resident) {
+  if (tiles * 4 <= (resident < 3072 ? resident : 3072)) return 4;
+  return tiles * 2 <= resident ? 2 : 1;
+}
+// (the forward at d = 64: four a SIMD, less a few: B2 H8 n2039 w128, 2048 tiles, forward + backward 84.5 us with one, 88.9 with two)
+constexpr int kResidentFwd64 = 4000, kResidentBwd64 = 3072, kResident128 = 2048;
 
 #define SA_LAUNCH_F32_W(KERNEL_, W_)                                                                              \
   do {                                                                                                            \
@@ -645,14 +657,14 @@ static int wavefronts_per_tile(long tiles) { return tiles < 1024 ? 4 : (tiles < 
     else if (p.perm) hipLaunchKernelGGL((KERNEL_<128, true, W_>), grid, block, 0, st, p, t, w);                   \
     else hipLaunchKernelGGL((KERNEL_<128, false, W_>), grid, block, 0, st, p, t, w);                              \
   } while (0)
-#define SA_LAUNCH_F32(KERNEL_, HEADS_)                                                                            \
+#define SA_LAUNCH_F32(KERNEL_, HEADS_, RES64_)                                                                              \
   do {                                                                                                            \
     const int tiles = (p.n + FT - 1) / FT;                                                                        \
     const long total = (long)tiles * (HEADS_)*p.B;                                                                \
     if (total > 0x7ffffff0L) return hipErrorInvalidValue;                                                         \
     const dim3 grid((unsigned)xcd_grid_blocks(total));                                                            \
     const unsigned t = (unsigned)tiles, w = (unsigned)total;                                                      \
-    switch (wavefronts_per_tile(total)) {                                                                         \
+    switch (wavefronts_per_tile(total, p.d == 64 ? RES64_ : kResident128)) {                                            \
       case 4: SA_LAUNCH_F32_W(KERNEL_, 4); break;                                                                 \
       case 2: SA_LAUNCH_F32_W(KERNEL_, 2); break;                                                                 \
       default: SA_LAUNCH_F32_W(KERNEL_, 1); break;                                                                \
@@ -661,19 +673,19 @@ static int wavefronts_per_tile(long tiles) { return tiles < 1024 ? 4 : (tiles < 
 
 hipError_t launch_fwd_f32(const Pass& p, hipStream_t st) {
   if (!f32_shape_ok(p)) return hipErrorInvalidValue;
-  SA_LAUNCH_F32(fwd_f32_kernel, p.Hq);
+  SA_LAUNCH_F32(fwd_f32_kernel, p.Hq, kResidentFwd64);
   return hipGetLastError();
 }
 
 static hipError_t launch_dkv_f32(const Pass& p, hipStream_t st) {
-  SA_LAUNCH_F32(bwd_dkv_f32_kernel, p.Hkv);
+  SA_LAUNCH_F32(bwd_dkv_f32_kernel, p.Hkv, kResidentBwd64);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_f32(const Pass& p, hipStream_t st) {
   if (!f32_shape_ok(p)) return hipErrorInvalidValue;
   if (p.O_rows ? !p.Dsum_out : !p.Dsum) return hipErrorInvalidValue;
-  SA_LAUNCH_F32(bwd_dq_f32_kernel, p.Hq);
+  SA_LAUNCH_F32(bwd_dq_f32_kernel, p.Hq, kResidentBwd64);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   Pass kv = p;
