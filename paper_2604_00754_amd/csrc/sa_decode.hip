@@ -61,11 +61,11 @@ __device__ __forceinline__ uint32_t dpp_move_u32(uint32_t v) {
 // Halving steps of a transposed sum over a row of 16 lanes (4 banks of 4).  The result is x + x(partner) in
 // the lanes of one half of the banks and y + y(partner) in the other half: each lane gives one of its two values
 // away and keeps the other, so two values cost two instructions instead of four.  A DPP instruction must not
-// read a register in the two issue slots after a vector instruction wrote it, and the compiler does not look
-// inside the block: hence the waits at both ends.
+// read a register in the two issue slots after a vector instruction wrote it, nor any vector instruction one that a dot
+// product wrote in the three before, and the compiler does not look inside the block: hence the waits at both ends.
 __device__ __forceinline__ float add_split_mirror(float x, float y) {        // partner 15 - i; banks {0,1} | {2,3}
   float r;
-  asm("s_nop 1\n\t"
+  asm("s_nop 2\n\t"
       "v_add_f32_dpp %0, %1, %1 row_mirror row_mask:0xf bank_mask:0x3\n\t"
       "v_add_f32_dpp %0, %2, %2 row_mirror row_mask:0xf bank_mask:0xc\n\t"
       "s_nop 1"
@@ -74,7 +74,7 @@ __device__ __forceinline__ float add_split_mirror(float x, float y) {        // 
 }
 __device__ __forceinline__ float add_split_half_mirror(float x, float y) {   // partner 7 - i of each 8; banks {0,2} | {1,3}
   float r;
-  asm("s_nop 1\n\t"
+  asm("s_nop 2\n\t"
       "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
       "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
       "s_nop 1"
