@@ -11,6 +11,8 @@
 // DPP moves inside a row of 16 lanes.
 #include <math.h>
 
+#include <type_traits>
+
 #include "sa_common.h"
 #include "sa_device.h"
 
@@ -32,9 +34,10 @@ namespace {
 
 constexpr int kChunkRows = 512;     // cached rows per workgroup at most (its set-up and the merge favour long chunks)
 constexpr int kTargetGroups = 512;  // shorter chunks (down to 64 rows) are taken until the launch has this many workgroups
-// Rows in use that exceed the memory-side cache (256 MB) are streamed past it: 16 sequences of up to 8192 rows, 8 KV heads, 74.5 ->
-// 71.8 us; a cache that fits is found there by the next token, and the hint costs (134 MB: 24.1 -> 25.4 us).
-constexpr double kCacheBytes = 256e6;
+// Rows in use that exceed the memory-side cache (256 MB) by enough are streamed past it; what fits, or nearly, is found there by
+// the next token.  16 sequences of 8 KV heads, cached / streamed us: 200 MB in use 35.9 / 37.1, 256 MB 48.3 / 50.6, 288 MB
+// 54.4 / 55.0, 320 MB 61.5 / 59.1, 384 MB 75.7 / 67.6, 512 MB 98.9 / 88.0 (16 KV heads of 64: 288 MB 45.8 / 46.1, 320 MB 51.7 / 49.6).
+constexpr double kCacheBytes = 300e6;
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 
@@ -112,8 +115,9 @@ struct Args {
   const void* V;
   float* part;      // [B*Hq][splits][d + 2]: weighted V sum, then running max (log2 domain) and sum
   const int32_t* lens;   // per-sequence row counts [B] or nullptr (then every sequence has `len` rows)
-  int Hq, Hkv, g, n, len, chunk, splits;
+  int B, Hq, Hkv, g, n, len, chunk, splits;
   float scale_log2e;
+  float stream_rows;     // rows in use, of all sequences together, from which on they are streamed past the cache
 };
 
 // exp2(a - b) where b is the reference maximum; a = b = -inf (nothing seen yet) gives 0
@@ -214,8 +218,13 @@ struct Lane<bf16_t, G, U> {
   }
 };
 
-// ONCE: the rows are loaded with the non-temporal hint (they do not fit the cache until the next token reads them again).
-template <typename T, int D, int G, bool ONCE>
+// Whether rows are loaded with the non-temporal hint: never, always (they do not fit the cache until the next token reads them
+// again), or if the lengths of the sequences add up to a.stream_rows (up to 16 of them, evenly spread, stand for a longer batch).
+// The host knows only the longest: 12 sequences of which one has 16 384 rows and the others 1000 (16 KV heads of 64, 112 of at
+// most 805 MB) take 44.5 us cached and 64.2 streamed.  The lengths arrive with the workgroup's own; a kernel that waited
+// for them first took 62.7 -> 69.9 us for 16 sequences of 4000 rows and one of 8192.
+enum { CACHED = 0, STREAMED = 1, BY_LENS = 2 };
+template <typename T, int D, int G, int MODE>
 __global__ __launch_bounds__(kThreads, DECODE_WAVES_PER_SIMD(T, D, G)) void decode_partial_kernel(Args a) {
   constexpr int LPR = D / 8;          // lanes per row
   constexpr int KPW = 64 / LPR;       // rows per wave-wide load
@@ -236,6 +245,13 @@ __global__ __launch_bounds__(kThreads, DECODE_WAVES_PER_SIMD(T, D, G)) void deco
   const size_t head_off = ((size_t)b * a.Hkv + hk) * (size_t)a.n * D + sub * 8;
   const T* Kh = reinterpret_cast<const T*>(a.K) + head_off;
   const T* Vh = reinterpret_cast<const T*>(a.V) + head_off;
+
+  int in_sample = 0, samples = 1;
+  if constexpr (MODE == BY_LENS) {
+    const int step = (a.B + 15) / 16, i = (lane & 15) * step;
+    in_sample = i < a.B ? a.lens[i] : 0;
+    samples = (a.B + step - 1) / step;
+  }
 
   Lane<T, G, U> st;
   float acc[G][8], m[G], l[G];
@@ -259,14 +275,30 @@ __global__ __launch_bounds__(kThreads, DECODE_WAVES_PER_SIMD(T, D, G)) void deco
     }
     return;
   }
+  bool once = false;
+  if constexpr (MODE == BY_LENS) {
+    const float rows = row_sum<16>((lane & 15) < samples ? (float)min(max(in_sample, 1), a.len) : 0.f);
+    once = __builtin_amdgcn_readfirstlane(rows * (float)a.B >= a.stream_rows * (float)samples ? 1 : 0) != 0;
+  }
   for (int it = k0; it < k1; it += STEP * U) {
     bool valid[U];
+    auto load = [&](auto hint) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = it + u * STEP + wave * KPW + grp;
-      valid[u] = j < k1;
-      const size_t row = (size_t)(valid[u] ? j : k1 - 1) * D;   // rows past the chunk re-read its last row
-      st.template load_row<ONCE>(Kh + row, Vh + row, u);
+      for (int u = 0; u < U; ++u) {
+        const int j = it + u * STEP + wave * KPW + grp;
+        valid[u] = j < k1;
+        const size_t row = (size_t)(valid[u] ? j : k1 - 1) * D;   // rows past the chunk re-read its last row
+        st.template load_row<decltype(hint)::value>(Kh + row, Vh + row, u);
+      }
+    };
+    if constexpr (MODE != BY_LENS) {
+      load(std::integral_constant<bool, MODE == STREAMED>{});
+    } else if (once) {
+      asm volatile("" ::: "memory");  // (the two sides would be made one, without the hint)
+      load(std::true_type{});
+      asm volatile("" ::: "memory");
+    } else {
+      load(std::false_type{});
     }
     if constexpr (kTransposed) {
       // Bank b of a row of 16 lanes ends up with the scores of load u = b only (all G heads), computes their
@@ -320,7 +352,6 @@ __global__ __launch_bounds__(kThreads, DECODE_WAVES_PER_SIMD(T, D, G)) void deco
       m[h] = mn;
     }
   }
-
   if constexpr (kTransposed) {   // every bank of a row kept its own share of the sums
 #pragma unroll
     for (int h = 0; h < G; ++h) {
@@ -452,7 +483,8 @@ size_t head_groups(int B, int Hkv, int g) { return (size_t)B * Hkv * (g / heads_
 size_t chunks_of(int rows, int chunk) { return ((size_t)rows + chunk - 1) / chunk; }
 
 // Rows per chunk of a cache with `rows` rows in use, cut into `most` chunks at most: as many chunks as give the launch
-// kTargetGroups workgroups, of 64 to kChunkRows rows each, in steps of 64 (the rows of an unrolled load at d = 128).
+// kTargetGroups workgroups, of 64 to kChunkRows rows each, in steps of 64 (the rows of an unrolled load at d = 128; half of one at
+// d = 64, where steps of 128 measured the same to 4 % and chunks of 128 for 8000 rows of 12 heads 12 % slower than of 64).
 // Cut by the rows in use and not by the capacity, a short sequence in a long cache still fills the chip (1100 rows of
 // 32 768, 8 KV heads: 144 workgroups instead of 24, 12.2 -> 5.9 us).
 int chunk_rows(size_t groups, int rows, size_t most) {
@@ -470,10 +502,13 @@ template <typename T, int D, int G>
 hipError_t launch_typed(const Decode& d, const Args& a, hipStream_t st) {
   const int gsets = a.g / G;
   dim3 grid((unsigned)a.splits, (unsigned)(d.B * d.Hkv * gsets));
-  bool once = false;
-  if constexpr (sizeof(T) == 2) once = 2.0 * d.B * d.Hkv * a.len * D * sizeof(T) >= kCacheBytes;
-  if (once) decode_partial_kernel<T, D, G, sizeof(T) == 2><<<grid, kThreads, 0, st>>>(a);
-  else decode_partial_kernel<T, D, G, false><<<grid, kThreads, 0, st>>>(a);
+  bool large = false;
+  if constexpr (sizeof(T) == 2) {
+    large = (float)d.B * (float)a.len >= a.stream_rows;
+    if (large && a.lens) decode_partial_kernel<T, D, G, BY_LENS><<<grid, kThreads, 0, st>>>(a);
+    else if (large) decode_partial_kernel<T, D, G, STREAMED><<<grid, kThreads, 0, st>>>(a);
+  }
+  if (!large) decode_partial_kernel<T, D, G, CACHED><<<grid, kThreads, 0, st>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   decode_merge_kernel<T, D><<<d.B * d.Hq, kMergeWaves * 64, 0, st>>>(a.part, reinterpret_cast<T*>(d.Y), d.LSE, a.splits);
@@ -503,11 +538,12 @@ hipError_t launch_decode(const Decode& d, hipStream_t st) {
   a.q = d.q; a.K = d.K; a.V = d.V;
   a.part = d.part;
   a.lens = d.lens;
-  a.Hq = d.Hq; a.Hkv = d.Hkv; a.g = d.Hq / d.Hkv; a.n = d.n; a.len = d.len;
+  a.B = d.B; a.Hq = d.Hq; a.Hkv = d.Hkv; a.g = d.Hq / d.Hkv; a.n = d.n; a.len = d.len;
   const size_t groups = head_groups(d.B, d.Hkv, a.g);
   a.chunk = chunk_rows(groups, d.len, most_chunks(groups, d.n));
   a.splits = (int)chunks_of(d.len, a.chunk);
   a.scale_log2e = d.scale * kLog2e;
+  a.stream_rows = (float)(kCacheBytes / (4.0 * d.Hkv * d.d));  // bf16 K and V
   if ((long long)d.B * d.Hkv * a.g > 65535) return hipErrorInvalidValue;   // grid.y
   if (d.bf16) return d.d == 64 ? launch_heads<bf16_t, 64>(d, a, st) : launch_heads<bf16_t, 128>(d, a, st);
   return d.d == 64 ? launch_heads<float, 64>(d, a, st) : launch_heads<float, 128>(d, a, st);
