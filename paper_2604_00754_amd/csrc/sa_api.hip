@@ -540,34 +540,37 @@ sa_status sa_bwd(const sa_desc* sa_d, const sa_desc* swa_d, const void* Q, const
   hipStream_t st = (hipStream_t)stream;
   char* base = reinterpret_cast<char*>(ws);
 
-  sa::Prep pr = {};
-  pr.rows = sa_d->B * sa_d->Hq * sa_d->n;
-  pr.d = sa_d->d;
-  pr.bf16 = sa_d->dtype == SA_BF16;
-  pr.gated = gated;
-  pr.gate_per_dim = sa_d->gate_per_dim;
-  pr.gate_f32 = sa_d->gate_dtype == SA_F32;
-  pr.dY = dY;
-  pr.Y_a = Y_sa; pr.Y_b = Y_swa;
-  pr.gate_a = gate_sa; pr.gate_b = gate_swa;
-  pr.D_a = reinterpret_cast<float*>(base + w.off_Da);
-  pr.D_b = gated ? reinterpret_cast<float*>(base + w.off_Db) : nullptr;
-  pr.dO_a = gated ? base + w.off_dOa : nullptr;
-  pr.dO_b = gated ? base + w.off_dOb : nullptr;
-  pr.dgate_a = dgate_sa; pr.dgate_b = dgate_swa;
-  // bf16, one gate per (head, token): the gate goes into the per-row scalars, both branches run on dY itself
-  // (the two shifted LSE vectors take the place of the first branch gradient in the workspace)
-  const bool fold = gated && !sa_d->gate_per_dim && sa_d->dtype == SA_BF16;
-  pr.fold = fold;
-  pr.lse_a = LSE_sa; pr.lse_b = LSE_swa;
-  pr.L_a = fold ? reinterpret_cast<float*>(base + w.off_dOa) : nullptr;
-  pr.L_b = fold ? pr.L_a + (size_t)pr.rows : nullptr;
-  // ungated: no separate pass, the dQ kernel forms rowsum(dY o Y) from the rows it holds
-  const bool rowsum_in_dq = !gated;
-  hipError_t e = rowsum_in_dq ? hipSuccess : sa::launch_bwd_prepare(pr, st);
-  if (e != hipSuccess) return hip_status(e);
-
+  float* D_a = reinterpret_cast<float*>(base + w.off_Da);
+  // ungated: the dQ kernel forms rowsum(dY o Y) from the rows it holds and leaves it in D_a
+  Pass b = make_pass(sa_d, Q, K, V, perm);
+  b.dO = dY;
+  b.lse_in = LSE_sa;
+  b.Dsum = D_a;
+  if (!gated) { b.O_rows = Y_sa; b.Dsum_out = D_a; }
+  b.dQ = dQ; b.dK = dK; b.dV = dV; b.accumulate = gated ? 1 : 0;
   if (gated) {
+    sa::Prep pr = {};
+    pr.rows = sa_d->B * sa_d->Hq * sa_d->n;
+    pr.d = sa_d->d;
+    pr.bf16 = sa_d->dtype == SA_BF16;
+    pr.gate_per_dim = sa_d->gate_per_dim;
+    pr.gate_f32 = sa_d->gate_dtype == SA_F32;
+    pr.dY = dY;
+    pr.Y_a = Y_sa; pr.Y_b = Y_swa;
+    pr.gate_a = gate_sa; pr.gate_b = gate_swa;
+    pr.D_a = D_a;
+    pr.D_b = reinterpret_cast<float*>(base + w.off_Db);
+    pr.dO_a = base + w.off_dOa;
+    pr.dO_b = base + w.off_dOb;
+    pr.dgate_a = dgate_sa; pr.dgate_b = dgate_swa;
+    // bf16, one gate per (head, token): the gate goes into the per-row scalars, both branches run on dY itself
+    // (the two shifted LSE vectors take the place of the first branch gradient in the workspace)
+    const bool fold = !sa_d->gate_per_dim && sa_d->dtype == SA_BF16;
+    pr.lse_a = LSE_sa; pr.lse_b = LSE_swa;
+    pr.L_a = fold ? reinterpret_cast<float*>(base + w.off_dOa) : nullptr;
+    pr.L_b = fold ? pr.L_a + (size_t)pr.rows : nullptr;
+    hipError_t e = sa::launch_bwd_prepare(pr, st);
+    if (e != hipSuccess) return hip_status(e);
     Pass a = make_pass(swa_d, Q, K, V, nullptr);
     a.dO = fold ? dY : pr.dO_b;
     a.lse_in = fold ? pr.L_b : LSE_swa;
@@ -575,13 +578,9 @@ sa_status sa_bwd(const sa_desc* sa_d, const sa_desc* swa_d, const void* Q, const
     a.dQ = dQ; a.dK = dK; a.dV = dV; a.accumulate = 0;
     e = run_bwd(swa_d, a, st);
     if (e != hipSuccess) return hip_status(e);
+    if (!fold) b.dO = pr.dO_a;
+    else b.lse_in = pr.L_a;
   }
-  Pass b = make_pass(sa_d, Q, K, V, perm);
-  b.dO = gated && !fold ? pr.dO_a : dY;
-  b.lse_in = fold ? pr.L_a : LSE_sa;
-  b.Dsum = pr.D_a;
-  if (rowsum_in_dq) { b.O_rows = Y_sa; b.Dsum_out = pr.D_a; }
-  b.dQ = dQ; b.dK = dK; b.dV = dV; b.accumulate = gated ? 1 : 0;
   return hip_status(run_bwd(sa_d, b, st));
 }
 

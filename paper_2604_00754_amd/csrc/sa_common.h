@@ -48,7 +48,7 @@ struct Pass {
   const void* dO;       // gradient w.r.t. this branch's output [B,Hq,n,d]
   const float* lse_in;  // [B,Hq,n]
   const float* Dsum;    // rowsum(dO * O) [B,Hq,n]
-  const void* O_rows;   // bf16 path, optional: this branch's output rows [B,Hq,n,d]; when given, the dQ kernel forms
+  const void* O_rows;   // optional: this branch's output rows [B,Hq,n,d]; when given, the dQ kernel forms
   float* Dsum_out;      // rowsum(dO * O) itself from its stationary rows and leaves it here for the dK/dV kernel
   void* dQ;
   void* dK;
@@ -70,7 +70,8 @@ hipError_t launch_fwd_sorted_bf16(const Pass& p, hipStream_t st);
 hipError_t launch_bwd_mfma_bf16(const Pass& p, hipStream_t st);
 
 hipError_t launch_permuted_copy_bf16(const Pass& p, hipStream_t st);
-// ws = nullptr: O(n^2) rank counting, no workspace; otherwise sample_perm_workspace_bytes(slices, n) bytes
+// ws = nullptr: one launch, every bucket of keys gathered by a pass over all of them; otherwise
+// sample_perm_workspace_bytes(slices, n) bytes, in which longer calls leave every key once, ordered by bucket
 hipError_t launch_sample_perm(int32_t* perm, int slices, int n, uint64_t seed, int layer, void* ws, hipStream_t st);
 size_t sample_perm_workspace_bytes(int slices, int n);
 // Eq. 6 + Eq. 5 (sa_gate_proj.hip); Y_swa = W_swa = nullptr selects the single-path gate
@@ -107,23 +108,22 @@ hipError_t launch_decode(const Decode& d, hipStream_t st);
 // helpers in sa_misc.hip
 hipError_t launch_check_perm(const int32_t* perm, int slices, int n, int* seen, int* flag,
                              hipStream_t st);
-// D = rowsum(dO * O); for the gated case also dO_x = sig(gamma_x) * dY and the gate-logit gradients.
+// Gated backward: dO_x = sig(gamma_x) * dY, D_x = rowsum(dO_x * Y_x) and the gate-logit gradients of both branches.
 struct Prep {
   int rows, d;               // rows = B*Hq*n
   int bf16;                  // dtype of Y, dY, dO
-  int gated, gate_per_dim, gate_f32;
+  int gate_per_dim, gate_f32;
   const void* dY;
-  const void* Y_a;  const void* Y_b;          // branch outputs (b unused when not gated)
+  const void* Y_a;  const void* Y_b;          // branch outputs
   const void* gate_a; const void* gate_b;
-  void* dO_a; void* dO_b;                      // gated only
+  void* dO_a; void* dO_b;
   float* D_a; float* D_b;
   void* dgate_a; void* dgate_b;
-  // gated with one gate per (head, token) and fold != 0: the gate is folded into the per-row scalars instead
+  // bf16 with one gate per (head, token): the gate is folded into the per-row scalars instead
   // of into a copy of dY.  With g = sigmoid(gamma_x): dO_x = g dY, so P^T dO_x = (g P)^T dY and
   // dS_x = P (dO_x V^T - D_x) = (g P) (dY V^T - E_x) with E_x = rowsum(dY * Y_x) = D_x / g.  The backward
   // kernels then run on dY itself with LSE_x - ln g in place of LSE_x (which turns P into g P) and E_x in
   // place of D_x; g = 0 gives +inf and P = 0.  D_a / D_b receive E_x, L_a / L_b the shifted LSE.
-  int fold;
   const float* lse_a; const float* lse_b;
   float* L_a; float* L_b;
 };

@@ -191,7 +191,7 @@ __global__ __launch_bounds__(NT, 3) void fwd_sorted_bf16_kernel(const Pass p, co
   else if (band <= 5 * NT) build(std::integral_constant<int, 5>{});
   else build(std::integral_constant<int, CAP / NT>{});
 
-  // ---- query rows on their way
+  // ---- loads of the query rows (issued per head set, once the list is complete)
   constexpr int NP = 8;  // passes of 4 rows
   const int prow = lane >> 4, chunk16 = lane & 15;
   u32x4 qv[NP];

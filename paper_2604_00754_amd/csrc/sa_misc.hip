@@ -1,5 +1,5 @@
-// Element-wise helpers of libsa: permutation check, zero fill, and the backward's preparation pass
-// (D = rowsum(dO * O), and for the gated sum of Eq. 5 the chain rule through the two sigmoid gates).
+// Element-wise helpers of libsa: permutation check, zero fill, permutation sampling, and the gated backward's preparation
+// pass (the chain rule through the two sigmoid gates of Eq. 5, and D = rowsum(dO * O) of both branches).
 #include "sa_common.h"
 #include "sa_device.h"
 
@@ -275,35 +275,24 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(Prep p) {
       dy[2 * k] = bf16lo(a[k]); dy[2 * k + 1] = bf16hi(a[k]);
       ya[2 * k] = bf16lo(b[k]); ya[2 * k + 1] = bf16hi(b[k]);
     }
-    if (p.gated) {
-      const u32x4 c = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(p.Y_b) + off);
+    const u32x4 c = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(p.Y_b) + off);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { yb[2 * k] = bf16lo(c[k]); yb[2 * k + 1] = bf16hi(c[k]); }
-    }
+    for (int k = 0; k < 4; ++k) { yb[2 * k] = bf16lo(c[k]); yb[2 * k + 1] = bf16hi(c[k]); }
   } else {
     const f32x4 a = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.dY) + off);
     const f32x4 b = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.Y_a) + off);
 #pragma unroll
     for (int k = 0; k < 4; ++k) { dy[k] = a[k]; ya[k] = b[k]; }
-    if (p.gated) {
-      const f32x4 c = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.Y_b) + off);
+    const f32x4 c = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.Y_b) + off);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) yb[k] = c[k];
-    }
+    for (int k = 0; k < 4; ++k) yb[k] = c[k];
   }
 
-  if (!p.gated) {
-    float s = 0.f;
-#pragma unroll
-    for (int k = 0; k < E; ++k) s = fmaf(dy[k], ya[k], s);
-    s = group_sum<LPR>(s);
-    if (valid && sub == 0) p.D_a[r] = s;
-    return;
-  }
-
-  // gated: dO_x = sig(gamma_x) * dY;  D_x = sum_d dO_x * Y_x;  dgamma_x = sig'(gamma_x) * dY * Y_x
+  // dO_x = sig(gamma_x) * dY;  D_x = sum_d dO_x * Y_x;  dgamma_x = sig'(gamma_x) * dY * Y_x
+  // (bf16 rows with one gate each go to bwd_fold_kernel)
+  const bool per_dim = BF16 || p.gate_per_dim;
   float ga[E], gb[E];
-  if (p.gate_per_dim) {
+  if (per_dim) {
 #pragma unroll
     for (int k = 0; k < E; ++k) {
       ga[k] = sigmoidf_exact(load_gate(p.gate_a, off + k, p.gate_f32));
@@ -334,7 +323,7 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(Prep p) {
     p.D_a[r] = sa;
     p.D_b[r] = sb;
   }
-  if (p.gate_per_dim) {
+  if (per_dim) {
     if (valid) {
 #pragma unroll
       for (int k = 0; k < E; ++k) {
@@ -420,16 +409,15 @@ __global__ __launch_bounds__(256) void bwd_fold_kernel(const Prep p) {
   store_gate(is_b ? p.dgate_b : p.dgate_a, r, p.gate_f32, g * (1.f - g) * e);
 }
 
+template <int LPR>
+hipError_t launch_fold_t(const Prep& p, hipStream_t st) {
+  const long per_block = 4 * 32;  // rows: LPR / 2 rows of 64 / LPR groups in each of 4 waves
+  hipLaunchKernelGGL(bwd_fold_kernel<LPR>, dim3((unsigned)((p.rows + per_block - 1) / per_block)), dim3(256), 0, st, p);
+  return hipGetLastError();
+}
+
 template <bool BF16, int LPR>
 hipError_t launch_prepare_t(const Prep& p, hipStream_t st) {
-  if (p.fold) {
-    if constexpr (BF16) {
-      const long per_block = 4 * 32;  // rows: LPR / 2 rows of 64 / LPR groups in each of 4 waves
-      hipLaunchKernelGGL(bwd_fold_kernel<LPR>, dim3((unsigned)((p.rows + per_block - 1) / per_block)), dim3(256), 0, st, p);
-      return hipGetLastError();
-    }
-    return hipErrorInvalidValue;
-  }
   const long threads = (long)p.rows * LPR;
   const unsigned blocks = (unsigned)((threads + 255) / 256);
   hipLaunchKernelGGL((bwd_prepare_kernel<BF16, LPR>), dim3(blocks), dim3(256), 0, st, p);
@@ -465,8 +453,8 @@ static int sample_bits(int n, int per_bucket) {
   return bits;
 }
 
-// Binned form: 128 keys a bucket (256 from 2^19 slots on: SAMPLE_MAX_BUCKETS), pieces of at least as many slots as there
-// are buckets, so that the boundaries stay smaller than the keys.
+// Binned form: 64 to 128 keys a bucket on average (past 2^19 slots, with SAMPLE_MAX_BUCKETS, up to 256), pieces of at
+// least as many slots as there are buckets, so that the boundaries stay smaller than the keys.
 static SampleWs sample_layout(int n) {
   SampleWs w = {};
   int bits = sample_bits(n, 128);
@@ -519,6 +507,7 @@ hipError_t launch_permuted_copy_bf16(const Pass& p, hipStream_t st) {
 
 hipError_t launch_bwd_prepare(const Prep& p, hipStream_t st) {
   if (p.rows < 1 || !(p.d == 64 || p.d == 128)) return hipErrorInvalidValue;
+  if (p.bf16 && !p.gate_per_dim) return p.d == 64 ? launch_fold_t<8>(p, st) : launch_fold_t<16>(p, st);
   if (p.bf16) return p.d == 64 ? launch_prepare_t<true, 8>(p, st) : launch_prepare_t<true, 16>(p, st);
   return p.d == 64 ? launch_prepare_t<false, 16>(p, st) : launch_prepare_t<false, 32>(p, st);
 }

@@ -10,12 +10,13 @@ pytestmark = pytest.mark.gpu
 
 
 def sample(B, H, perm_B, perm_H, n, seed, layer, workspace=False):
-    """workspace=False: the O(n^2) rank count; True: the bucketed O(n) path with its workspace."""
+    """workspace=False: every bucket of keys gathered by a pass over all of them; True: with the workspace, where longer calls leave
+    every key once."""
     from paper_2604_00754_amd import binding as sa
     desc = sa.make_desc(B, H, H, n, 64, 8, perm_B=perm_B, perm_H=perm_H)
     perm = torch.full((perm_B, perm_H, n), -1, device=U.DEV, dtype=torch.int32)
     ws = None
-    if workspace:  # filled with ones: the call must clear what it counts in
+    if workspace:  # filled with ones: nothing may be read from it that the call did not write
         ws = torch.full((sa.sa_workspace_bytes(desc, sa.SA_OP_SAMPLE_PERM),), 0xFF, device=U.DEV, dtype=torch.uint8)
     sa.sa_sample_perm(desc, seed, layer, perm, ws)
     torch.cuda.synchronize()
