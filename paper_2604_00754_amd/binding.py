@@ -83,6 +83,8 @@ def _load():
     lib.sa_decode_fwd_static.argtypes = [dp, vp, vp, vp, C.c_int32, vp, vp, vp]
     lib.sa_decode_fwd_varlen.restype = C.c_int
     lib.sa_decode_fwd_varlen.argtypes = [dp, vp, vp, vp, ip, C.c_int32, vp, vp, vp, sz, vp]
+    lib.sa_internal_sample_perm.restype = C.c_int
+    lib.sa_internal_sample_perm.argtypes = [dp, C.c_uint64, C.c_int32, ip, vp, sz, C.c_int, vp]
     lib.sa_internal_fwd_kernel.restype = C.c_char_p
     lib.sa_internal_fwd_kernel.argtypes = [dp, C.c_int, C.c_int]
     lib.swa_fwd.restype = C.c_int

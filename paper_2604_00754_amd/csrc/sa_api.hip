@@ -310,6 +310,11 @@ sa_status decode_common(const sa_desc* c, const void* q, const void* K, const vo
 
 sa_status sa_sample_perm(const sa_desc* c, uint64_t seed, int32_t layer, int32_t* perm, void* ws, size_t ws_bytes,
                          void* stream) {
+  return sa_internal_sample_perm(c, seed, layer, perm, ws, ws_bytes, 0, stream);
+}
+
+sa_status sa_internal_sample_perm(const sa_desc* c, uint64_t seed, int32_t layer, int32_t* perm, void* ws, size_t ws_bytes, int cap,
+                                  void* stream) {
   sa_status s = validate_desc(c);
   if (s != SA_OK) return s;
   if (!perm) return SA_ERR_NULL;
@@ -318,7 +323,7 @@ sa_status sa_sample_perm(const sa_desc* c, uint64_t seed, int32_t layer, int32_t
   if (c->n > (1 << 20)) return SA_ERR_UNSUPPORTED;
   const int slices = c->perm_B * c->perm_H;
   if (ws && ws_bytes < sa::sample_perm_workspace_bytes(slices, c->n)) return SA_ERR_WORKSPACE;
-  return hip_status(sa::launch_sample_perm(perm, slices, c->n, seed, layer, ws, (hipStream_t)stream));
+  return hip_status(sa::launch_sample_perm(perm, slices, c->n, seed, layer, ws, (hipStream_t)stream, cap));
 }
 
 sa_status sa_fwd_rope(const sa_desc* c, const void* Q, const void* K, const void* V, const int32_t* perm,

@@ -72,7 +72,8 @@ hipError_t launch_bwd_mfma_bf16(const Pass& p, hipStream_t st);
 hipError_t launch_permuted_copy_bf16(const Pass& p, hipStream_t st);
 // ws = nullptr: one launch, every bucket of keys gathered by a pass over all of them; otherwise
 // sample_perm_workspace_bytes(slices, n) bytes, in which longer calls leave every key once, ordered by bucket
-hipError_t launch_sample_perm(int32_t* perm, int slices, int n, uint64_t seed, int layer, void* ws, hipStream_t st);
+// (cap: keys of a bucket kept in LDS, 0 = as many as fit; a bucket with more is ranked another way)
+hipError_t launch_sample_perm(int32_t* perm, int slices, int n, uint64_t seed, int layer, void* ws, hipStream_t st, int cap = 0);
 size_t sample_perm_workspace_bytes(int slices, int n);
 // Eq. 6 + Eq. 5 (sa_gate_proj.hip); Y_swa = W_swa = nullptr selects the single-path gate
 hipError_t launch_gate_proj_fwd_bf16(int B, int Hq, int n, int d, const void* Y_sa, const void* Y_swa,
@@ -132,6 +133,11 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st);
 
 }  // namespace sa
 
-// The kernel that an ungated forward of this descriptor runs on (with an index tensor; with sa_fwd_rope's rotation), for tests
-// and measurements.  No part of include/sa.h.
-extern "C" const char* sa_internal_fwd_kernel(const sa_desc* desc, int permuted, int rotated);
+// For tests and measurements; no part of include/sa.h.
+extern "C" {
+// the kernel that an ungated forward of this descriptor runs on (with an index tensor; with sa_fwd_rope's rotation)
+const char* sa_internal_fwd_kernel(const sa_desc* desc, int permuted, int rotated);
+// sa_sample_perm with room for `cap` keys of a bucket
+sa_status sa_internal_sample_perm(const sa_desc* desc, uint64_t seed, int32_t layer, int32_t* perm, void* ws, size_t ws_bytes, int cap,
+                                  void* stream);
+}

@@ -142,9 +142,9 @@ __device__ void rank_oversized(uint64_t stream, int bucket, int shift, int n, in
   }
 }
 
-// grid (buckets, slices); bucket of key k = k >> shift, shift <= 63
+// grid (buckets, slices); bucket of key k = k >> shift, shift <= 63; cap <= SAMPLE_CAP
 __global__ __launch_bounds__(256) void sample_scan_kernel(int32_t* __restrict__ perm, const int n, const uint64_t seed, const int layer,
-                                                          const int shift) {
+                                                          const int shift, const int cap) {
   __shared__ uint64_t keys[SAMPLE_CAP];
   __shared__ int counters[2];  // keys in the bucket, keys below it
   const int bucket = blockIdx.x, slice = blockIdx.y;
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void sample_scan_kernel(int32_t* __restrict__ 
     lower += b < bucket ? 1 : 0;
     if (b == bucket) {
       const int at = atomicAdd(&counters[0], 1);
-      if (at < SAMPLE_CAP) keys[at] = k;
+      if (at < cap) keys[at] = k;
     }
   }
 #pragma unroll
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void sample_scan_kernel(int32_t* __restrict__ 
   __syncthreads();
   const int cnt = counters[0];
   int32_t* out = perm + (size_t)slice * n;
-  if (cnt > SAMPLE_CAP) rank_oversized(stream, bucket, shift, n, out);
+  if (cnt > cap) rank_oversized(stream, bucket, shift, n, out);
   else rank_bucket(keys, cnt, counters[1], out);
 }
 
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void sample_bin_kernel(const SampleWs w, const
 
 // grid (buckets, slices)
 __global__ __launch_bounds__(256) void sample_merge_kernel(const SampleWs w, int32_t* __restrict__ perm, const int n, const uint64_t seed,
-                                                           const int layer) {
+                                                           const int layer, const int cap) {
   __shared__ uint64_t keys[SAMPLE_CAP];
   __shared__ int counters[2];
   const int bucket = blockIdx.x, slice = blockIdx.y;
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(256) void sample_merge_kernel(const SampleWs w, int
     lower += i0;
     int at = i1 > i0 ? atomicAdd(&counters[0], i1 - i0) : 0;
     for (int i = i0; i < i1; ++i, ++at)
-      if (at < SAMPLE_CAP) keys[at] = src[i];
+      if (at < cap) keys[at] = src[i];
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) lower += __shfl_xor(lower, o);
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void sample_merge_kernel(const SampleWs w, int
   __syncthreads();
   const int cnt = counters[0];
   int32_t* out = perm + (size_t)slice * n;
-  if (cnt > SAMPLE_CAP) rank_oversized(slice_stream(seed, layer, slice), bucket, w.shift, n, out);
+  if (cnt > cap) rank_oversized(slice_stream(seed, layer, slice), bucket, w.shift, n, out);
   else rank_bucket(keys, cnt, counters[1], out);
 }
 
@@ -471,7 +471,8 @@ size_t sample_perm_workspace_bytes(int slices, int n) {
   return (size_t)slices * ((size_t)n * 8 + (size_t)w.pieces * (w.buckets + 1) * 2) + 512;
 }
 
-hipError_t launch_sample_perm(int32_t* perm, int slices, int n, uint64_t seed, int layer, void* ws, hipStream_t st) {
+hipError_t launch_sample_perm(int32_t* perm, int slices, int n, uint64_t seed, int layer, void* ws, hipStream_t st, int cap) {
+  if (cap < 1 || cap > SAMPLE_CAP) cap = SAMPLE_CAP;
   if (!perm || slices < 1 || slices > 65535 || n < 1) return hipErrorInvalidValue;
   if (n > (1 << 20)) return hipErrorNotSupported;  // the slot index takes the low 20 bits of the sort key
   const int bits = sample_bits(n, n <= 32768 ? 64 : 256);
@@ -485,10 +486,10 @@ hipError_t launch_sample_perm(int32_t* perm, int slices, int n, uint64_t seed, i
     w.keys = reinterpret_cast<uint64_t*>(base);
     w.bounds = reinterpret_cast<uint16_t*>(base + (size_t)slices * n * 8);
     hipLaunchKernelGGL(sample_bin_kernel, dim3((unsigned)w.pieces, (unsigned)slices), dim3(256), 0, st, w, n, seed, layer);
-    hipLaunchKernelGGL(sample_merge_kernel, dim3((unsigned)w.buckets, (unsigned)slices), dim3(256), 0, st, w, perm, n, seed, layer);
+    hipLaunchKernelGGL(sample_merge_kernel, dim3((unsigned)w.buckets, (unsigned)slices), dim3(256), 0, st, w, perm, n, seed, layer, cap);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(sample_scan_kernel, dim3(1u << bits, (unsigned)slices), dim3(256), 0, st, perm, n, seed, layer, 64 - bits);
+  hipLaunchKernelGGL(sample_scan_kernel, dim3(1u << bits, (unsigned)slices), dim3(256), 0, st, perm, n, seed, layer, 64 - bits, cap);
   return hipGetLastError();
 }
 

@@ -96,3 +96,22 @@ def test_sample_perm_gathering_forms(slices, n):
     for workspace in (False, True):
         _, perm = sample(1, slices, 1, slices, n, 31, 4, workspace)
         assert np.array_equal(perm.cpu().numpy(), ref), f"workspace={workspace}"
+
+
+@pytest.mark.parametrize("workspace", [False, True])
+@pytest.mark.parametrize("cap", [1, 40, 64, 140])
+@pytest.mark.parametrize("slices,n", [(2, 300), (3, 20000)])
+def test_sample_perm_buckets_that_do_not_fit(slices, n, cap, workspace):
+    """With room for fewer keys than a bucket holds (64 to 128 on average) some or all buckets are ranked by a pass over every key:
+    the same permutation, bit for bit."""
+    import ctypes as C
+    from oracle import perm_sampler as ps
+    from paper_2604_00754_amd import binding as sa
+    print(f"case sample_perm {slices} x {n} cap {cap} workspace={workspace}", flush=True)
+    desc = sa.make_desc(1, slices, slices, n, 64, 8, perm_H=slices)
+    perm = torch.full((1, slices, n), -1, device=U.DEV, dtype=torch.int32)
+    ws = torch.full((sa.sa_workspace_bytes(desc, sa.SA_OP_SAMPLE_PERM),), 0xFF, device=U.DEV, dtype=torch.uint8) if workspace else None
+    assert sa.raw().sa_internal_sample_perm(C.byref(desc), 7, 2, perm.data_ptr(), ws.data_ptr() if workspace else None,
+                                            ws.numel() if workspace else 0, cap, torch.cuda.current_stream().cuda_stream) == sa.SA_OK
+    torch.cuda.synchronize()
+    assert np.array_equal(perm.cpu().numpy(), ps.sample_perm(7, 2, 1, slices, n))
