@@ -43,3 +43,23 @@ def test_multi_gpu_request_is_refused():
     import sys
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode == 2 and "ONE GPU" in r.stderr
+
+
+def test_flop_counts_of_the_forward():
+    """Pairs that are seen, and what the sorted kernel walks for them, counted one by one on a small ring."""
+    import numpy as np
+    b = load_bench()
+    n, w, d = 300, 101, 128
+    perm = np.random.default_rng(0).permutation(n)
+    slot = np.arange(n)
+    dist = abs(slot[:, None] - slot[None, :])
+    near = 2 * np.minimum(dist, n - dist) < w
+    assert b.visible_flop(n, w, d, 1, 4) == 4 * d * 4 * int((near & (perm[None, :] <= perm[:, None])).sum())
+    tiles = 0
+    for p0 in range(0, n, 128):
+        group = sorted(range(p0, min(p0 + 128, n)), key=lambda s: perm[s])
+        band = [t % n for t in range(p0 - 50, min(p0 + 128, n) + 50)]
+        for q in range(0, len(group), 32):
+            keys = sum(any(perm[t] <= perm[s] for s in group[q:q + 32]) for t in band)
+            tiles += -(-keys // 32)
+    assert b.executed_flop_sorted(perm, w, d, 1, 4) == tiles * 4 * 32 * 32 * d * 4
