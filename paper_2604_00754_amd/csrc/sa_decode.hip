@@ -34,10 +34,11 @@ namespace {
 
 constexpr int kChunkRows = 512;     // cached rows per workgroup at most (its set-up and the merge favour long chunks)
 constexpr int kTargetGroups = 512;  // shorter chunks (down to 64 rows) are taken until the launch has this many workgroups
-// Rows in use that exceed the memory-side cache (256 MB) by enough are streamed past it; what fits, or nearly, is found there by
-// the next token.  16 sequences of 8 KV heads, cached / streamed us: 200 MB in use 35.9 / 37.1, 256 MB 48.3 / 50.6, 288 MB
-// 54.4 / 55.0, 320 MB 61.5 / 59.1, 384 MB 75.7 / 67.6, 512 MB 98.9 / 88.0 (16 KV heads of 64: 288 MB 45.8 / 46.1, 320 MB 51.7 / 49.6).
-constexpr double kCacheBytes = 300e6;
+// Rows in use that exceed the memory-side cache (256 MB) are streamed past it.  16 sequences of 8 KV heads, cached / streamed us, the
+// same cache token after token: 134 MB in use 24.1 / 25.4, 200 MB 35.9 / 37.1, 256 MB 48.3 / 50.6, 288 MB 54.4 / 55.0, 320 MB
+// 61.5 / 59.1, 512 MB 98.9 / 88.0; four caches in turn, as the layers of a model come: 64 MB 17.2 / 18.0, 134 MB 30.2 / 27.3, 256 MB
+// 56.5 / 51.7, 384 MB 76.6 / 69.0.  The line lies where the gain of the second is past the loss of the first.
+constexpr double kCacheBytes = 256e6;
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 
