@@ -6,9 +6,10 @@
 // One workgroup (1, 2 or 4 wavefronts) owns a tile of 16 slots of one head in permuted order; the streamed blocks of 16
 // slots of the window band (Eq. 3) are dealt to its wavefronts in turn, and what they accumulate is added through
 // LDS at the end.  Streamed rows are requested one block ahead and there is no barrier in the loop, so the wavefronts of
-// a SIMD run freely against each other: a 16 x 16 block costs 32 cycles of the matrix pipe for every 4 elements of
-// the head size and each product, which is what bounds a long call (fp32 matrix rate 148 TFLOP/s); a short one is bound by
-// the chain index -> rows -> products of one tile.
+// a SIMD run freely against each other.  What bounds a call is the chain of a wavefront: rows -> LDS -> scores -> weights -> sums
+// for every block, index -> rows before the first one.  A 16 x 16 block costs 32 cycles of the matrix pipe for every 4
+// elements of the head size and each product; at two wavefronts a SIMD (B2 H8 n2039 d64 w128) that pipe is busy 33 % (forward)
+// to 44 % (dK, dV) of the time and a wavefront waits 47 to 60 % of its life.
 //
 // Operand layouts (lane = 16 g + c).  The instruction takes A[c][g], B[g][c] and leaves C[4g + i][c] in
 // accumulator i.  Which element of a row is contraction index g of which instruction is free as long as both

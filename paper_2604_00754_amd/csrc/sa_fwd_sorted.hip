@@ -55,8 +55,8 @@ __global__ __launch_bounds__(NT, 3) void fwd_sorted_bf16_kernel(const Pass p, co
   // Work list: the quarters of a slot group, then the next group (neighbours share K/V rows), then the next `per` head sets
   // (four query heads of a KV group each), which one workgroup takes one after another: the list is the same for all of them.
   // Workgroups are dealt to the four shader engines of an XCD in turn, so the quarters of a group start with another one in
-  // every group: in one fixed order one engine gets all the long lists (32 768 slots, w = 512: 391 -> 344 us, waves resident
-  // 65 % -> 95 %)
+  // every group: in one fixed order one engine gets all the long lists (32 768 slots, w = 512: 391 -> 344 us when this was
+  // measured; now 291 us with 2.4 of three waves a SIMD resident on average)
   const unsigned chunk_work = (total_work + NXCD - 1) / NXCD, local = blockIdx.x / NXCD;
   const unsigned work = (blockIdx.x % NXCD) * chunk_work + local;
   if (local >= chunk_work || work >= total_work) return;
