@@ -459,7 +459,7 @@ __global__ __launch_bounds__(NT, 3) void fwd_sorted_bf16_kernel(const Pass p, co
 static long quarters_of(const Pass& p) { return (long)((p.n + GROUP - 1) / GROUP) * (GROUP / 32); }
 
 // Where the shorter walk pays for the list (a workgroup spends about six tiles' time on its prologue, hidden the better the
-// more workgroups a CU goes through).  Items: quarters x sets of four heads; window: its slots.  Time here over time of the
+// more workgroups a CU goes through).  Items: quarters that hold queries x sets of four heads; window: its slots, at most n.  Time here over time of the
 // kernel of sa_fwd_mfma.hip at the line and at the next smaller window measured, 32 query heads on 8 KV heads (4 to 48
 // heads in groups of 4 to 12 are within 0.02 of it), without rotation:
 //   items                256    512    1024   1536   2048   4096   8192   16 384
@@ -477,9 +477,9 @@ constexpr Line kLines[] = {{256, 767}, {512, 639}, {1024, 575}, {1536, 448}, {20
 constexpr Line kLinesRotated[] = {{256, 448}, {2048, 256}, {8192, 192}};
 
 bool fwd_sorted_serves(const Pass& p) {
-  const int w = p.win.L + p.win.R + 1;
-  if (!(p.d == D && p.perm && p.perm_H == 1 && p.causal && p.g % 4 == 0 && !p.gate_mode && w - 1 + GROUP <= CAP)) return false;
-  const long items = quarters_of(p) * (p.Hq >> 2) * p.B;
+  const int reach = p.win.L + p.win.R + 1, w = reach < p.n ? reach : p.n;
+  if (!(p.d == D && p.perm && p.perm_H == 1 && p.causal && p.g % 4 == 0 && !p.gate_mode && reach - 1 + GROUP <= CAP)) return false;
+  const long items = (long)(p.n / GROUP * (GROUP / 32) + (p.n % GROUP + 31) / 32) * (p.Hq >> 2) * p.B;
   int least = 0x7fffffff;
   auto lower = [&](const Line& l) { least = items >= l.items ? l.window : least; };
   if (p.rope_table) for (const Line& l : kLinesRotated) lower(l);

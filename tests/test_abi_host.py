@@ -245,5 +245,8 @@ def test_forward_kernel_that_each_case_of_its_gpu_test_expects():
     for d in (mk(1, 32, 8, 32768, 128, 512, perm_H=32), mk(1, 32, 8, 32768, 64, 512), mk(1, 16, 8, 32768, 128, 512),
               mk(1, 32, 8, 32768, 128, 512, causal_orig=0)):
         assert sa.fwd_kernel(d) == "fwd_mfma_bf16_kernel"
+    # a window that reaches past both ends of a short sequence counts as the sequence, quarters without queries not at all
+    for n in (148, 191):
+        assert sa.fwd_kernel(mk(22, 48, 12, n, 128, 562, window=sa.SA_WIN_SYM_LINEAR, perm_B=22), rotated=True) == "fwd_mfma_bf16_kernel"
     assert sa.fwd_kernel(mk(1, 32, 8, 32768, 128, 512, dtype=sa.SA_F32)) == "fwd_f32_kernel"
     assert sa.fwd_kernel(mk(1, 32, 8, 0, 128, 512)) == ""

@@ -47,7 +47,7 @@ LARGE = [
     (171, 12, 3, 320, 400, CIRC, 171, False),   # a window longer than the sequence; a group of 64
     (256, 12, 3, 257, 257, CIRC, 256, True),    # a group of one slot
     (342, 12, 3, 255, 193, ONE, 342, True),     # narrow windows; a group of 127
-    (683, 12, 3, 200, 193, LIN, 1, False),      # the narrowest; one permutation for the batch
+    (781, 12, 3, 200, 193, LIN, 1, False),      # the narrowest; one permutation for the batch
     # ... and one set, window longer than the sequence
     (9, 12, 3, 460, 900, CIRC, 1, True),
 ]
