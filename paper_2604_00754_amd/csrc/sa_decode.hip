@@ -33,7 +33,7 @@ namespace sa {
 namespace {
 
 constexpr int kChunkRows = 512;     // cached rows per workgroup at most (its set-up and the merge favour long chunks)
-constexpr int kTargetGroups = 512;  // shorter chunks (down to 64 rows) are taken until the launch has this many workgroups
+constexpr int kTargetGroups = 512;  // shorter chunks (down to one loop iteration) are taken until the launch has this many workgroups
 // Rows in use that exceed the memory-side cache (256 MB) are streamed past it.  16 sequences of 8 KV heads, cached / streamed us, the
 // same cache token after token: 134 MB in use 24.1 / 25.4, 200 MB 35.9 / 37.1, 256 MB 48.3 / 50.6, 288 MB 54.4 / 55.0, 320 MB
 // 61.5 / 59.1, 512 MB 98.9 / 88.0; four caches in turn, as the layers of a model come: 64 MB 17.2 / 18.0, 134 MB 30.2 / 27.3, 256 MB
@@ -484,20 +484,20 @@ size_t head_groups(int B, int Hkv, int g) { return (size_t)B * Hkv * (g / heads_
 size_t chunks_of(int rows, int chunk) { return ((size_t)rows + chunk - 1) / chunk; }
 
 // Rows per chunk of a cache with `rows` rows in use, cut into `most` chunks at most: as many chunks as give the launch
-// kTargetGroups workgroups, of 64 to kChunkRows rows each, in steps of 64 (the rows of an unrolled load at d = 128; half of one at
-// d = 64, where steps of 128 measured the same to 4 % and chunks of 128 for 8000 rows of 12 heads 12 % slower than of 64).
+// kTargetGroups workgroups, of one to kChunkRows rows' worth of whole loop iterations (64 rows at d = 128, 128 at d = 64: a chunk of
+// 64 rows takes as long there as one of 128; B4, 64 / 8 heads, 879 of 3606 rows 14.5 against 11.7 us).
 // Cut by the rows in use and not by the capacity, a short sequence in a long cache still fills the chip (1100 rows of
 // 32 768, 8 KV heads: 144 workgroups instead of 24, 12.2 -> 5.9 us).
-int chunk_rows(size_t groups, int rows, size_t most) {
+int chunk_rows(size_t groups, int rows, size_t most, int d) {
   size_t want = ((size_t)kTargetGroups + groups - 1) / groups;
   if (want > most) want = most;
   const size_t even = ((size_t)rows + want - 1) / want;
-  const size_t chunk = (even + 63) / 64 * 64;
+  const size_t step = (size_t)kWaves * (64 / (d / 8)) * DECODE_UNROLL, chunk = (even + step - 1) / step * step;
   return (int)(chunk < kChunkRows ? chunk : kChunkRows);
 }
 
 // What a cache of capacity n is cut into at most, whatever part of it is in use (the workspace is sized for that).
-size_t most_chunks(size_t groups, int n) { return chunks_of(n, chunk_rows(groups, n, (size_t)n)); }
+size_t most_chunks(size_t groups, int n, int d) { return chunks_of(n, chunk_rows(groups, n, (size_t)n, d)); }
 
 template <typename T, int D, int G>
 hipError_t launch_typed(const Decode& d, const Args& a, hipStream_t st) {
@@ -529,7 +529,7 @@ hipError_t launch_heads(const Decode& d, const Args& a, hipStream_t st) {
 }  // namespace
 
 size_t decode_workspace_bytes(int B, int Hq, int Hkv, int n, int d) {
-  const size_t splits = most_chunks(head_groups(B, Hkv, Hq / Hkv), n);
+  const size_t splits = most_chunks(head_groups(B, Hkv, Hq / Hkv), n, d);
   return (size_t)B * Hq * splits * (d + 2) * sizeof(float);
 }
 
@@ -541,7 +541,7 @@ hipError_t launch_decode(const Decode& d, hipStream_t st) {
   a.lens = d.lens;
   a.B = d.B; a.Hq = d.Hq; a.Hkv = d.Hkv; a.g = d.Hq / d.Hkv; a.n = d.n; a.len = d.len;
   const size_t groups = head_groups(d.B, d.Hkv, a.g);
-  a.chunk = chunk_rows(groups, d.len, most_chunks(groups, d.n));
+  a.chunk = chunk_rows(groups, d.len, most_chunks(groups, d.n, d.d), d.d);
   a.splits = (int)chunks_of(d.len, a.chunk);
   a.scale_log2e = d.scale * kLog2e;
   a.stream_rows = (float)(kCacheBytes / (4.0 * d.Hkv * d.d));  // bf16 K and V
