@@ -573,8 +573,10 @@ hipError_t launch_t(const Pass& p, hipStream_t st) {
   } while (0)
   const bool gated = p.gate_mode != 0;
   // Gates per dimension are read in the accumulator layout, 32 rows an instruction: with four workgroups per CU at d = 64 they push each
-  // other's lines out of the cache (calls 3 - 7 % slower than with three), so unused LDS keeps it at three.
-  const unsigned pad = D == 64 && p.gate_per_dim ? 16384 : 0;
+  // other's lines out of the cache (causal calls 3 - 7 % slower than with three, 4 heads of n = 70 000 213 against 184 us), so unused
+  // LDS keeps it at three.  Without the causal test four are mostly the faster ones (B10 H32 n272 46 against 58 us, B4 H16 n8192
+  // w256 286 / 307, w64 304 / 295) and it had four before.
+  const unsigned pad = D == 64 && p.gate_per_dim && mode != CAUSAL_NONE ? 16384 : 0;
   if (p.perm) {
     if (mode == CAUSAL_NONE) SA_LAUNCH_FWD(true, CAUSAL_NONE);
     else if (mode == CAUSAL_I16) SA_LAUNCH_FWD(true, CAUSAL_I16);
