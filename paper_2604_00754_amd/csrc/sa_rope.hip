@@ -62,21 +62,33 @@ struct Row8<float> {
   }
 };
 
-// X, Xout: [heads][n][d].  Thread (m, c) owns elements 8c .. 8c+7 of position m, so that the threads of a row read and write it as
-// one contiguous piece (a thread that owned both halves of its pairs touched half rows, 128-byte lines asked for twice: 16 x 16
-// heads, n = 4096, d = 64 59 against 47 us = 5.8 TB/s; 4 heads, n = 131 072, d = 128 58 against 52 us).
-//   adjacent pairs: they are pairs 4c .. 4c+3;
-//   split halves: the other members of their pairs are the 8 elements of the thread half a row away in the wave.
-template <typename T, bool INTERLEAVED>
+// Whether a thread owns both members of its split pairs: the halves of a row are whole 128-byte lines.
+template <typename T, int d, bool INTERLEAVED>
+constexpr bool rope_both_halves() {
+  return !INTERLEAVED && d / 2 * sizeof(T) >= 128;
+}
+
+// X, Xout: [heads][n][d].  A thread owns 8 pairs of a position or 8 neighbouring elements, so that what neighbouring threads touch
+// with one load is a contiguous piece of whole 128-byte lines:
+//   adjacent pairs: elements 8c .. 8c+7, pairs 4c .. 4c+3, a row as one piece (32 heads, n = 32768, d = 128, with K of 8 heads:
+//     116 us against 145 with 16 elements to a thread);
+//   split halves of a line or more (fp32, or d = 128): elements 8c .. 8c+7 of both halves, pairs 8c .. 8c+7;
+//   split halves of half a line (bf16, d = 64): elements 8c .. 8c+7, a row as one piece, and the other members of their pairs from the
+//     thread half a row away in the wave.  As both halves per thread, lines were asked for twice: 16 x 16 heads, n = 4096, Q and K
+//     115 against 90 us.
+// The exchange does not pay where the halves are lines already: one tensor at d = 128 in bf16 of 32 x 1 x 17379 rows 53.4 against 50.0 us,
+// 912 x 147 15.5 against 14.2, 32 x 131072 415 against 382 (256 x 4096 90.6 against 94.6), in fp32 32 x 8192 45.9 against 43.9.
+template <typename T, int d, bool INTERLEAVED>
 __global__ __launch_bounds__(ROPE_THREADS) void rope_apply_kernel(const T* __restrict__ X, T* __restrict__ Xout,
                                                                    const float2* __restrict__ table, int heads, int n,
-                                                                   int d, int inverse) {
-  const int cpr = d / 8;  // threads per row: 8 or 16, whole rows to a wave
+                                                                   int inverse) {
+  constexpr bool BOTH = rope_both_halves<T, d, INTERLEAVED>();
+  constexpr int cpr = BOTH ? d / 16 : d / 8;  // threads per row: 4, 8 or 16, whole rows to a wave
+  constexpr int NPAIR = INTERLEAVED ? 4 : 8;
   const long t = (long)blockIdx.x * ROPE_THREADS + threadIdx.x;
   const bool live = t < (long)n * cpr;  // (every lane takes part in the exchange)
   const int m = live ? (int)(t / cpr) : n - 1, c = (int)(t % cpr);
-  constexpr int NPAIR = INTERLEAVED ? 4 : 8;
-  const bool second = !INTERLEAVED && c >= cpr / 2;  // holds the second members of its pairs
+  const bool second = !INTERLEAVED && !BOTH && c >= cpr / 2;  // holds the second members of its pairs
   float cs[NPAIR], sn[NPAIR];
   {
     const float4* tp = reinterpret_cast<const float4*>(table + (size_t)m * (d / 2) + NPAIR * (second ? c - cpr / 2 : c));
@@ -93,40 +105,60 @@ __global__ __launch_bounds__(ROPE_THREADS) void rope_apply_kernel(const T* __res
   }
   const int h0 = blockIdx.y * ROPE_HEADS_PER_BLOCK;
   const int h1 = min(h0 + ROPE_HEADS_PER_BLOCK, heads);
-#pragma unroll 4
-  for (int h = h0; h < h1; ++h) {
-    const size_t at = ((size_t)h * n + m) * d + 8 * c;
-    float x[8], o[8];
-    Row8<T>::load(X + at, x);
-    if (INTERLEAVED) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        o[2 * j] = x[2 * j] * cs[j] - x[2 * j + 1] * sn[j];
-        o[2 * j + 1] = x[2 * j] * sn[j] + x[2 * j + 1] * cs[j];
-      }
-    } else {
+  if constexpr (BOTH) {
+    if (!live) return;
+    for (int h = h0; h < h1; ++h) {
+      const size_t at = ((size_t)h * n + m) * d + 8 * c;
+      float u[8], v[8], ou[8], ov[8];
+      Row8<T>::load(X + at, u);
+      Row8<T>::load(X + at + d / 2, v);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const float other = __shfl_xor(x[j], cpr / 2);
-        o[j] = x[j] * cs[j] - other * sn[j];
+        ou[j] = u[j] * cs[j] - v[j] * sn[j];
+        ov[j] = u[j] * sn[j] + v[j] * cs[j];
       }
+      Row8<T>::store(Xout + at, ou);
+      Row8<T>::store(Xout + at + d / 2, ov);
     }
-    if (live) Row8<T>::store(Xout + at, o);
+  } else {
+#pragma unroll 4
+    for (int h = h0; h < h1; ++h) {
+      const size_t at = ((size_t)h * n + m) * d + 8 * c;
+      float x[8], o[8];
+      Row8<T>::load(X + at, x);
+      if (INTERLEAVED) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          o[2 * j] = x[2 * j] * cs[j] - x[2 * j + 1] * sn[j];
+          o[2 * j + 1] = x[2 * j] * sn[j] + x[2 * j + 1] * cs[j];
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float other = __shfl_xor(x[j], cpr / 2);
+          o[j] = x[j] * cs[j] - other * sn[j];
+        }
+      }
+      if (live) Row8<T>::store(Xout + at, o);
+    }
   }
 }
 
-template <typename T>
-hipError_t launch_apply(const void* X, void* Xout, const float* table, int heads, int n, int d, int interleaved,
-                        int inverse, hipStream_t st) {
-  const long threads = (long)n * (d / 8);
+template <typename T, int d, bool INTERLEAVED>
+hipError_t launch_apply(const void* X, void* Xout, const float* table, int heads, int n, int inverse, hipStream_t st) {
+  const long threads = (long)n * (rope_both_halves<T, d, INTERLEAVED>() ? d / 16 : d / 8);
   dim3 grid((unsigned)((threads + ROPE_THREADS - 1) / ROPE_THREADS),
             (unsigned)((heads + ROPE_HEADS_PER_BLOCK - 1) / ROPE_HEADS_PER_BLOCK));
-  const float2* tb = reinterpret_cast<const float2*>(table);
-  if (interleaved)
-    rope_apply_kernel<T, true><<<grid, ROPE_THREADS, 0, st>>>((const T*)X, (T*)Xout, tb, heads, n, d, inverse);
-  else
-    rope_apply_kernel<T, false><<<grid, ROPE_THREADS, 0, st>>>((const T*)X, (T*)Xout, tb, heads, n, d, inverse);
+  rope_apply_kernel<T, d, INTERLEAVED><<<grid, ROPE_THREADS, 0, st>>>(
+      (const T*)X, (T*)Xout, reinterpret_cast<const float2*>(table), heads, n, inverse);
   return hipGetLastError();
+}
+
+template <typename T, int d>
+hipError_t launch_apply(const void* X, void* Xout, const float* table, int heads, int n, int interleaved,
+                        int inverse, hipStream_t st) {
+  return interleaved ? launch_apply<T, d, true>(X, Xout, table, heads, n, inverse, st)
+                     : launch_apply<T, d, false>(X, Xout, table, heads, n, inverse, st);
 }
 
 }  // namespace
@@ -141,8 +173,12 @@ hipError_t launch_rope_table(float* table, int n, int d, double base, int pos0, 
 hipError_t launch_rope_apply(const void* X, void* Xout, const float* table, int heads, int n, int d, int bf16,
                              int interleaved, int inverse, hipStream_t st) {
   if (heads > 65535 * ROPE_HEADS_PER_BLOCK) return hipErrorNotSupported;
-  return bf16 ? launch_apply<uint16_t>(X, Xout, table, heads, n, d, interleaved, inverse, st)
-              : launch_apply<float>(X, Xout, table, heads, n, d, interleaved, inverse, st);
+  if (d == 64)
+    return bf16 ? launch_apply<uint16_t, 64>(X, Xout, table, heads, n, interleaved, inverse, st)
+                : launch_apply<float, 64>(X, Xout, table, heads, n, interleaved, inverse, st);
+  if (d != 128) return hipErrorNotSupported;
+  return bf16 ? launch_apply<uint16_t, 128>(X, Xout, table, heads, n, interleaved, inverse, st)
+              : launch_apply<float, 128>(X, Xout, table, heads, n, interleaved, inverse, st);
 }
 
 }  // namespace sa
