@@ -340,9 +340,11 @@ __global__ __launch_bounds__(256) void gate_bwd_setup_kernel(const GateBwd p, co
 // zero give the same bits in either order, so dW repeats itself.  (It is the faster cut as well for 12 and 16 heads of 64:
 // every further piece adds its 64 KB per tile in memory; the whole backward of the gates with 4 and 8 pieces, as many as fill the chip,
 // and with two: n = 1100 51.6 / 44.3 us, 2048 65.4 / 48.3, 4096 78.5 / 64.6; with two heads, one tile, n = 8192 28.6 / 56.4.)
-// Longer calls add in no fixed order: WCHUNK, halved down to WCHUNK_LEAST until the launch has WTARGET workgroups, two per CU.
+// Longer calls add in no fixed order: WCHUNK, halved down to WCHUNK_LEAST until the launch has WTARGET workgroups, one per CU.  Two per CU
+// cost more in additions than they gave (whole backward, both branches, two per CU / one): 13 x 476 tokens of 8 heads of 64 79.0 / 60.0 us,
+// 13 x 407 of 4 of 128 77.7 / 58.2, 6 x 2735 of 12 of 64 168 / 152; 66 drawn calls 0.75 ... 1.02.
 constexpr int WCHUNK = 4096, WCHUNK_LEAST = 256;
-constexpr long WTARGET = 512;
+constexpr long WTARGET = 256;
 constexpr int WSTEP = 32;
 constexpr int WSTAGES = 4;
 constexpr int WTILE_BYTES = WSTEP * 128 * 2;  // one operand, one step
@@ -545,7 +547,7 @@ static hipError_t gate_proj_bwd_branches(int branches, int B, int Hq, int n, int
   int chunk = WCHUNK;
   auto workgroups = [&]() -> long { return (long)num_ft * num_ft * ((n + chunk - 1) / chunk) * B * branches; };
   if ((long)((n + WCHUNK - 1) / WCHUNK) * B <= 2) {
-    if (B == 1 && n > WCHUNK_LEAST && workgroups() < WTARGET) chunk = ((n + 1) / 2 + WSTEP - 1) / WSTEP * WSTEP;
+    if (B == 1 && n > WCHUNK_LEAST && workgroups() < 2 * WTARGET) chunk = ((n + 1) / 2 + WSTEP - 1) / WSTEP * WSTEP;
   } else {
     while (chunk > WCHUNK_LEAST && workgroups() < WTARGET) chunk /= 2;
   }
