@@ -484,13 +484,20 @@ __global__ __launch_bounds__(64 * FW, D == 64 ? 3 : 2) void bwd_dq_f32_kernel(co
 // A tile of 16 key slots; dV_j = sum_i P_ij dO_i, dK_j = scale * sum_i dS_ij Q_i over the queries whose window
 // holds the key and over the query heads hg_begin .. hg_end - 1 of the group (they share a slot order, or there is
 // one of them), whose (head, query block) pairs are dealt to the wavefronts in turn.
-template <int D, bool PERM, int FW>
+// OWN: every head has an order of its own.  The tile holds 16 keys in their original order, its band is all slots, and the slot
+// of a key in a head's order is looked for in that order: for a few slots only, see launch_bwd_f32.
+template <int D, bool PERM, int FW, bool OWN = false>
 __global__ __launch_bounds__(64 * FW, 2) void bwd_dkv_f32_kernel(const Pass p, const unsigned num_tiles, const unsigned total_work) {
   __shared__ __attribute__((aligned(16))) float area[FW * 2 * Stage<D>::FLOATS];
   Tile t;
   if (!pick_tile(t, p, num_tiles, total_work, p.Hkv)) return;
   const int n = p.n;
-  set_band(t, p, p.win.R, p.win.L);  // queries at slots s with -L <= t - s <= R, i.e. s in [t - R, t + L]
+  if constexpr (OWN) {
+    t.lo = 0;
+    t.nblocks = (n + FT - 1) / FT;
+  } else {
+    set_band(t, p, p.win.R, p.win.L);  // queries at slots s with -L <= t - s <= R, i.e. s in [t - R, t + L]
+  }
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int hg0 = p.hq_only >= 0 ? p.hq_only : 0, heads = p.hq_only >= 0 ? 1 : p.g;
@@ -498,7 +505,7 @@ __global__ __launch_bounds__(64 * FW, 2) void bwd_dkv_f32_kernel(const Pass p, c
   const size_t kv_row0 = ((size_t)t.b * p.Hkv + t.h) * n;
 
   const int k = t.s0 + c;  // this lane's key slot
-  const int orig_k = PERM ? perm[min(k, n - 1)] : min(k, n - 1);
+  const int orig_k = PERM && !OWN ? perm[min(k, n - 1)] : min(k, n - 1);
   const int first_q = p.causal ? orig_k : -1;  // no query before it sees this key
   // query slot s sees the key iff 0 <= s - k + Rl <= LRl
   const int Rl = p.win.circular ? p.win.R : min(p.win.R, k);
@@ -513,17 +520,32 @@ __global__ __launch_bounds__(64 * FW, 2) void bwd_dkv_f32_kernel(const Pass p, c
   const float cs = p.scale * kLog2e;
   const int units = heads * t.nblocks;
   auto unit_row0 = [&](int u) -> size_t { return ((size_t)t.b * p.Hq + t.h * p.g + hg0 + min(u, units - 1) / t.nblocks) * n; };
-  auto unit_row = [&](int u) -> int { return streamed_row<PERM>(t, perm, min(u, units - 1) % t.nblocks, c, n); };
+  auto unit_order = [&](int u) { return perm_of<PERM>(p, t.b, t.h * p.g + min(u, units - 1) / t.nblocks); };
+  auto unit_row = [&](int u) -> int {
+    if constexpr (OWN) return unit_order(u)[min(FT * (min(u, units - 1) % t.nblocks) + c, n - 1)];
+    else return streamed_row<PERM>(t, perm, min(u, units - 1) % t.nblocks, c, n);
+  };
   const float* __restrict__ Q = reinterpret_cast<const float*>(p.Q);
   const float* __restrict__ dO = reinterpret_cast<const float*>(p.dO);
   int pos = unit_row(wave), pos1 = unit_row(wave + FW);
   f32x4 qn[D / 16], gn[D / 16];
   auto probabilities = [&](int u, const f32x4 st, const int* qpos, const float* lse2) -> f32x4 {  // of queries 4g + i for key c
     const int s0 = t.lo + FT * (u % t.nblocks) + 4 * g - k + Rl;
+    int own_at = -(1 << 20);  // (a key without a slot is seen by no query)
+    if constexpr (OWN) {
+      const int32_t* __restrict__ order = unit_order(u);
+      for (int s = 0; s < n; ++s) own_at = order[s] == orig_k ? s : own_at;
+    }
     f32x4 pr;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const bool seen = ((unsigned)(s0 + i) <= LRl) & (first_q <= qpos[i]);
+      bool seen = ((unsigned)(s0 + i) <= LRl) & (first_q <= qpos[i]);
+      if constexpr (OWN) {
+        const int s = FT * (u % t.nblocks) + 4 * g + i;
+        int r = s - own_at + p.win.R;
+        if (p.win.circular) r = r < 0 ? r + n : r >= n ? r - n : r;
+        seen = (s < n) & ((unsigned)r <= (unsigned)(p.win.L + p.win.R)) & (first_q <= qpos[i]);
+      }
       const float pe = __builtin_amdgcn_exp2f(fmaf(st[i], cs, -lse2[i]));
       pr[i] = seen ? pe : 0.f;
     }
@@ -683,6 +705,18 @@ static hipError_t launch_dkv_f32(const Pass& p, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Grouped heads with permutations of their own: up to 64 slots one launch walks all slots of all heads of a group, beyond that a pass
+// per head walks bands.  The passes are launches of 5 us one behind the other; whole sequences instead of bands cost more from 65
+// slots on, and once the tiles are more than the chip takes in about a round.  Whole backward, w = 64, passes / one launch, us:
+//   slots                              16          32          64          65          128
+//   10 x 32 / 4 heads of 64            53.0/17.4   56.3/25.6   72.4/54.1   74.3/63.7   95.2/151
+//   1 x 8 / 2 heads of 64              29.2/14.3   29.3/16.0   36.6/28.8   36.1/33.0   36.9/66.7
+//   2 x 32 / 8 heads of 128            40.5/16.9   41.7/22.2   54.7/39.5   58.0/48.0   59.7/87.7
+//   64 x 32 / 8 heads of 64, tiles     42.7/19.9   72.8/49.6   161/140 (2048)
+//   500 x 8 / 4 heads of 64, tiles     56.2/44.1 (2000)        258/292 (8000); 33 slots (6000) 128/147
+constexpr int kOwnOrderSlots = 64;
+constexpr long kOwnOrderTiles = 2048;
+
 hipError_t launch_bwd_f32(const Pass& p, hipStream_t st) {
   if (!f32_shape_ok(p)) return hipErrorInvalidValue;
   if (p.O_rows ? !p.Dsum_out : !p.Dsum) return hipErrorInvalidValue;
@@ -692,7 +726,16 @@ hipError_t launch_bwd_f32(const Pass& p, hipStream_t st) {
   Pass kv = p;
   if (p.O_rows) kv.Dsum = p.Dsum_out;  // the dQ kernel has left the row sums there
   if (!(p.perm && p.perm_H != 1 && p.g > 1)) return launch_dkv_f32(kv, st);
-  // every query head of a group has its own slot order: one pass per head, summed in place
+  // every query head of a group has its own slot order
+  const int tiles = (p.n + FT - 1) / FT;
+  const long total = (long)tiles * p.Hkv * p.B;
+  if (p.n <= kOwnOrderSlots && total <= kOwnOrderTiles) {
+    const dim3 grid((unsigned)xcd_grid_blocks(total)), block(64 * 4);
+    if (p.d == 64) hipLaunchKernelGGL((bwd_dkv_f32_kernel<64, true, 4, true>), grid, block, 0, st, kv, (unsigned)tiles, (unsigned)total);
+    else hipLaunchKernelGGL((bwd_dkv_f32_kernel<128, true, 4, true>), grid, block, 0, st, kv, (unsigned)tiles, (unsigned)total);
+    return hipGetLastError();
+  }
+  // one pass per head, summed in place
   for (int hg = 0; hg < p.g; ++hg) {
     kv.hq_only = hg;
     kv.accumulate = hg == 0 ? p.accumulate : 1;

@@ -32,6 +32,16 @@ CASES = [
     (1, 16, 4, 1025, 128, 48, CIRC, 1, 1, False),   # 1040: one (dK/dV: 260 tiles, four)
     (2, 16, 16, 1023, 64, 33, LIN, 1, 16, False),   # 2048 tiles: one
     (2, 16, 8, 1025, 128, 15, CIRC, 1, 16, False),  # one; dK/dV one pass per head of the group
+    # permutations per head under grouped heads: one dK/dV launch up to 64 slots and 2048 tiles
+    (2, 4, 1, 1, 128, 1, CIRC, 1, 4, False),
+    (2, 8, 2, 16, 64, 5, CIRC, 1, 8, False),
+    (1, 6, 2, 17, 64, 9, ONE, 0, 6, False),
+    (1, 4, 2, 47, 128, 94, LIN, 1, 4, False),
+    (2, 8, 2, 64, 64, 64, CIRC, 1, 8, False),
+    (1, 8, 2, 64, 128, 21, LIN, 0, 8, False),
+    (1, 8, 2, 65, 64, 21, CIRC, 0, 8, False),       # one pass per head
+    (64, 16, 8, 64, 64, 7, CIRC, 0, 16, False),     # 2048 tiles
+    (65, 16, 8, 64, 64, 7, ONE, 1, 16, False),      # 2080: one pass per head
 ]
 
 
@@ -52,6 +62,7 @@ UNSEEN = [
     (1, 16, 16, 600, 128, 33, CIRC, 1, 16),         # two
     (2, 16, 16, 1025, 64, 33, LIN, 1, 16),          # one
     (2, 16, 8, 1025, 128, 15, CIRC, 1, 16),
+    (1, 6, 2, 61, 64, 9, CIRC, 1, 6),               # dK/dV of a group in one launch
 ]
 
 
