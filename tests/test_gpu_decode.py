@@ -47,7 +47,8 @@ def test_bf16_parity_group_sizes(B, Hq, Hkv, n, d, length):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,n,d,length", [(1, 2, 2, 1024, 64, 1000), (2, 4, 1, 600, 128, 600),
-                                                  (1, 8, 1, 333, 64, 333)])
+                                                  (1, 8, 1, 333, 64, 333),
+                                                  (3, 16, 8, 2000, 128, 1999)])  # halved to 64 rows
 def test_f32_parity(B, Hq, Hkv, n, d, length):
     run_decode(B, Hq, Hkv, n, d, length, dtype="f32")
 
@@ -110,6 +111,7 @@ def test_decode_continues_the_prompt_pass():
     (3, 8, 1, 900, 64, [64, 65, 900]),
     (5, 4, 4, 2100, 128, [2100, 2099, 33, 1024, 1025]),
     (2, 6, 2, 800, 128, [5, 300]),          # max_len below the capacity
+    (3, 16, 8, 2000, 128, [1999, 65, 1300]),  # chunks of 512 rows halved to 64, where an even cut has 128
 ])
 def test_sequences_of_different_lengths(B, Hq, Hkv, n, d, lens):
     """sa_decode_fwd_varlen: every sequence of the batch against the oracle run on that sequence alone with its own
