@@ -6,7 +6,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsa.so")
-SOURCES = ["sa_api.hip", "sa_misc.hip", "sa_f32_mfma.hip", "sa_fwd_mfma.hip", "sa_fwd_sorted.hip", "sa_bwd_mfma.hip", "sa_gate_proj.hip", "sa_rope.hip", "sa_decode.hip"]
+SOURCES = ["sa_api.hip", "sa_misc.hip", "sa_f32_mfma.hip", "sa_fwd_mfma.hip", "sa_fwd_sorted.hip", "sa_bwd_mfma.hip", "sa_bwd_strip.hip", "sa_gate_proj.hip", "sa_rope.hip", "sa_decode.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # no packed fp32 vector instructions: some of their forms have given wrong results
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -817,6 +817,7 @@ hipError_t launch_bwd_mfma_bf16(const Pass& p, hipStream_t st) {
   if ((long)p.n * p.d * 2 >= (1L << 31)) return hipErrorNotSupported;  // 32-bit row offsets inside a head
   if (p.rope_dk && !p.rope_table) return hipErrorInvalidValue;
   if (p.rope_table && !p.Q_rot) return hipErrorInvalidValue;
+  if (bwd_strip_serves(p)) return launch_bwd_strip_bf16(p, st);
   hipError_t e = p.d == 64 ? launch_dq_t<64>(p, st) : launch_dq_t<128>(p, st);
   if (e != hipSuccess) return e;
   Pass kv = p;

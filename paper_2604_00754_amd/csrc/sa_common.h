@@ -68,6 +68,8 @@ hipError_t launch_fwd_mfma_bf16(const Pass& p, hipStream_t st);
 bool fwd_sorted_serves(const Pass& p);  // sa_fwd_sorted.hip: can it, and is it the faster one
 hipError_t launch_fwd_sorted_bf16(const Pass& p, hipStream_t st);
 hipError_t launch_bwd_mfma_bf16(const Pass& p, hipStream_t st);
+bool bwd_strip_serves(const Pass& p);  // sa_bwd_strip.hip: can it, and is it the faster one
+hipError_t launch_bwd_strip_bf16(const Pass& p, hipStream_t st);
 
 hipError_t launch_permuted_copy_bf16(const Pass& p, hipStream_t st);
 // ws = nullptr: one launch, every bucket of keys gathered by a pass over all of them; otherwise
