@@ -17,7 +17,7 @@
 // Bound: the issue of vector instructions (per SIMD and interval about 3000 cycles of 4500 at NB = 9: 150 instructions and 16
 // exponentials for a block of 32 x 32, 2.25 blocks a SIMD, 1000 instructions for the three other roles), then the LDS latencies of the
 // slowest role.  Measured against the two kernels (us): 64 heads, 8192 slots, d = 64, w = 256, one call alone 242 -> 159, the
-// one-sided branch 223 -> 150; 256 heads, 4096 slots with rotations 590 -> 430.  NB + 3 waves of 168 registers at NB = 9 fill a
+// one-sided branch 223 -> 150; 256 heads, 4096 slots with rotations 590 -> 345 (430 while dK's table rows went through LDS to the accumulators).  NB + 3 waves of 168 registers at NB = 9 fill a
 // CU; its LDS (155 KB) holds query tiles three intervals ahead and one K tile a wave.  The strip is as long as one round of 256
 // workgroups allows (2048 slots there): every strip walks its windows' reach on top of its own slots.
 #include "sa_common.h"
@@ -42,7 +42,7 @@ enum { CAUSAL_NONE = 0, CAUSAL_I16 = 2 };
 enum { ROWS_PLAIN = 0, ROWS_ADD = 1, ROWS_TURN = 2 };
 typedef short s16x2 __attribute__((ext_vector_type(2)));
 
-template <int NB>
+template <int NB, int ROWS>
 struct Cfg {
   static constexpr int W = NB + 3;        // waves
   static constexpr int NT = 64 * W;
@@ -55,7 +55,8 @@ struct Cfg {
   static constexpr int VALS = RB * 16 + RB * 2;                // operand rows of -LSE / scale and -D | 16-bit positions in accumulator order
   static constexpr int OFF_VAL = OFF_DQ + 2 * ROWS_F32;
   static constexpr int OFF_POS = OFF_VAL + NQ * VALS;          // positions of the strip's slots and of those its windows reach
-  static constexpr int LDS_BYTES = OFF_POS + kMostPos * 2;
+  static constexpr int OFF_TURN = OFF_POS + kMostPos * 2;      // fp32 rows of dK that are turned on their way out
+  static constexpr int LDS_BYTES = OFF_TURN + (ROWS == ROWS_TURN ? ROWS_F32 : 0);
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a CU");
 };
 
@@ -119,6 +120,49 @@ __device__ __forceinline__ float from_lane(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
 }
 
+// What lanes hold of 32 fp32 rows in LDS, turned back by the angles of their rows (the transpose of RoPE), times mul, as 16-byte
+// chunks of bf16 rows.  Lane (r8, c8) turns pairs 4 c8 .. 4 c8 + 3 of rows 8 v + r8; t = their (cos, sin), 32 bytes a row.  Split halves:
+// a lane has four columns of either half, and neighbours trade so that the even one leaves with eight of the lower half and the
+// odd one with eight of the upper.  Returns the lane's chunk.
+__device__ __forceinline__ int turn_rows(const char* area, const u32x4* t, float mul, int interleaved, int lane, u32x4* w) {
+  const int r8 = lane >> 3, c8 = lane & 7;
+  f32x4 a[4], b[4];
+  auto fetch = [&](int v) {
+    const int row = 8 * v + r8;
+    a[v] = *reinterpret_cast<const f32x4*>(area + row * (D * 4) + (((interleaved ? 2 * c8 : c8) ^ (row & 15)) * 16));
+    b[v] = *reinterpret_cast<const f32x4*>(area + row * (D * 4) + (((interleaved ? 2 * c8 + 1 : 8 + c8) ^ (row & 15)) * 16));
+  };
+  fetch(0);
+  fetch(1);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    if (v == 1) { fetch(2); fetch(3); }
+    __builtin_amdgcn_sched_barrier(0);
+    const f32x4 t0 = __builtin_bit_cast(f32x4, t[2 * v]), t1 = __builtin_bit_cast(f32x4, t[2 * v + 1]);
+    f32x4 x, y;
+    if (interleaved) {
+      x = f32x4{a[v][0] * t0[0] + a[v][1] * t0[1], a[v][1] * t0[0] - a[v][0] * t0[1], a[v][2] * t0[2] + a[v][3] * t0[3], a[v][3] * t0[2] - a[v][2] * t0[3]};
+      y = f32x4{b[v][0] * t1[0] + b[v][1] * t1[1], b[v][1] * t1[0] - b[v][0] * t1[1], b[v][2] * t1[2] + b[v][3] * t1[3], b[v][3] * t1[2] - b[v][2] * t1[3]};
+    } else {
+      x = f32x4{a[v][0] * t0[0] + b[v][0] * t0[1], a[v][1] * t0[2] + b[v][1] * t0[3], a[v][2] * t1[0] + b[v][2] * t1[1], a[v][3] * t1[2] + b[v][3] * t1[3]};
+      y = f32x4{b[v][0] * t0[0] - a[v][0] * t0[1], b[v][1] * t0[2] - a[v][1] * t0[3], b[v][2] * t1[0] - a[v][2] * t1[1], b[v][3] * t1[2] - a[v][3] * t1[3]};
+    }
+    const u32x2 lo = {pack_bf16(x[0] * mul, x[1] * mul), pack_bf16(x[2] * mul, x[3] * mul)};
+    const u32x2 hi = {pack_bf16(y[0] * mul, y[1] * mul), pack_bf16(y[2] * mul, y[3] * mul)};
+    if (interleaved) {
+      w[v] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+    } else {
+      const bool odd = c8 & 1;
+      u32x2 got;
+#pragma unroll
+      for (int e = 0; e < 2; ++e)  // quad_perm [1,0,3,2]
+        got[e] = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? lo[e] : hi[e]), 0xB1, 0xf, 0xf, true);
+      w[v] = odd ? u32x4{got[0], got[1], hi[0], hi[1]} : u32x4{lo[0], lo[1], got[0], got[1]};
+    }
+  }
+  return interleaved ? c8 : (c8 & 1) * 4 + (c8 >> 1);
+}
+
 // The lane's number, formed anew at each use: a copy that the optimiser cannot trace, so that what a role derives from it is
 // formed in that role instead of being kept in registers through all the others.
 __device__ __forceinline__ int fresh(int lane) {
@@ -127,8 +171,8 @@ __device__ __forceinline__ int fresh(int lane) {
 }
 
 template <int NB, int CAUSAL, int ROWS>
-__global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass p, const Strips strips, const long total_work) {
-  using C = Cfg<NB>;
+__global__ __launch_bounds__((Cfg<NB, ROWS>::NT)) void bwd_strip_bf16_kernel(const Pass p, const Strips strips, const long total_work) {
+  using C = Cfg<NB, ROWS>;
   __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
   const long work = xcd_work_index(total_work);
   if (work < 0) return;
@@ -179,8 +223,10 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
   };
   const float cs = p.scale * kLog2e;
 
-  constexpr int kAsks = 3;  // the active wave, by the intervals it has left, that requests a query block (3: key block 0 for query block 0)
-  int i = -(NB + 2);  // interval
+  // the active wave, by the intervals it has left, that requests a query block (3 at least: key block 0 for query block 0; six
+  // instead of three: 542 -> 533 us for the gated training step)
+  constexpr int kAsks = NB - 3 > 3 ? NB - 3 : 3;
+  int i = -(NB + 2);  // interval; the first wave requests key block 0
   // the end of an interval: what this wave wrote to LDS is there before the barrier; loads and stores stay under way
   auto next_interval = [&]() -> bool {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -240,6 +286,7 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
 
   f32x16 dk[2], dv[2];
   for (int j = wave;; j += C::W) {
+    const uint32_t ktile = C::OFF_K + (uint32_t)wave * TILE;
     // ---- between two key blocks, first interval (i = j - NB - 2)
     __builtin_amdgcn_s_setprio(2);
     const int iq = i + 3;                       // the query block of which this wave brings in what goes with its rows
@@ -257,36 +304,42 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
         if (ROWS == ROWS_ADD) {
           aux[v] = row_at_offset(dKh, row + c);
           aux[4 + v] = row_at_offset(dVh, row + c);
-        } else {  // 32 rows of 256 bytes: pairs 0..15, then 16..31
-          aux[v] = row_at_offset(rope, 2 * row + c);
-          aux[4 + v] = row_at_offset(rope, 2 * row + c + 128);
+        } else {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) aux[2 * v + h] = row_at_offset(rope, 2 * row + (lane & 7) * 32 + h * 16);
         }
       }
     }
+    int pos_q = 0;  // position of this lane's query slot (both halves of the wave alike)
+    u32x4 orow[4] = {};
+    float lse = 0.f, dsum = 0.f;
+    auto request_scalars = [&]() {
+      const int lane = fresh(lane0), r8 = lane >> 3;
+      pos_q = qpos_lds[want_q ? RB * iq + (lane & 31) : 0];
+      if (want_q) {
+        lse = p.lse_in[row0 + pos_q];
+        if (!Oh) dsum = p.Dsum[row0 + pos_q];
+        if (Oh) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) orow[v] = row_at_offset(Oh, query_row(iq, 8 * v + r8) + (uint32_t)lane_chunk(lane, v) * 16);
+        }
+      }
+    };
+    // (in the interval that is the shorter one: gated step 549 us with both branches' in the second, 533 here; a plain branch whose row
+    // sums are formed here, w = 128, 64 heads of 8192 slots, 135 us here, 123 in the second)
+    const bool scalars_later = ROWS == ROWS_PLAIN && Oh;
+    if (!scalars_later) request_scalars();
     if (next_interval()) return;
 
     // ---- second interval: dK and dV of the finished block leave
     const bool out_q = i - 1 >= 0 && i - 1 < nqb && query_block_owned(i - 1);  // in the next interval
-    u32x4 auxq[8] = {};
-    if (out_q && ROWS != ROWS_PLAIN) {
-      const int lane = fresh(lane0), r8 = lane >> 3, c8 = lane & 7;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const uint32_t row = query_row(i - 1, 8 * v + r8);
-        if (ROWS == ROWS_ADD) auxq[v] = row_at_offset(dQh, row + c8 * 16);
-        else {
-#pragma unroll
-          for (int h = 0; h < 2; ++h) auxq[2 * v + h] = row_at_offset(rope, 2 * row + c8 * 32 + h * 16);
-        }
-      }
-    }
     // dK and dV take the way through LDS (this wave's K tile, which dQ no longer needs, and its V tile): out of the accumulators
     // a lane has 8-byte pieces of its own row; what comes in and goes out of memory are whole rows.
-    const uint32_t ktile = C::OFF_K + (uint32_t)wave * TILE, vtile = C::OFF_V + (uint32_t)(i & 1) * TILE;
+    const uint32_t vtile = C::OFF_V + (uint32_t)(i & 1) * TILE;
     if (out_kv) {
       const int lane = fresh(lane0), g2 = lane >> 5, c32 = lane & 31, r8 = lane >> 3;
       const uint32_t own = (uint32_t)(c32 * D * 2 + swz<D>(c32) * 16);  // 16-byte chunk c of the lane's row: ^ 16 c
-      if (ROWS == ROWS_ADD || (ROWS == ROWS_TURN && p.rope_dk)) {
+      if (ROWS == ROWS_ADD) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           *reinterpret_cast<u32x4*>(smem + ktile + v * 1024 + lane * 16) = aux[v];
@@ -294,35 +347,7 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
         }
         wave_lds_sync();
       }
-      if (ROWS == ROWS_TURN && p.rope_dk) {
-#pragma unroll
-        for (int mq = 0; mq < 4; ++mq) {
-          if (p.rope_interleaved) {
-#pragma unroll
-            for (int db = 0; db < 2; ++db) {  // pairs 16 db + 4 mq + 2 g2 + {0, 1}
-              const f32x4 t = *reinterpret_cast<const f32x4*>(smem + (db ? vtile : ktile) + (own ^ (16 * (2 * mq + g2))));
-#pragma unroll
-              for (int x = 0; x < 4; x += 2) {
-                const float a = dk[db][4 * mq + x], bb = dk[db][4 * mq + x + 1];
-                dk[db][4 * mq + x] = a * t[x] + bb * t[x + 1];
-                dk[db][4 * mq + x + 1] = bb * t[x] - a * t[x + 1];
-              }
-            }
-          } else {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {  // pairs 8 mq + 4 g2 + 2 h + {0, 1}
-              const f32x4 t = *reinterpret_cast<const f32x4*>(smem + (mq >> 1 ? vtile : ktile) + (own ^ (16 * (4 * (mq & 1) + 2 * g2 + h))));
-#pragma unroll
-              for (int x = 0; x < 2; ++x) {
-                const float a = dk[0][4 * mq + 2 * h + x], bb = dk[1][4 * mq + 2 * h + x], cn = t[2 * x], sn = t[2 * x + 1];
-                dk[0][4 * mq + 2 * h + x] = a * cn + bb * sn;
-                dk[1][4 * mq + 2 * h + x] = bb * cn - a * sn;
-              }
-            }
-          }
-        }
-        wave_lds_sync();
-      }
+      const bool turn = ROWS == ROWS_TURN && p.rope_dk;
       auto put = [&](const f32x16* acc, float mul, uint32_t tile) {
         u32x2 old[8];
         if (ROWS == ROWS_ADD) {
@@ -341,31 +366,65 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
           *reinterpret_cast<u32x2*>(smem + tile + (own ^ (16 * c)) + 8 * g2) = u32x2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
         }
       };
-      put(dk, p.scale, ktile);
+      if (turn) {
+        put_rows(smem + C::OFF_TURN, dk[0], 0, lane);
+        put_rows(smem + C::OFF_TURN, dk[1], 8, lane);
+      } else {
+        put(dk, p.scale, ktile);
+      }
       put(dv, 1.f, vtile);
       wave_lds_sync();
       uint32_t at[4];
-      u32x4 wk[4], wv[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        at[v] = key_row(jp, 8 * v + r8) + (uint32_t)lane_chunk(lane, v) * 16;
-        wk[v] = *reinterpret_cast<const u32x4*>(smem + ktile + v * 1024 + lane * 16);
-        wv[v] = *reinterpret_cast<const u32x4*>(smem + vtile + v * 1024 + lane * 16);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+      for (int v = 0; v < 4; ++v) at[v] = key_row(jp, 8 * v + r8);
+      // one tensor at a time where the rotation's registers leave no room for both
+      auto tiles_out = [&](bool with_k, bool with_v) {
+        u32x4 wk[4], wv[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int s = T0 + RB * jp + 8 * v + r8;
-        if (s >= k0 && s < k1) {
-          store_at_offset(dKh, at[v], wk[v]);
-          store_at_offset(dVh, at[v], wv[v]);
+        for (int v = 0; v < 4; ++v) {
+          if (with_k) wk[v] = *reinterpret_cast<const u32x4*>(smem + ktile + v * 1024 + lane * 16);
+          if (with_v) wv[v] = *reinterpret_cast<const u32x4*>(smem + vtile + v * 1024 + lane * 16);
         }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int s = T0 + RB * jp + 8 * v + r8;
+          if (s >= k0 && s < k1) {
+            const uint32_t to = at[v] + (uint32_t)lane_chunk(lane, v) * 16;
+            if (with_k) store_at_offset(dKh, to, wk[v]);
+            if (with_v) store_at_offset(dVh, to, wv[v]);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      tiles_out(ROWS != ROWS_TURN, true);
+      if (turn) {
+        u32x4 w[4];
+        const int c = turn_rows(smem + C::OFF_TURN, aux, p.scale, p.rope_interleaved, lane, w);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int s = T0 + RB * jp + 8 * v + r8;
+          if (s >= k0 && s < k1) store_at_offset(dKh, at[v] + c * 16, w[v]);
+        }
+      } else if (ROWS == ROWS_TURN) {
+        tiles_out(true, false);
       }
     }
     __builtin_amdgcn_sched_barrier(0);  // the accumulators' registers are free from here on
-    int pos_q;  // position of this lane's query slot (both halves of the wave alike)
-    u32x4 orow[4] = {}, tq[8] = {};
-    float lse = 0.f, dsum = 0.f;
+    u32x4 auxq[8] = {};
+    if (out_q && ROWS != ROWS_PLAIN) {
+      const int lane = fresh(lane0), r8 = lane >> 3, c8 = lane & 7;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const uint32_t row = query_row(i - 1, 8 * v + r8);
+        if (ROWS == ROWS_ADD) auxq[v] = row_at_offset(dQh, row + c8 * 16);
+        else {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) auxq[2 * v + h] = row_at_offset(rope, 2 * row + c8 * 32 + h * 16);
+        }
+      }
+    }
+    u32x4 tq[8] = {};
     {
       const int lane = fresh(lane0), r8 = lane >> 3, c8 = lane & 7;
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the rows have been read: their tiles take the next key block
@@ -378,20 +437,13 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
         load_to_lds_16(Kh, goff[v], lds0 + ktile + v * 1024);
         load_to_lds_16(Vh, goff[v], lds0 + vtile + v * 1024);
       }
-      pos_q = qpos_lds[want_q ? RB * iq + (lane & 31) : 0];
-      if (want_q) {
-        lse = p.lse_in[row0 + pos_q];
-        if (!Oh) dsum = p.Dsum[row0 + pos_q];
-        if (Oh || ROWS == ROWS_TURN) {
+      if (scalars_later) request_scalars();
+      if (ROWS == ROWS_TURN && want_q) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const uint32_t row = query_row(iq, 8 * v + r8);
-            if (Oh) orow[v] = row_at_offset(Oh, row + (uint32_t)lane_chunk(lane, v) * 16);
-            if (ROWS == ROWS_TURN) {
+        for (int v = 0; v < 4; ++v) {
+          const uint32_t row = query_row(iq, 8 * v + r8);
 #pragma unroll
-              for (int h = 0; h < 2; ++h) tq[2 * v + h] = row_at_offset(rope, 2 * row + c8 * 32 + h * 16);
-            }
-          }
+          for (int h = 0; h < 2; ++h) tq[2 * v + h] = row_at_offset(rope, 2 * row + c8 * 32 + h * 16);
         }
       }
     }
@@ -402,53 +454,34 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
       const int lane = fresh(lane0), r8 = lane >> 3, c8 = lane & 7;
       const int slot0 = Q0 + RB * (i - 2);
       char* const area = smem + C::OFF_DQ + (i & 1) * ROWS_F32;
-      if (ROWS == ROWS_TURN) {  // the transpose of RoPE: turn by the negative angle, in place; a lane turns pairs 4 c8 .. 4 c8 + 3
-        f32x4 a[4], bb[4];
-        f32x4 *pa[4], *pb[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = 8 * v + r8;
-          char* const ra = area + row * (D * 4);
-          pa[v] = reinterpret_cast<f32x4*>(ra + (((p.rope_interleaved ? 2 * c8 : c8) ^ (row & 15)) * 16));
-          pb[v] = reinterpret_cast<f32x4*>(ra + (((p.rope_interleaved ? 2 * c8 + 1 : 8 + c8) ^ (row & 15)) * 16));
-          a[v] = *pa[v];
-          bb[v] = *pb[v];
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const f32x4 t0 = __builtin_bit_cast(f32x4, auxq[2 * v]), t1 = __builtin_bit_cast(f32x4, auxq[2 * v + 1]);
-          if (p.rope_interleaved) {
-            *pa[v] = f32x4{a[v][0] * t0[0] + a[v][1] * t0[1], a[v][1] * t0[0] - a[v][0] * t0[1], a[v][2] * t0[2] + a[v][3] * t0[3], a[v][3] * t0[2] - a[v][2] * t0[3]};
-            *pb[v] = f32x4{bb[v][0] * t1[0] + bb[v][1] * t1[1], bb[v][1] * t1[0] - bb[v][0] * t1[1], bb[v][2] * t1[2] + bb[v][3] * t1[3], bb[v][3] * t1[2] - bb[v][2] * t1[3]};
-          } else {
-            *pa[v] = f32x4{a[v][0] * t0[0] + bb[v][0] * t0[1], a[v][1] * t0[2] + bb[v][1] * t0[3], a[v][2] * t1[0] + bb[v][2] * t1[1], a[v][3] * t1[2] + bb[v][3] * t1[3]};
-            *pb[v] = f32x4{bb[v][0] * t0[0] - a[v][0] * t0[1], bb[v][1] * t0[2] - a[v][1] * t0[3], bb[v][2] * t1[0] - a[v][2] * t1[1], bb[v][3] * t1[2] - a[v][3] * t1[3]};
-          }
-        }
-        wave_lds_sync();
-      }
       uint32_t at[4];
-      float x[4][8];
+      u32x4 w[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        at[v] = query_row(i - 2, 8 * v + r8) + c8 * 16;
-        get_row8(area, 8 * v + r8, c8, x[v]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
+      for (int v = 0; v < 4; ++v) at[v] = query_row(i - 2, 8 * v + r8);
+      int c = c8;
+      if (ROWS == ROWS_TURN) {
+        c = turn_rows(area, auxq, p.scale, p.rope_interleaved, lane, w);
+      } else {
+        float x[4][8];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        u32x4 w;
+        for (int v = 0; v < 4; ++v) get_row8(area, 8 * v + r8, c8, x[v]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float v0 = x[v][2 * e] * p.scale, v1 = x[v][2 * e + 1] * p.scale;
-          if (ROWS == ROWS_ADD) {
-            v0 += bf16lo(auxq[v][e]);
-            v1 += bf16hi(auxq[v][e]);
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float v0 = x[v][2 * e] * p.scale, v1 = x[v][2 * e + 1] * p.scale;
+            if (ROWS == ROWS_ADD) {
+              v0 += bf16lo(auxq[v][e]);
+              v1 += bf16hi(auxq[v][e]);
+            }
+            w[v][e] = pack_bf16(v0, v1);
           }
-          w[e] = pack_bf16(v0, v1);
-        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
         const int s = slot0 + 8 * v + r8;
-        if (s >= k0 && s < k1) store_at_offset(dQh, at[v], w);
+        if (s >= k0 && s < k1) store_at_offset(dQh, at[v] + c * 16, w[v]);
       }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the query tiles requested two intervals ago (not seen by the compiler)
@@ -529,6 +562,13 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
       kf[kk] = lds_row((row_at + ktile) ^ (32 * kk));
       vf[kk] = lds_row((row_at + vtile) ^ (32 * kk));
     }
+    // ones against the three values of -LSE / scale, of -D, in the operand rows (contraction indices 0..2 and 4..6)
+    const uint32_t one2 = g2 == 0 ? 0x3F803F80u : 0u, one1 = one2 & 0xffffu;
+    const bf16x8 ones_l = __builtin_bit_cast(bf16x8, (u32x4{one2, one1, 0, 0})), ones_d = __builtin_bit_cast(bf16x8, (u32x4{0, 0, one2, one1}));
+    __builtin_amdgcn_s_setprio(0);
+    if (next_interval()) return;
+
+    // ---- NB intervals with key block j
     {  // dQ needs the K tile as the transposed operand (columns 32 db.., key rows 16 c..): laid out so once instead of NB times
       bf16x8 kt[4];
 #pragma unroll
@@ -537,13 +577,6 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
 #pragma unroll
       for (int m = 0; m < 4; ++m) *reinterpret_cast<bf16x8*>(smem + ktile + m * 1024 + lane_a * 16) = kt[m];
     }
-    // ones against the three values of -LSE / scale, of -D, in the operand rows (contraction indices 0..2 and 4..6)
-    const uint32_t one2 = g2 == 0 ? 0x3F803F80u : 0u, one1 = one2 & 0xffffu;
-    const bf16x8 ones_l = __builtin_bit_cast(bf16x8, (u32x4{one2, one1, 0, 0})), ones_d = __builtin_bit_cast(bf16x8, (u32x4{0, 0, one2, one1}));
-    __builtin_amdgcn_s_setprio(0);
-    if (next_interval()) return;
-
-    // ---- NB intervals with key block j
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -664,7 +697,7 @@ __global__ __launch_bounds__(Cfg<NB>::NT) void bwd_strip_bf16_kernel(const Pass 
 
 // Strips of a call: as many per head as fill k rounds of the card's CUs (one workgroup per CU), with the k for which the rounds'
 // intervals are fewest.
-Strips plan(const Pass& p, int nb, long* intervals) {
+Strips plan(const Pass& p, int nb) {
   const long heads = (long)p.B * p.Hq;
   const int most = (p.n + RB - 1) / RB;
   Strips best = {};
@@ -682,18 +715,16 @@ Strips plan(const Pass& p, int nb, long* intervals) {
       best = {m, slots};
     }
   }
-  *intervals = least;
   return best;
 }
 
 template <int NB, int CAUSAL>
 hipError_t launch_t(const Pass& p, hipStream_t st) {
-  long intervals;
-  const Strips s = plan(p, NB, &intervals);
+  const Strips s = plan(p, NB);
   const long total = (long)p.B * p.Hq * s.per_head;
   const long blocks = xcd_grid_blocks(total);
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks), block(Cfg<NB>::NT);
+  const dim3 grid((unsigned)blocks), block((Cfg<NB, ROWS_PLAIN>::NT));
   if (p.rope_table) hipLaunchKernelGGL((bwd_strip_bf16_kernel<NB, CAUSAL, ROWS_TURN>), grid, block, 0, st, p, s, total);
   else if (p.accumulate) hipLaunchKernelGGL((bwd_strip_bf16_kernel<NB, CAUSAL, ROWS_ADD>), grid, block, 0, st, p, s, total);
   else hipLaunchKernelGGL((bwd_strip_bf16_kernel<NB, CAUSAL, ROWS_PLAIN>), grid, block, 0, st, p, s, total);
