@@ -279,6 +279,260 @@ __global__ __launch_bounds__(GNT, 2) void gate_proj_fwd_bf16_kernel(const GatePr
   stage_flush(reinterpret_cast<bf16_t*>(MODE == GP_BWD_INPUT ? p.Y_out[only] : p.Y));
 }
 
+// The same two products in wide tiles: a wave owns 128 tokens x 64 output features as 4 x 2 blocks.  Per 16 contraction indices it
+// reads 6 KB of operands from LDS for eight matrix instructions (64 x 64: 4 KB for four), and a workgroup brings in half to three
+// quarters of the bytes per product; both are nearly as much time as the matrix work at 64 x 64.  Eight waves, one workgroup per
+// CU; tiles arrive by direct global-to-LDS loads, one barrier a step.
+//   BOTH (forward of both branches): 256 tokens x 128 features of either branch, four waves each, steps of 32 contraction
+//            indices, three buffers.  Neither branch's term of Eq. 5 waits in registers for the other: at the end each wave gives
+//            its half of the terms to the wave of the other branch with the same outputs (fp32, through LDS) and writes the other
+//            half of Y.
+//   else     256 x 256, steps of 64 (whole lines), two buffers: input gradients (the branches are independent parts of the work
+//            list) and the forward of a single path.
+// Measured at B4, n = 8192, 16 heads of 64 (us): forward of both branches 180 -> 171 (124 without the loads: half lines, 64 bytes of a row
+// a step, cost 12 of the rest; two buffers of whole lines do not fit beside either branch's tiles), single path 94 -> 78 = 0.88
+// PFLOP/s, backward of both 460 -> 427.  A step's loads go out with the first two operand groups, not all behind the barrier:
+// 173 -> 170, 80 -> 78.  Wave priorities around the products: no change.
+constexpr int XTM = 256;
+constexpr int XNT = 512;
+constexpr int XSTR = 64 + 8;                     // bf16 per staged row
+constexpr int XAREA = 64 * XSTR * 2;             // staged 64 tokens x 64 features
+static_assert(2 * XAREA >= 64 * 64 * 4, "a wave's two staging areas hold 64 x 64 in fp32");
+
+template <bool BOTH>
+struct Wide {
+  static constexpr int FEATS = BOTH ? 128 : 256;              // output features of a workgroup
+  static constexpr int K = BOTH ? 32 : 64;                    // contraction step
+  static constexpr int STAGES = BOTH ? 3 : 2;
+  static constexpr int ROW = K * 2;                           // bytes of a tile row, 16-byte chunks XORed by swizzle()
+  static constexpr int PART = (XTM + FEATS) * ROW;            // a branch's share of a stage: tokens | weights
+  static constexpr int STAGE = (BOTH ? 2 : 1) * PART;
+  static constexpr int LDS = STAGES * STAGE > 8 * 2 * XAREA ? STAGES * STAGE : 8 * 2 * XAREA;
+  static constexpr int ROWS = 1024 / ROW;                     // rows that one instruction of a wave fills
+  static constexpr int WAVES = BOTH ? 4 : 8;                  // that load a part
+  static constexpr int TLOADS = XTM / ROWS / WAVES, WLOADS = FEATS / ROWS / WAVES;
+  // 16 rows x the same chunk are 16 different places of 16 bytes in the 64 banks
+  static __device__ int swizzle(int row) { return BOTH ? (row >> 2) & 3 : swz<64>(row); }
+};
+
+template <int D, int MODE, bool BOTH>
+__global__ __launch_bounds__(XNT, 2) void gate_proj_wide_bf16_kernel(const GateProj p, const int num_tt, const int num_ft,
+                                                                     const long total_work) {
+  using X = Wide<BOTH>;
+  __shared__ __attribute__((aligned(1024))) char smem[X::LDS];
+  const long work = xcd_work_index(total_work);
+  if (work < 0) return;
+  const int ft = (int)(work % num_ft);
+  long rest = work / num_ft;
+  const int tt = (int)(rest % num_tt);
+  rest /= num_tt;
+  const int b = (int)(rest % p.B);
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int x = BOTH ? wave >> 2 : (MODE == GP_BWD_INPUT ? (int)(rest / p.B) : 0);  // this wave's branch
+  const int wl = BOTH ? wave & 3 : wave, wm = wl & 1, wn = wl >> 1;                 // among the branch's waves: token half, 64 features
+  const int g2 = lane >> 5, c32 = lane & 31;
+  const int n = p.n, H = p.Hq, dm = H * D;
+  const int i0 = tt * XTM, o0 = ft * X::FEATS;
+  const int nk = dm / X::K;
+  const bf16_t* __restrict__ Yb = reinterpret_cast<const bf16_t*>(p.Y_x[x]) + (size_t)b * H * n * D;
+  const bf16_t* __restrict__ Wb = reinterpret_cast<const bf16_t*>(p.W_x[x]) + (size_t)o0 * dm;
+
+  // loader: one instruction of a wave fills 1 KB of a tile; the lane delivers one physical chunk of one of its rows
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+  const uint32_t part = lds0 + (BOTH ? x * X::PART : 0);
+  constexpr int CH = X::ROW / 16;  // chunks of a row
+  uint32_t toff[X::TLOADS], woff[X::WLOADS];
+#pragma unroll
+  for (int j = 0; j < X::TLOADS; ++j) {
+    const int row = X::ROWS * (wl + X::WAVES * j) + lane / CH;
+    toff[j] = (uint32_t)min(i0 + row, n - 1) * (uint32_t)(D * 2) + (((lane % CH) ^ X::swizzle(row)) * 16);
+  }
+#pragma unroll
+  for (int j = 0; j < X::WLOADS; ++j) {
+    const int row = X::ROWS * (wl + X::WAVES * j) + lane / CH;
+    woff[j] = (uint32_t)row * (uint32_t)(dm * 2) + (((lane % CH) ^ X::swizzle(row)) * 16);
+  }
+  constexpr int LOADS = X::TLOADS + X::WLOADS;
+  auto request = [&](int st, int buf, int from, int till) {  // instructions `from` to `till` of a step's LOADS
+    const int k0 = st * X::K;
+    const bf16_t* ys = Yb + (size_t)(k0 / D) * n * D + k0 % D;
+    const bf16_t* ws = Wb + k0;
+    const uint32_t to = part + buf * X::STAGE + wl * 1024;
+#pragma unroll
+    for (int j = from; j < till; ++j)
+      load_to_lds_16(j < X::TLOADS ? ys : ws, j < X::TLOADS ? toff[j < X::TLOADS ? j : 0] : woff[j < X::TLOADS ? 0 : j - X::TLOADS], to + X::WAVES * 1024 * j);
+  };
+
+  // accumulator 4q + e of block (fi, ti) of lane (g2, c32): token 128 wm + 32 ti + c32, feature 64 wn + 32 fi + 8 q + 4 g2 + e
+  f32x16 acc[2][4];
+#pragma unroll
+  for (int fi = 0; fi < 2; ++fi)
+#pragma unroll
+    for (int ti = 0; ti < 4; ++ti)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[fi][ti][i] = 0.f;
+
+  typedef __attribute__((address_space(3))) const bf16x8* lds_bf16x8;
+  const uint32_t chunk = (uint32_t)((g2 ^ X::swizzle(c32)) * 16);  // chunk g2 of row c32; chunk 2 ks + g2: ^ 32 ks
+  const uint32_t tok_at = part + (128 * wm + c32) * X::ROW + chunk, wgt_at = part + (XTM + 64 * wn + c32) * X::ROW + chunk;
+  request(0, 0, 0, LOADS);
+  if (X::STAGES == 3) request(1, 1, 0, LOADS);
+  int buf = 0;
+  for (int st = 0; st < nk; ++st) {
+    // step st of this wave has landed (the younger one of three buffers may be under way); after the barrier it is whole, and
+    // everyone has read the operands of step st - 1, whose buffer is the next to be filled
+    static_assert(!BOTH || X::TLOADS + X::WLOADS == 6, "the wait below");
+    if (X::STAGES == 3 && st + 1 < nk) asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const bool more = st + X::STAGES - 1 < nk;
+    const int into = buf == 0 ? X::STAGES - 1 : buf - 1;
+    const uint32_t ta = tok_at + buf * X::STAGE, wa = wgt_at + buf * X::STAGE;
+    bf16x8 fa[2][2], fb[2][4];
+    auto operands = [&](int ks) {
+#pragma unroll
+      for (int fi = 0; fi < 2; ++fi) fa[ks & 1][fi] = *(lds_bf16x8)(uintptr_t)((wa ^ (32 * ks)) + fi * 32 * X::ROW);
+#pragma unroll
+      for (int ti = 0; ti < 4; ++ti) fb[ks & 1][ti] = *(lds_bf16x8)(uintptr_t)((ta ^ (32 * ks)) + ti * 32 * X::ROW);
+    };
+    operands(0);
+#pragma unroll
+    for (int ks = 0; ks < X::K / 16; ++ks) {
+      if (ks + 1 < X::K / 16) operands(ks + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (more && ks < 2) request(st + X::STAGES - 1, into, ks * LOADS / 2, (ks + 1) * LOADS / 2);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ti = 0; ti < 4; ++ti)
+#pragma unroll
+        for (int fi = 0; fi < 2; ++fi) acc[fi][ti] = mfma_bf16(fa[ks & 1][fi], fb[ks & 1][ti], acc[fi][ti]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    buf = buf == X::STAGES - 1 ? 0 : buf + 1;
+  }
+
+  // The epilogue takes the wave's outputs in two halves of 64 tokens; tensors come and go as whole 128-byte pieces of rows
+  // through the wave's own two areas.  (rows past n: the last row's values, never stored)
+  char* const mine = smem + wave * (2 * XAREA);
+  bf16_t* const area[2] = {reinterpret_cast<bf16_t*>(mine), reinterpret_cast<bf16_t*>(mine + XAREA)};
+  const int o = o0 + 64 * wn;  // first of the wave's 64 features: inside one head
+  const size_t col = ((size_t)b * H + o / D) * n * D + o % D + (lane & 7) * 8;
+  const int t0 = i0 + 128 * wm + (lane >> 3);
+  auto fetch_rows = [&](const void* src, int half, u32x4* v) {
+#pragma unroll
+    for (int pass = 0; pass < 8; ++pass)
+      v[pass] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const bf16_t*>(src) + col + (size_t)min(t0 + 64 * half + 8 * pass, n - 1) * D);
+  };
+  auto put_rows = [&](bf16_t* a, const u32x4* v) {
+#pragma unroll
+    for (int pass = 0; pass < 8; ++pass) *reinterpret_cast<u32x4*>(a + (pass * 8 + (lane >> 3)) * XSTR + (lane & 7) * 8) = v[pass];
+  };
+  auto flush = [&](void* dst, int half, const bf16_t* a) {
+#pragma unroll
+    for (int pass = 0; pass < 8; ++pass) {
+      const int token = t0 + 64 * half + 8 * pass;
+      if (token < n)
+        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(a + (pass * 8 + (lane >> 3)) * XSTR + (lane & 7) * 8),
+                                    reinterpret_cast<u32x4*>(reinterpret_cast<bf16_t*>(dst) + col + (size_t)token * D));
+    }
+  };
+  auto at = [&](bf16_t* a, int fi, int t2, int q) { return reinterpret_cast<u32x2*>(a + (32 * t2 + c32) * XSTR + 32 * fi + 8 * q + 4 * g2); };
+
+  void* const Gx = MODE == GP_FORWARD ? p.G_x[x] : nullptr;
+  u32x4 r1[8], r2[8];
+  fetch_rows(MODE == GP_FORWARD ? p.Y_x[x] : p.E1, 0, r1);
+  if (MODE == GP_BWD_INPUT) fetch_rows(p.E2[x], 0, r2);
+  __syncthreads();  // every wave has read its last operands: the areas are free
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    put_rows(area[0], r1);
+    if (MODE == GP_BWD_INPUT) put_rows(area[1], r2);
+    wave_lds_sync();
+    if (half == 0) {
+      fetch_rows(MODE == GP_FORWARD ? p.Y_x[x] : p.E1, 1, r1);
+      if (MODE == GP_BWD_INPUT) fetch_rows(p.E2[x], 1, r2);
+    }
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+      for (int fi = 0; fi < 2; ++fi)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          f32x16& v = acc[fi][2 * half + t2];
+          const u32x2 a = *at(area[0], fi, t2, q);
+          const float av[4] = {bf16lo(a[0]), bf16hi(a[0]), bf16lo(a[1]), bf16hi(a[1])};
+          if (MODE == GP_FORWARD) {
+            float gv[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              gv[e] = sigmoidf_rcp(v[4 * q + e]);
+              v[4 * q + e] = gv[e] * av[e];
+            }
+            if (Gx) *at(area[1], fi, t2, q) = u32x2{pack_bf16(gv[0], gv[1]), pack_bf16(gv[2], gv[3])};
+          } else {
+            const u32x2 c = *at(area[1], fi, t2, q);
+            const float r[4] = {fmaf(av[0], bf16lo(c[0]), v[4 * q]), fmaf(av[1], bf16hi(c[0]), v[4 * q + 1]),
+                                fmaf(av[2], bf16lo(c[1]), v[4 * q + 2]), fmaf(av[3], bf16hi(c[1]), v[4 * q + 3])};
+            *at(area[0], fi, t2, q) = u32x2{pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3])};
+          }
+        }
+    if (MODE == GP_BWD_INPUT || Gx) {
+      wave_lds_sync();
+      flush(MODE == GP_BWD_INPUT ? p.Y_out[x] : Gx, half, area[MODE == GP_BWD_INPUT ? 0 : 1]);
+    }
+    wave_lds_sync();
+  }
+  if (MODE == GP_BWD_INPUT) return;
+
+  // Y: this wave writes the half of its branch's number, with the other branch's terms added (single path: both halves)
+  auto terms = [&](int fi, int t2, int q, const char* w) { return reinterpret_cast<const f32x4*>(w + ((fi * 2 + t2) * 4 + q) * 1024 + lane * 16); };
+  if (BOTH) {
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+      for (int fi = 0; fi < 2; ++fi)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          f32x4 give;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float lo = acc[fi][t2][4 * q + e], hi = acc[fi][2 + t2][4 * q + e];
+            give[e] = x == 0 ? hi : lo;
+            acc[fi][t2][4 * q + e] = x == 0 ? lo : hi;
+          }
+          *const_cast<f32x4*>(terms(fi, t2, q, mine)) = give;
+        }
+    __syncthreads();
+    const char* theirs = smem + (wave ^ 4) * (2 * XAREA);
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+      for (int fi = 0; fi < 2; ++fi)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 got = *terms(fi, t2, q, theirs);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[fi][t2][4 * q + e] += got[e];
+        }
+    __syncthreads();  // the partner has read this wave's share
+  }
+#pragma unroll
+  for (int half = 0; half < (BOTH ? 1 : 2); ++half) {
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+      for (int fi = 0; fi < 2; ++fi)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& v = acc[fi][2 * half + t2];
+          *at(area[0], fi, t2, q) = u32x2{pack_bf16(v[4 * q], v[4 * q + 1]), pack_bf16(v[4 * q + 2], v[4 * q + 3])};
+        }
+    wave_lds_sync();
+    flush(p.Y, BOTH ? x : half, area[0]);
+    wave_lds_sync();
+  }
+}
 
 // The backward's launches serve both branches at once (blockIdx.y, .z or a part of the work list): per branch the three small
 // passes cost a launch of 5 us each, and short calls leave the chip idle in the products.
@@ -471,11 +725,42 @@ __global__ __launch_bounds__(256) void gate_dw_round_kernel(const GateBwd p, con
   }
 }
 
+// The wide tiles come in rounds of 256 workgroups, one per CU; the narrow ones, half a wide one of both branches each, fill a round in
+// two goes.  So the wide ones win where more than half of the last round's CUs have one.  Wide / narrow (us), 16 heads of 64:
+//   both branches forward   112 wide workgroups 34.9 / 30.6, 144 35.1 / 40.6, 256 43.7 / 48.0, 272 75.7 / 72.2, 384 77.3 / 75.7, 416 79.6 / 87.9,
+//                           512 86.2 / 92.2, 640 119 / 117, 704 123 / 129, 1024 171 / 180
+//   backward of both        112 80.2 / 77.4, 144 88.3 / 95.0, 256 124 / 131, 320 159 / 154, 416 183 / 196, 512 207 / 224, 576 272 / 270, 640 283 / 297
+//   single path             128 29.3 / 26.6, 136 28.7 / 39.3, 256 38.8 / 49.2, 288 63.5 / 61.0, 448 69.1 / 86.8
+// Past two rounds the 256 x 256 ones are at least level at any remainder.  12 and 8 heads of 64 and 8 of 128 agree.
+bool wide_is_faster(long workgroups, bool both) {
+  if (workgroups <= 0) return false;
+  return (workgroups - 1) % 256 >= 128 || (!both && workgroups > 512);
+}
+
 template <int MODE>
 hipError_t launch_gemm(const GateProj& p, hipStream_t st) {
   const long dm = (long)p.Hq * p.d;
-  const int num_tt = (p.n + TM - 1) / TM, num_ft = (int)(dm / TN);
-  const long total = (long)num_tt * num_ft * p.B * (MODE == GP_BWD_INPUT && p.Y_x[1] ? 2 : 1);
+  const int num_ft = (int)(dm / TN);
+  const int parts = MODE == GP_BWD_INPUT && p.Y_x[1] ? 2 : 1;  // of the work list
+  const bool both = MODE == GP_FORWARD && p.Y_x[1];
+  const int feats = both ? Wide<true>::FEATS : Wide<false>::FEATS;
+  const long wide = dm % feats ? 0 : (long)((p.n + XTM - 1) / XTM) * (dm / feats) * p.B * parts;
+  if ((size_t)p.n * p.d * 2 < ((size_t)1 << 32) && wide_is_faster(wide, both)) {  // 32-bit offsets inside a head
+    const int num_tt = (p.n + XTM - 1) / XTM, num_ft = (int)(dm / feats);
+    const long blocks = xcd_grid_blocks(wide);
+    if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks);
+    if (both) {
+      if (p.d == 64) hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<64, GP_FORWARD, true>), grid, dim3(XNT), 0, st, p, num_tt, num_ft, wide);
+      else hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<128, GP_FORWARD, true>), grid, dim3(XNT), 0, st, p, num_tt, num_ft, wide);
+    } else {
+      if (p.d == 64) hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<64, MODE, false>), grid, dim3(XNT), 0, st, p, num_tt, num_ft, wide);
+      else hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<128, MODE, false>), grid, dim3(XNT), 0, st, p, num_tt, num_ft, wide);
+    }
+    return hipGetLastError();
+  }
+  const int num_tt = (p.n + TM - 1) / TM;
+  const long total = (long)num_tt * num_ft * p.B * parts;
   const long blocks = xcd_grid_blocks(total);
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
   if (p.d == 64) hipLaunchKernelGGL((gate_proj_fwd_bf16_kernel<64, MODE>), dim3((unsigned)blocks), dim3(GNT), 0, st, p, num_tt, num_ft, total);

@@ -188,3 +188,15 @@ def test_weight_gradients_of_short_calls_repeat_themselves(B, H, d, n, dual):
     for x in range(k):
         ref = (tok(dY) * tok(Y[x]) * tok(G[x]) * (1 - tok(G[x]))).T @ tok(Y[x])
         assert (first[x].double() - ref).norm() <= 5e-3 * ref.norm()
+
+
+@pytest.mark.parametrize("B,H,n,d,dual", [(130, 2, 40, 64, True), (44, 2, 600, 64, True), (130, 1, 257, 128, True), (130, 4, 40, 64, False),
+                                          (65, 2, 257, 128, False)])
+def test_wide_tiles_forward(B, H, n, d, dual):
+    """130 and 132 workgroups of 256 tokens x 128 (both branches) or 256 (single path) features: more than half a round."""
+    run_case(B, H, n, d, seed=B + n, dual=dual, want_gates=n != 600)
+
+
+@pytest.mark.parametrize("B,H,n,d,dual", [(65, 4, 40, 64, True), (33, 2, 300, 128, True), (22, 8, 129, 64, True), (44, 4, 600, 64, False)])
+def test_wide_tiles_backward(B, H, n, d, dual):
+    run_bwd_case(B, H, n, d, seed=B + n, dual=dual)
