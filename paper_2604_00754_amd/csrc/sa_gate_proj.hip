@@ -21,9 +21,9 @@
 //   dy_x = dY * g_x + W_x^T dz_x                          the forward kernel again: tokens = dz_x,
 //                                                         weights = W_x^T (transposed once), epilogue = + dY * g_x
 //   dW_x = sum_t dz_x[t] y_x[t]^T                         contraction over tokens: both operands are
-//                                                         transposed on their way into LDS (4 x 8 register
-//                                                         transposes), a workgroup owns 128 x 128 of dW for a
-//                                                         chunk of tokens and adds it with fp32 atomics
+//                                                         read by the transposing LDS read, a workgroup
+//                                                         owns 128 x 128 of dW for a piece of the tokens and
+//                                                         adds it with fp32 atomics
 #include "sa_common.h"
 #include "sa_mfma.h"
 
@@ -547,24 +547,30 @@ struct GateBwd {
   uint16_t* dW[2];
 };
 
-// dz = dY * y * g * (1 - g), rounded to bf16; 8 elements per thread.  blockIdx.y = branch.
+// dz = dY * y * g * (1 - g), rounded to bf16; 8 elements per thread, all branches at once: dY is read once for both (bound: HBM; the
+// pass was 81 us for two branches at B4, n = 8192, 16 heads of 64, and the call is 13 us shorter without the second reading).
+template <int BRANCHES>
 __global__ __launch_bounds__(256) void gate_dz_bf16_kernel(const GateBwd p, const size_t vecs) {
-  const uint16_t* __restrict__ dY = p.dY;
-  const uint16_t* __restrict__ Yx = p.Y_x[blockIdx.y];
-  const uint16_t* __restrict__ Gx = p.G_x[blockIdx.y];
-  uint16_t* __restrict__ dz = p.dz[blockIdx.y];
   size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * 256;
   for (; i < vecs; i += stride) {
-    const u32x4 a = *reinterpret_cast<const u32x4*>(dY + 8 * i), y = *reinterpret_cast<const u32x4*>(Yx + 8 * i);
-    const u32x4 g = *reinterpret_cast<const u32x4*>(Gx + 8 * i);
-    u32x4 o;
+    const u32x4 a = *reinterpret_cast<const u32x4*>(p.dY + 8 * i);
+    u32x4 y[BRANCHES], g[BRANCHES];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float gl = bf16lo(g[e]), gh = bf16hi(g[e]);
-      o[e] = pack_bf16(bf16lo(a[e]) * bf16lo(y[e]) * gl * (1.f - gl), bf16hi(a[e]) * bf16hi(y[e]) * gh * (1.f - gh));
+    for (int x = 0; x < BRANCHES; ++x) {
+      y[x] = *reinterpret_cast<const u32x4*>(p.Y_x[x] + 8 * i);
+      g[x] = *reinterpret_cast<const u32x4*>(p.G_x[x] + 8 * i);
     }
-    *reinterpret_cast<u32x4*>(dz + 8 * i) = o;
+#pragma unroll
+    for (int x = 0; x < BRANCHES; ++x) {
+      u32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float gl = bf16lo(g[x][e]), gh = bf16hi(g[x][e]);
+        o[e] = pack_bf16(bf16lo(a[e]) * bf16lo(y[x][e]) * gl * (1.f - gl), bf16hi(a[e]) * bf16hi(y[x][e]) * gh * (1.f - gh));
+      }
+      *reinterpret_cast<u32x4*>(p.dz[x] + 8 * i) = o;
+    }
   }
 }
 
@@ -583,21 +589,24 @@ __global__ __launch_bounds__(256) void gate_bwd_setup_kernel(const GateBwd p, co
   for (int e = threadIdx.x; e < 64 * 64; e += 256) Wt[(size_t)(c0 + e / 64) * dm + r0 + e % 64] = tile[e % 64][e / 64];
 }
 
-// dW[o][k] += sum over a chunk of tokens of dz[t][o] * y[t][k].  Workgroup = 128 x 128 of dW, 4 waves
+// dW[o][k] += sum over a piece of the tokens of dz[t][o] * y[t][k].  Workgroup = 128 x 128 of dW, 4 waves
 // as 2 x 2.  The contraction runs over tokens, which is the slow index of both operands in memory, so
 // both tiles are brought in as they lie ([token][128 features], by direct global-to-LDS loads, unpadded
 // rows with swizzled 16-byte chunks) and both operands are read with the transposing LDS read: a lane
 // gets the same 8 tokens of one feature column for the A operand (dz^T) and the B operand (y).
-// Steps of 32 tokens, four buffers, three steps in flight.  Tokens past the chunk's end are zeroed in
+// Steps of 32 tokens, four buffers, three steps in flight.  Tokens past a batch's end are zeroed in
 // the dz tile after it has landed.
-// Tokens per workgroup.  A call that pieces of WCHUNK tokens cut into one or two is cut into two at most: two additions to
-// zero give the same bits in either order, so dW repeats itself.  (It is the faster cut as well for 12 and 16 heads of 64:
+// A piece of the tokens per workgroup: a run of steps, over the batches one after the other.  A call of one or two batches that pieces
+// of WCHUNK tokens cut into one or two is cut into two at most: two additions to zero give the same bits in either order, so dW
+// repeats itself.  (It is the faster cut as well for 12 and 16 heads of 64:
 // every further piece adds its 64 KB per tile in memory; the whole backward of the gates with 4 and 8 pieces, as many as fill the chip,
 // and with two: n = 1100 51.6 / 44.3 us, 2048 65.4 / 48.3, 4096 78.5 / 64.6; with two heads, one tile, n = 8192 28.6 / 56.4.)
-// Longer calls add in no fixed order: WCHUNK, halved down to WCHUNK_LEAST until the launch has WTARGET workgroups, one per CU.  Two per CU
-// cost more in additions than they gave (whole backward, both branches, two per CU / one): 13 x 476 tokens of 8 heads of 64 79.0 / 60.0 us,
-// 13 x 407 of 4 of 128 77.7 / 58.2, 6 x 2735 of 12 of 64 168 / 152; 66 drawn calls 0.75 ... 1.02.
-constexpr int WCHUNK = 4096, WCHUNK_LEAST = 256;
+// Longer calls add in no fixed order: equal pieces, as many as fill the chip once, with two workgroups per CU where a piece then has WLONG
+// tokens and one where not (whole backward, 512 / 256 workgroups, us: 16 heads of 64, B4 n = 8192 409 / 431, B1 n = 16384 203 / 217,
+// 9000 145.5 / 144.9, B3 n = 2048 104 / 100; 8 heads, 13 x 476 64 / 55), each of WLEAST at least (3 x 512 of 4 heads 23.8, 256 workgroups 29.3).
+// Half as many pieces again (768 workgroups) 5 % slower and more.  Pieces that end with their batch at 4096 tokens took 13 x 613
+// tokens of 16 heads 190 us, now 139; 8 x 1024 of 12 heads 105, now 90; 16 x 4096 of 16 heads 840, now 798.
+constexpr int WCHUNK = 4096, WLONG = 2048, WLEAST = 256;
 constexpr long WTARGET = 256;
 constexpr int WSTEP = 32;
 constexpr int WSTAGES = 4;
@@ -607,7 +616,7 @@ constexpr int WLOADS_PER_STAGE = 4;           // instructions per thread: 2 rows
 
 template <int D>
 __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, const int B, const int H, const int n, const int num_ft,
-                                                               const int chunk, const int chunks_per_b, const long total_work) {
+                                                               const int piece_steps, const int pieces, const long total_work) {
   __shared__ __attribute__((aligned(16))) char smem[WSTAGES * WSTAGE_BYTES];
   const long work = xcd_work_index(total_work);
   if (work < 0) return;
@@ -615,9 +624,7 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
   long rest = work / num_ft;
   const int ot = (int)(rest % num_ft);  // output-feature tile (rows of dW)
   rest /= num_ft;
-  const int ch = (int)(rest % chunks_per_b);
-  rest /= chunks_per_b;
-  const int b = (int)(rest % B), x = (int)(rest / B);  // x = branch
+  const int piece = (int)(rest % pieces), x = (int)(rest / pieces);  // x = branch
   const bf16_t* __restrict__ dz = reinterpret_cast<const bf16_t*>(p.dz[x]);
   const bf16_t* __restrict__ Yx = reinterpret_cast<const bf16_t*>(p.Y_x[x]);
   float* __restrict__ dW = p.dWf[x];
@@ -627,8 +634,8 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wo = wave & 1, wk = wave >> 1;
   const int g2 = lane >> 5, c32 = lane & 31;
-  const int t_begin = ch * chunk, t_end = min(t_begin + chunk, n);
-  const int nsteps = (t_end - t_begin + WSTEP - 1) / WSTEP;
+  const int steps_b = (n + WSTEP - 1) / WSTEP;  // steps of a batch
+  const int first = piece * piece_steps, nsteps = min(piece_steps, B * steps_b - first);
 
   // loader: one instruction of a wave fills 4 token rows (256 bytes each) of a tile; the lane delivers
   // physical chunk lane % 16 of token row wave * 4 + lane / 16 (+16 for the second instruction), i.e.
@@ -639,19 +646,21 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
   auto feature_offset = [&](int f) -> uint32_t {  // bytes from the batch's first element to (token 0, feature f)
     return (uint32_t)(((size_t)(f / D) * n * D + f % D) * 2);
   };
-  const bf16_t* zb = dz + (size_t)b * H * n * D;
-  const bf16_t* yb = Yx + (size_t)b * H * n * D;
   const uint32_t zfeat = feature_offset(ot * 128 + ld_feat), yfeat = feature_offset(kt * 128 + ld_feat);
-  auto request_step = [&](int st) {  // steps past the last one fetch its rows again and are never used
+  int rb = first / steps_b, rt = first % steps_b;  // batch and step of the next request
+  auto request_step = [&](int st) {  // past the call's last step: its rows again, never used
     const int buf = st & (WSTAGES - 1);
+    const bf16_t *zb = dz + (size_t)rb * H * n * D, *yb = Yx + (size_t)rb * H * n * D;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int token = min(t_begin + st * WSTEP + 16 * j + ld_row, t_end - 1);
+      const int token = min(rt * WSTEP + 16 * j + ld_row, n - 1);
       const uint32_t trow = (uint32_t)token * (uint32_t)(D * 2);
       const uint32_t dst = lds0 + buf * WSTAGE_BYTES + (16 * j + wave * 4) * 256;
       load_to_lds_16(zb, zfeat + trow, dst);
       load_to_lds_16(yb, yfeat + trow, dst + WTILE_BYTES);
     }
+    if (rt + 1 < steps_b) ++rt;
+    else if (rb + 1 < B) { rt = 0; ++rb; }
   };
 
   int troff[4][2];
@@ -668,6 +677,7 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
   request_step(0);
   request_step(1);
   request_step(2);
+  int ct = first % steps_b;  // step of the batch
   for (int st = 0; st < nsteps; ++st) {
     const int buf = st & (WSTAGES - 1);
     // all but the two youngest steps of this wave have landed; after the barrier step st is visible and
@@ -677,9 +687,9 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
     request_step(st + 3);
     bf16_t* Zt = reinterpret_cast<bf16_t*>(smem + buf * WSTAGE_BYTES);
     const bf16_t* Yt = reinterpret_cast<const bf16_t*>(smem + buf * WSTAGE_BYTES + WTILE_BYTES);
-    if (t_begin + (st + 1) * WSTEP > t_end) {  // ragged last step: tokens past the end contribute zeros
+    if ((ct + 1) * WSTEP > n) {  // a batch's ragged last step: tokens past the end contribute zeros
       const int row = tid >> 3;
-      if (t_begin + st * WSTEP + row >= t_end) {
+      if (ct * WSTEP + row >= n) {
         u32x4* r = reinterpret_cast<u32x4*>(Zt + row * 128 + (tid & 7) * 16);
         r[0] = u32x4{0u, 0u, 0u, 0u};
         r[1] = u32x4{0u, 0u, 0u, 0u};
@@ -698,6 +708,7 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
 #pragma unroll
         for (int ki = 0; ki < 2; ++ki) acc[oi][ki] = mfma_bf16(fa[oi], fb[ki], acc[oi][ki]);
     }
+    ct = ct + 1 < steps_b ? ct + 1 : 0;
   }
   wait_all_loads();  // the surplus steps requested near the end
   // accumulator 4q + x of lane (g2, c32): row o = 64wo + 32oi + 8q + 4g2 + x, column k = 64wk + 32ki + c32
@@ -819,28 +830,35 @@ static hipError_t gate_proj_bwd_branches(int branches, int B, int Hq, int n, int
     g.Y_x[x] = p.dz[x]; g.W_x[x] = p.Wt[x];
     g.Y_out[x] = dY_x[x]; g.E2[x] = G_x[x];
   }
-  const unsigned tiles = (unsigned)(dm / 64);
-  hipLaunchKernelGGL(gate_bwd_setup_kernel, dim3(tiles, tiles, branches), dim3(256), 0, st, p, (int)dm);
+  const unsigned blocks64 = (unsigned)(dm / 64);
+  hipLaunchKernelGGL(gate_bwd_setup_kernel, dim3(blocks64, blocks64, branches), dim3(256), 0, st, p, (int)dm);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(gate_dz_bf16_kernel, dim3(capped_blocks(act / 8, 256), branches), dim3(256), 0, st, p, act / 8);
+  if (branches == 2) hipLaunchKernelGGL(gate_dz_bf16_kernel<2>, dim3(capped_blocks(act / 8, 256)), dim3(256), 0, st, p, act / 8);
+  else hipLaunchKernelGGL(gate_dz_bf16_kernel<1>, dim3(capped_blocks(act / 8, 256)), dim3(256), 0, st, p, act / 8);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   e = launch_gemm<GP_BWD_INPUT>(g, st);
   if (e != hipSuccess) return e;
   const int num_ft = (int)(dm / 128);
-  int chunk = WCHUNK;
-  auto workgroups = [&]() -> long { return (long)num_ft * num_ft * ((n + chunk - 1) / chunk) * B * branches; };
+  const long tiles = (long)num_ft * num_ft * branches, steps = (long)((n + WSTEP - 1) / WSTEP) * B, tokens = (long)n * B;
+  if (steps > 0x7fffffffL) return hipErrorNotSupported;
+  long pieces;
   if ((long)((n + WCHUNK - 1) / WCHUNK) * B <= 2) {
-    if (B == 1 && n > WCHUNK_LEAST && workgroups() < 2 * WTARGET) chunk = ((n + 1) / 2 + WSTEP - 1) / WSTEP * WSTEP;
+    pieces = (n + WCHUNK - 1) / WCHUNK * B;
+    if (B == 1 && n > WLEAST && tiles * pieces < 2 * WTARGET) pieces = 2;
   } else {
-    while (chunk > WCHUNK_LEAST && workgroups() < WTARGET) chunk /= 2;
+    pieces = 2 * WTARGET / tiles;
+    if (pieces * WLONG > tokens) pieces = WTARGET / tiles;
+    if (pieces * WLEAST > tokens) pieces = tokens / WLEAST;
+    if (pieces < 1) pieces = 1;
   }
-  const int chunks = (n + chunk - 1) / chunk;
-  const long total = workgroups(), blocks = xcd_grid_blocks(total);
+  const int piece_steps = (int)((steps + pieces - 1) / pieces);
+  pieces = (steps + piece_steps - 1) / piece_steps;
+  const long total = tiles * pieces, blocks = xcd_grid_blocks(total);
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  if (d == 64) hipLaunchKernelGGL(gate_dw_bf16_kernel<64>, dim3((unsigned)blocks), dim3(GNT), 0, st, p, B, Hq, n, num_ft, chunk, chunks, total);
-  else hipLaunchKernelGGL(gate_dw_bf16_kernel<128>, dim3((unsigned)blocks), dim3(GNT), 0, st, p, B, Hq, n, num_ft, chunk, chunks, total);
+  if (d == 64) hipLaunchKernelGGL(gate_dw_bf16_kernel<64>, dim3((unsigned)blocks), dim3(GNT), 0, st, p, B, Hq, n, num_ft, piece_steps, (int)pieces, total);
+  else hipLaunchKernelGGL(gate_dw_bf16_kernel<128>, dim3((unsigned)blocks), dim3(GNT), 0, st, p, B, Hq, n, num_ft, piece_steps, (int)pieces, total);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(gate_dw_round_kernel, dim3(capped_blocks((size_t)dm * dm / 2, 256), branches), dim3(256), 0, st, p, (size_t)dm * dm / 2);

@@ -200,3 +200,9 @@ def test_wide_tiles_forward(B, H, n, d, dual):
 @pytest.mark.parametrize("B,H,n,d,dual", [(65, 4, 40, 64, True), (33, 2, 300, 128, True), (22, 8, 129, 64, True), (44, 4, 600, 64, False)])
 def test_wide_tiles_backward(B, H, n, d, dual):
     run_bwd_case(B, H, n, d, seed=B + n, dual=dual)
+
+
+@pytest.mark.parametrize("B,H,n,d,dual", [(7, 2, 333, 64, True), (9, 1, 97, 128, False), (40, 2, 31, 64, True)])
+def test_weight_gradient_pieces_across_batches(B, H, n, d, dual):
+    """Pieces of dW that end inside one batch and begin inside another, ragged last steps within a piece."""
+    run_bwd_case(B, H, n, d, seed=B + n, dual=dual)
