@@ -736,16 +736,19 @@ __global__ __launch_bounds__(256) void gate_dw_round_kernel(const GateBwd p, con
   }
 }
 
-// The wide tiles come in rounds of 256 workgroups, one per CU; the narrow ones, half a wide one of both branches each, fill a round in
-// two goes.  So the wide ones win where more than half of the last round's CUs have one.  Wide / narrow (us), 16 heads of 64:
-//   both branches forward   112 wide workgroups 34.9 / 30.6, 144 35.1 / 40.6, 256 43.7 / 48.0, 272 75.7 / 72.2, 384 77.3 / 75.7, 416 79.6 / 87.9,
-//                           512 86.2 / 92.2, 640 119 / 117, 704 123 / 129, 1024 171 / 180
-//   backward of both        112 80.2 / 77.4, 144 88.3 / 95.0, 256 124 / 131, 320 159 / 154, 416 183 / 196, 512 207 / 224, 576 272 / 270, 640 283 / 297
-//   single path             128 29.3 / 26.6, 136 28.7 / 39.3, 256 38.8 / 49.2, 288 63.5 / 61.0, 448 69.1 / 86.8
-// Past two rounds the 256 x 256 ones are at least level at any remainder.  12 and 8 heads of 64 and 8 of 128 agree.
-bool wide_is_faster(long workgroups, bool both) {
-  if (workgroups <= 0) return false;
-  return (workgroups - 1) % 256 >= 128 || (!both && workgroups > 512);
+// Wide tiles come in rounds of 256 workgroups, one per CU; narrow ones (half a wide one of both branches each, a quarter of a 256 x 256
+// one) in half rounds, a second one per CU.  A wide round takes as long as two half rounds of the forward of both branches, and as
+// three at least where a wide tile is four narrow ones.  Wide / narrow (us), 16 heads of 64, one sequence, by wide workgroups:
+//   both branches forward   112 34.9 / 30.6, 144 35.1 / 40.6, 256 43.7 / 48.0, 272 75.7 / 72.2, 384 77.3 / 75.7, 416 79.6 / 87.9, 512 86.2 / 92.2,
+//                           640 119 / 117, 704 123 / 129, 1024 171 / 180
+//   backward of both        112 80.2 / 77.4, 144 88.3 / 95.0, 256 124 / 131, 320 159 / 154, 352 165 / 169, 416 183 / 196, 512 207 / 224, 576 272 / 270
+//   single path             128 29.3 / 26.6, 136 28.7 / 39.3, 256 38.8 / 49.2, 288 63.5 / 61.0, 352 65.1 / 69.2, 448 69.1 / 86.8
+// Short sequences, whose last tile a wide one pads further (batch x tokens, heads of 64): 16 x 300 of 16 38.6 / 40.6, 16 x 513 of 12 54.1 / 34.5,
+// 13 x 1030 of 16 109 / 84, backward 10 x 513 of 16 97 / 107, 16 x 513 of 12 109 / 99; 130 x 40 of 2 13.7 / 9.7.  Below dm = 512 the forward of
+// both has too few steps for its longer start and end (64 x 300 of 4 19.7 / 17.3).
+bool wide_is_faster(long wide, long narrow, bool both, long dm) {
+  const long rounds = (wide + 255) / 256, halves = (narrow + 255) / 256;
+  return wide > 0 && (both ? halves >= 2 * rounds && dm >= 512 : halves >= 3 * rounds);
 }
 
 template <int MODE>
@@ -753,10 +756,12 @@ hipError_t launch_gemm(const GateProj& p, hipStream_t st) {
   const long dm = (long)p.Hq * p.d;
   const int num_ft = (int)(dm / TN);
   const int parts = MODE == GP_BWD_INPUT && p.Y_x[1] ? 2 : 1;  // of the work list
+  const int num_tt = (p.n + TM - 1) / TM;
+  const long total = (long)num_tt * num_ft * p.B * parts;
   const bool both = MODE == GP_FORWARD && p.Y_x[1];
   const int feats = both ? Wide<true>::FEATS : Wide<false>::FEATS;
   const long wide = dm % feats ? 0 : (long)((p.n + XTM - 1) / XTM) * (dm / feats) * p.B * parts;
-  if ((size_t)p.n * p.d * 2 < ((size_t)1 << 32) && wide_is_faster(wide, both)) {  // 32-bit offsets inside a head
+  if ((size_t)p.n * p.d * 2 < ((size_t)1 << 32) && wide_is_faster(wide, total, both, dm)) {  // 32-bit offsets inside a head
     const int num_tt = (p.n + XTM - 1) / XTM, num_ft = (int)(dm / feats);
     const long blocks = xcd_grid_blocks(wide);
     if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
@@ -770,8 +775,6 @@ hipError_t launch_gemm(const GateProj& p, hipStream_t st) {
     }
     return hipGetLastError();
   }
-  const int num_tt = (p.n + TM - 1) / TM;
-  const long total = (long)num_tt * num_ft * p.B * parts;
   const long blocks = xcd_grid_blocks(total);
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
   if (p.d == 64) hipLaunchKernelGGL((gate_proj_fwd_bf16_kernel<64, MODE>), dim3((unsigned)blocks), dim3(GNT), 0, st, p, num_tt, num_ft, total);
