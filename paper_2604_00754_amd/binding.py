@@ -87,6 +87,8 @@ def _load():
     lib.sa_internal_sample_perm.argtypes = [dp, C.c_uint64, C.c_int32, ip, vp, sz, C.c_int, vp]
     lib.sa_internal_fwd_kernel.restype = C.c_char_p
     lib.sa_internal_fwd_kernel.argtypes = [dp, C.c_int, C.c_int]
+    lib.sa_internal_bwd_kernel.restype = C.c_char_p
+    lib.sa_internal_bwd_kernel.argtypes = [dp, C.c_int, C.c_int]
     lib.swa_fwd.restype = C.c_int
     lib.swa_fwd.argtypes = [dp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.gated_sa_swa_fwd.restype = C.c_int
@@ -249,6 +251,11 @@ def sa_bwd(sa, swa, Q, K, V, perm, gate_sa, gate_swa, Y_sa, Y_swa, LSE_sa, LSE_s
 def fwd_kernel(desc, permuted=True, rotated=False) -> str:
     """Name of the kernel that sa_fwd (rotated: sa_fwd_rope) runs on for this descriptor."""
     return _lib.sa_internal_fwd_kernel(C.byref(desc), int(permuted), int(rotated)).decode()
+
+
+def bwd_kernel(desc, permuted=True, rotated=False) -> str:
+    """Name of the kernel that a branch of sa_bwd (rotated: sa_bwd_rope) runs on for this descriptor."""
+    return _lib.sa_internal_bwd_kernel(C.byref(desc), int(permuted), int(rotated)).decode()
 
 
 def raw():

@@ -254,6 +254,14 @@ const char* sa_internal_fwd_kernel(const sa_desc* c, int permuted, int rotated) 
   return sa::fwd_sorted_serves(p) ? "fwd_sorted_bf16_kernel" : "fwd_mfma_bf16_kernel";
 }
 
+const char* sa_internal_bwd_kernel(const sa_desc* c, int permuted, int rotated) {
+  if (validate_desc(c) != SA_OK) return "";
+  if (c->dtype == SA_F32) return "bwd_f32_kernel";
+  Pass p = make_pass(c, nullptr, nullptr, nullptr, permuted ? reinterpret_cast<const int32_t*>(c) : nullptr);  // (never read)
+  p.rope_table = rotated ? reinterpret_cast<const float*>(c) : nullptr;
+  return sa::bwd_strip_serves(p) ? "bwd_strip_bf16_kernel" : "bwd_mfma_bf16_kernel";
+}
+
 namespace {
 sa_status decode_common(const sa_desc* c, const void* q, const void* K, const void* V, const int32_t* lens,
                         int32_t len, void* Y, float* LSE, void* ws, size_t ws_bytes, void* stream);

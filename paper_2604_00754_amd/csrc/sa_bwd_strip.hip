@@ -718,6 +718,43 @@ Strips plan(const Pass& p, int nb) {
   return best;
 }
 
+int key_blocks(const Pass& p) { return p.win.L + p.win.R <= 128 ? 5 : 9; }
+// plain causal SWA: the window already leaves out every later key
+bool masks_positions(const Pass& p) { return p.causal && !(!p.perm && !p.win.circular && p.win.R == 0); }
+
+// Microseconds of a call with either form, as far as the choice needs them: workgroups of 128 slots fill the CUs in small pieces,
+// strips in rounds of 256, each with the intervals of its start, of its windows' reach and of its own slots.  Both lines go through what was
+// measured with both forms on 1608 calls (1 to 2048 heads, 40 to 65535 slots, w = 1 to 257; plain, one-sided, gated and with rotations).
+// Two kernels / strips (us), no rotations, circular, by heads x slots, w = 33 | 129 | 257:
+//   1 x 300     14.5 / 9.1  | 18.1 / 11.6 | 23.4 / 18.3      64 x 512    15.9 / 13.0 | 19.5 / 16.8 | 24.5 / 25.2
+//   12 x 16384  65.9 / 39.9 | 79.1 / 46.8 | 94.1 / 63.8      64 x 8192   161 / 115   | 196 / 122   | 238 / 146
+//   256 x 256   21.8 / 18.6 | 26.9 / 23.0 | 34.0 / 32.5      257 x 256   29.1 / 34.5 | 36.9 / 42.9 | 46.4 / 61.0
+//   320 x 512   58.8 / 54.1 | 68.8 / 64.7 | 83.0 / 89.2      480 x 300   54.2 / 38.6 | 65.9 / 50.3 | 85.1 / 69.2
+//   1024 x 256  83.5 / 69.6 | 98.5 / 87.3 | 119 / 124        2048 x 256  159 / 159   | 192 / 182   | 236 / 256
+// One-sided without a permutation, w = 257: 256 x 256 24.8 / 28.6, 257 x 256 33.6 / 53.7, 192 x 512 48.5 / 40.8; rotations, w = 257: 64 x 512
+// 28.7 / 30.9, 480 x 300 87 / 76.
+bool strips_are_faster(const Pass& p) {
+  const int nb = key_blocks(p);
+  const Strips s = plan(p, nb);
+  const long heads = (long)p.B * p.Hq;
+  const double reach = p.win.L + p.win.R;
+  const double rounds = (double)((heads * s.per_head + kCUs - 1) / kCUs), blocks = (double)s.slots / RB;
+  double strips = 0.92 * (nb + 2 + reach / RB) + (1.2 + 0.0025 * reach) * blocks;
+  if (!masks_positions(p)) strips *= 0.92;
+  if (p.rope_table) strips += 2.5 + 0.65 * blocks;
+  // what 128 neighbouring slots see beyond themselves, on average over a sequence with ends
+  double seen = reach;
+  if (!p.win.circular)
+    for (const double side : {(double)p.win.L, (double)p.win.R}) seen -= side * (side + 128) / (2. * p.n);
+  if (seen < 0) seen = 0;
+  // Workgroups per CU, one that is not whole counting as more than its slots.  A second one on the CUs: 1.4 times; a third, for which the dK/dV
+  // kernel has no place: 1.8.
+  const double fills = (double)heads * ((p.n + 127) / 128 + p.n / 128.) / 2 / kCUs;
+  double two = (reach > 0 ? 14.5 + 0.039 * seen : 11.) * (fills <= 1 ? 1. : (fills <= 2 ? 1.38 : 0.7 + 0.53 * fills));
+  if (p.rope_table) two += 2.5 + 1.8 * fills;
+  return rounds * strips <= two;
+}
+
 template <int NB, int CAUSAL>
 hipError_t launch_t(const Pass& p, hipStream_t st) {
   const Strips s = plan(p, NB);
@@ -739,9 +776,8 @@ hipError_t launch_t(const Pass& p, bool causal, hipStream_t st) {
 
 // Where it can: the registers of a wave hold d = 64, its W waves a window of 257 slots, LDS 16-bit positions; the two-kernel form
 // reads K, V and dO once more after dQ is written, so outputs laid over inputs (dK over K, dV over V) stay with it.
-// Where it is the faster one: everywhere else but in calls of more than one round of workgroups over short sequences, where a
-// workgroup's first and last intervals are most of it (480 heads, 128 slots, w = 64: 25 us in two kernels, 28 us here; 300 slots
-// 59.5 against 43; 12 heads, 512 slots, w = 128 20.7 against 12.5; 64 heads, 8192 slots, w = 256 242 against 159).
+// Where it is the faster one: by strips_are_faster(), and not in calls of more than one round of workgroups over fewer than 256 slots, where a
+// workgroup's first and last intervals are most of it (480 heads, 128 slots, w = 64: 25 us in two kernels, 28 us here).
 bool bwd_strip_serves(const Pass& p) {
   if (p.d != D || p.g != 1 || p.win.L + p.win.R > kMostReach || p.n > 65535 || !(p.scale > 1e-20f)) return false;
   if ((long)p.B * p.Hq > kCUs && p.n < 256) return false;
@@ -753,7 +789,7 @@ bool bwd_strip_serves(const Pass& p) {
       const uintptr_t x = reinterpret_cast<uintptr_t>(o), y = reinterpret_cast<uintptr_t>(in);
       if (in && x < y + bytes && y < x + bytes) return false;
     }
-  return true;
+  return strips_are_faster(p);
 }
 
 hipError_t launch_bwd_strip_bf16(const Pass& p, hipStream_t st) {
@@ -763,9 +799,7 @@ hipError_t launch_bwd_strip_bf16(const Pass& p, hipStream_t st) {
   if (p.win.circular && p.win.L + p.win.R + 1 > p.n) return hipErrorInvalidValue;
   if (!p.dO || !p.lse_in || !p.dQ || !p.dK || !p.dV || !(p.O_rows || p.Dsum)) return hipErrorInvalidValue;
   if ((p.rope_dk && !p.rope_table) || (p.rope_table && p.accumulate)) return hipErrorInvalidValue;
-  // plain causal SWA: the window already leaves out every later key
-  const bool causal = p.causal && !(!p.perm && !p.win.circular && p.win.R == 0);
-  return p.win.L + p.win.R <= 128 ? launch_t<5>(p, causal, st) : launch_t<9>(p, causal, st);
+  return key_blocks(p) == 5 ? launch_t<5>(p, masks_positions(p), st) : launch_t<9>(p, masks_positions(p), st);
 }
 
 }  // namespace sa

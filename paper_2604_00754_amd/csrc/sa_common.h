@@ -139,6 +139,9 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t st);
 extern "C" {
 // the kernel that an ungated forward of this descriptor runs on (with an index tensor; with sa_fwd_rope's rotation)
 const char* sa_internal_fwd_kernel(const sa_desc* desc, int permuted, int rotated);
+// the kernel that a branch of a bf16 backward of this descriptor runs on (sa_bwd, sa_bwd_rope: with an index tensor; with rotations), its
+// outputs apart from its inputs
+const char* sa_internal_bwd_kernel(const sa_desc* desc, int permuted, int rotated);
 // sa_sample_perm with room for `cap` keys of a bucket
 sa_status sa_internal_sample_perm(const sa_desc* desc, uint64_t seed, int32_t layer, int32_t* perm, void* ws, size_t ws_bytes, int cap,
                                   void* stream);

@@ -250,3 +250,35 @@ def test_forward_kernel_that_each_case_of_its_gpu_test_expects():
         assert sa.fwd_kernel(mk(22, 48, 12, n, 128, 562, window=sa.SA_WIN_SYM_LINEAR, perm_B=22), rotated=True) == "fwd_mfma_bf16_kernel"
     assert sa.fwd_kernel(mk(1, 32, 8, 32768, 128, 512, dtype=sa.SA_F32)) == "fwd_f32_kernel"
     assert sa.fwd_kernel(mk(1, 32, 8, 0, 128, 512)) == ""
+
+
+# heads, n, w, window, rotated, kernel; microseconds of a call with (two kernels, strips) on one MI355X
+BWD_ROUTES = [
+    (257, 256, 257, sa.SA_WIN_ONE_SIDED, 0, "mfma"),     # 33.6, 53.7: a second round of workgroups for one head
+    (257, 256, 33, sa.SA_WIN_SYM_CIRCULAR, 0, "mfma"),   # 29.1, 34.5
+    (300, 256, 200, sa.SA_WIN_SYM_CIRCULAR, 1, "mfma"),  # 56.8, 73.5
+    (260, 300, 130, sa.SA_WIN_ONE_SIDED, 0, "mfma"),     # 38.9, 48.7
+    (256, 256, 257, sa.SA_WIN_ONE_SIDED, 0, "mfma"),     # 24.8, 28.6: one round, windows as long as the sequence
+    (2048, 256, 257, sa.SA_WIN_SYM_CIRCULAR, 0, "mfma"),  # 236, 256
+    (480, 128, 64, sa.SA_WIN_SYM_CIRCULAR, 0, "mfma"),   # 25, 28
+    (256, 256, 129, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 26.9, 23.0
+    (480, 300, 257, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 85, 69
+    (512, 256, 65, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 48.0, 35.6
+    (1, 300, 17, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),    # 14.5, 9.1
+    (192, 512, 257, sa.SA_WIN_ONE_SIDED, 0, "strip"),    # 48.5, 40.8
+    (64, 8192, 256, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 238, 146
+    (256, 4096, 256, sa.SA_WIN_SYM_CIRCULAR, 1, "strip"),  # 590, 345
+    (64, 65535, 257, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),
+    (64, 65536, 257, sa.SA_WIN_SYM_CIRCULAR, 0, "mfma"),  # positions no longer fit 16 bits
+    (64, 8192, 258, sa.SA_WIN_ONE_SIDED, 0, "mfma"),     # a window past what the waves of a workgroup hold
+]
+
+
+@pytest.mark.parametrize("case", BWD_ROUTES, ids=lambda c: "-".join(map(str, c)))
+def test_backward_takes_the_faster_kernel(case):
+    heads, n, w, window, rotated, kernel = case
+    desc = sa.make_desc(1, heads, heads, n, 64, w, window)
+    assert sa.bwd_kernel(desc, permuted=window != sa.SA_WIN_ONE_SIDED, rotated=rotated) == f"bwd_{kernel}_bf16_kernel"
+    # grouped heads and d = 128 have the two kernels only
+    for other in (sa.make_desc(1, 2 * heads, heads, n, 64, w, window), sa.make_desc(1, heads, heads, n, 128, w, window)):
+        assert sa.bwd_kernel(other) == "bwd_mfma_bf16_kernel"
