@@ -99,10 +99,15 @@ __device__ __forceinline__ bf16x8 lds_transposed(uint32_t at) {
 }
 
 // What a row adds to all its products enters as one more product: three bf16 values that sum to it to the last bit of fp32,
-// against ones.  (In accumulator order a lane needs 16 rows' values, which would be four 16-byte reads each.)
+// against ones.  (In accumulator order a lane needs 16 rows' values, which would be four 16-byte reads each.)  Eight contraction indices, the
+// lane group's four: S and dP have an operand each, so that an infinite D stays out of S and of dV.
 __device__ __forceinline__ void put_split(char* at, float x) {
   const float h = bf16lo(pack_bf16(x, 0.f)), m = bf16lo(pack_bf16(x - h, 0.f));
   *reinterpret_cast<u32x2*>(at) = u32x2{pack_bf16(h, m), pack_bf16(x - h - m, 0.f)};
+}
+__device__ __forceinline__ f32x16 mfma_row_values(s16x4 rows, s16x4 ones) {
+  const f32x16 zero = {};
+  return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(rows, ones, zero, 0, 0, 0);
 }
 constexpr float kFar = 1e30f;  // an LSE of +infinity (a gate of zero): as far as a finite operand can be
 
@@ -562,9 +567,9 @@ __global__ __launch_bounds__((Cfg<NB, ROWS>::NT)) void bwd_strip_bf16_kernel(con
       kf[kk] = lds_row((row_at + ktile) ^ (32 * kk));
       vf[kk] = lds_row((row_at + vtile) ^ (32 * kk));
     }
-    // ones against the three values of -LSE / scale, of -D, in the operand rows (contraction indices 0..2 and 4..6)
-    const uint32_t one2 = g2 == 0 ? 0x3F803F80u : 0u, one1 = one2 & 0xffffu;
-    const bf16x8 ones_l = __builtin_bit_cast(bf16x8, (u32x4{one2, one1, 0, 0})), ones_d = __builtin_bit_cast(bf16x8, (u32x4{0, 0, one2, one1}));
+    // ones against the three values of -LSE / scale, of -D
+    const uint32_t one2 = g2 == 0 ? 0x3F803F80u : 0u;
+    const s16x4 ones = __builtin_bit_cast(s16x4, (u32x2{one2, one2 & 0xffffu}));
     __builtin_amdgcn_s_setprio(0);
     if (next_interval()) return;
 
@@ -611,10 +616,9 @@ __global__ __launch_bounds__((Cfg<NB, ROWS>::NT)) void bwd_strip_bf16_kernel(con
         const bool inside = dmin >= -L && dmax <= R && (circular || (tb >= 0 && tb + RB <= n && qb + RB <= n));
         f32x16 s, dp;
         {
-          const f32x16 zero = {};
-          const bf16x8 rows = *reinterpret_cast<const bf16x8*>(vals + r_u * 16);
-          s = mfma_bf16(rows, ones_l, zero);   // S / scale starts from -LSE / scale, dP from -D
-          dp = mfma_bf16(rows, ones_d, zero);
+          const u32x4 rows = *reinterpret_cast<const u32x4*>(vals + r_u * 16);
+          s = mfma_row_values(__builtin_bit_cast(s16x4, (u32x2{rows[0], rows[1]})), ones);   // S / scale starts from -LSE / scale, dP from -D
+          dp = mfma_row_values(__builtin_bit_cast(s16x4, (u32x2{rows[2], rows[3]})), ones);
         }
         {
           bf16x8 qa[2], ga[2];

@@ -78,3 +78,35 @@ def test_rows_of_a_closed_gate_and_large_scores(window, causal):
     torch.cuda.synchronize()
     for got, r, what in zip(g, ref, ("dQ", "dK", "dV")):
         grad_close(U.to_np64(got), r, "bf16", what)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_infinite_row_sums_stay_out_of_the_probabilities(d):
+    """An infinity in dO, or an output row that is not finite (D = rowsum(dO o O) then is neither), spoils dQ and dK; the probabilities,
+    and with them what dV gets from finite columns of dO, are those of a finite call.  (d = 128: the two kernels)"""
+    from paper_2604_00754_amd import binding as sa
+    wl, x = U.make_case(1, 2, 2, 300, d, 80, "bf16", 1, 1, 21, grads=True)
+    Q, K, V, dY = (U.to_dev(x[k], "bf16") for k in ("Q", "K", "V", "dY"))
+    perm = torch.from_numpy(x["perm"]).to(U.DEV)
+    desc = U.sa_desc(wl, CIRC, 1)
+    assert sa.bwd_kernel(desc) == ("bwd_strip_bf16_kernel" if d == 64 else "bwd_mfma_bf16_kernel")
+    Y, L = torch.empty_like(Q), torch.empty((1, 2, 300), device=U.DEV)
+    sa.sa_fwd(desc, Q, K, V, perm, Y, L)
+    ws = torch.empty(sa.sa_workspace_bytes(desc, sa.SA_OP_BWD), device=U.DEV, dtype=torch.uint8)
+
+    def dv(Y, dY):
+        g = [torch.empty_like(Q) for _ in range(3)]
+        sa.sa_bwd(desc, None, Q, K, V, perm, None, None, Y, None, L, None, dY, *g, None, None, ws)
+        torch.cuda.synchronize()
+        assert not torch.isfinite(g[0]).all() or torch.isfinite(dY).all() and torch.isfinite(Y).all()
+        return g[2]
+
+    want = dv(Y, dY)
+    assert torch.isfinite(want).all()
+    bad = dY.clone()
+    bad[0, 1, 77, 5] = float("inf")
+    got, rest = dv(Y, bad), [c for c in range(d) if c != 5]
+    assert torch.equal(got[..., rest], want[..., rest])
+    bad = Y.clone()
+    bad[0, 0, 123, 9] = float("-inf")
+    assert torch.equal(dv(bad, dY), want)
