@@ -433,14 +433,17 @@ __global__ __launch_bounds__((Cfg<NB, ROWS>::NT)) void bwd_strip_bf16_kernel(con
     {
       const int lane = fresh(lane0), r8 = lane >> 3, c8 = lane & 7;
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the rows have been read: their tiles take the next key block
-      uint32_t goff[4];
+      // past the last key block nothing is requested (this wave's tiles then hold old rows that no product reads): every request has been waited
+      // for when a wave ends, and one-block strips bring in the blocks they need and no more
+      if (j < nkb) {
+        uint32_t goff[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        goff[v] = key_row(min(j, nkb - 1), 8 * v + r8) + (uint32_t)lane_chunk(lane, v) * 16;
+        for (int v = 0; v < 4; ++v) goff[v] = key_row(j, 8 * v + r8) + (uint32_t)lane_chunk(lane, v) * 16;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        load_to_lds_16(Kh, goff[v], lds0 + ktile + v * 1024);
-        load_to_lds_16(Vh, goff[v], lds0 + vtile + v * 1024);
+        for (int v = 0; v < 4; ++v) {
+          load_to_lds_16(Kh, goff[v], lds0 + ktile + v * 1024);
+          load_to_lds_16(Vh, goff[v], lds0 + vtile + v * 1024);
+        }
       }
       if (scalars_later) request_scalars();
       if (ROWS == ROWS_TURN && want_q) {
