@@ -115,6 +115,9 @@ constexpr float kFar = 1e30f;  // an LSE of +infinity (a gate of zero): as far a
 __device__ __forceinline__ u32x4 row_at_offset(const void* base, uint32_t off) {
   return *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(base) + off);
 }
+__device__ __forceinline__ u32x4 table_at_offset(const void* base, uint32_t off) {
+  return *reinterpret_cast<const table_u32x4*>(reinterpret_cast<const char*>(base) + off);
+}
 __device__ __forceinline__ void store_at_offset(void* base, uint32_t off, u32x4 v) {
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(reinterpret_cast<char*>(base) + off));
 }
@@ -283,7 +286,7 @@ __global__ __launch_bounds__((Cfg<NB, ROWS>::NT)) void bwd_strip_bf16_kernel(con
   bf16_t* const dQh = reinterpret_cast<bf16_t*>(p.dQ) + row0 * D;
   bf16_t* const dKh = reinterpret_cast<bf16_t*>(p.dK) + row0 * D;
   bf16_t* const dVh = reinterpret_cast<bf16_t*>(p.dV) + row0 * D;
-  const float4* const rope = reinterpret_cast<const float4*>(p.rope_table);  // two pairs (cos, sin) each, D / 4 of them a row
+  const float* const rope = p.rope_table;  // (cos, sin) of D / 2 pairs a row
 
   __syncthreads();
   for (int w = 0; w < wave; ++w)
@@ -311,7 +314,7 @@ __global__ __launch_bounds__((Cfg<NB, ROWS>::NT)) void bwd_strip_bf16_kernel(con
           aux[4 + v] = row_at_offset(dVh, row + c);
         } else {
 #pragma unroll
-          for (int h = 0; h < 2; ++h) aux[2 * v + h] = row_at_offset(rope, 2 * row + (lane & 7) * 32 + h * 16);
+          for (int h = 0; h < 2; ++h) aux[2 * v + h] = table_at_offset(rope, 2 * row + (lane & 7) * 32 + h * 16);
         }
       }
     }
@@ -425,7 +428,7 @@ __global__ __launch_bounds__((Cfg<NB, ROWS>::NT)) void bwd_strip_bf16_kernel(con
         if (ROWS == ROWS_ADD) auxq[v] = row_at_offset(dQh, row + c8 * 16);
         else {
 #pragma unroll
-          for (int h = 0; h < 2; ++h) auxq[2 * v + h] = row_at_offset(rope, 2 * row + c8 * 32 + h * 16);
+          for (int h = 0; h < 2; ++h) auxq[2 * v + h] = table_at_offset(rope, 2 * row + c8 * 32 + h * 16);
         }
       }
     }
@@ -451,7 +454,7 @@ __global__ __launch_bounds__((Cfg<NB, ROWS>::NT)) void bwd_strip_bf16_kernel(con
         for (int v = 0; v < 4; ++v) {
           const uint32_t row = query_row(iq, 8 * v + r8);
 #pragma unroll
-          for (int h = 0; h < 2; ++h) tq[2 * v + h] = row_at_offset(rope, 2 * row + c8 * 32 + h * 16);
+          for (int h = 0; h < 2; ++h) tq[2 * v + h] = table_at_offset(rope, 2 * row + c8 * 32 + h * 16);
         }
       }
     }

@@ -255,7 +255,7 @@ __global__ __launch_bounds__(NT, 3) void fwd_sorted_bf16_kernel(const Pass p, co
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = own_pos[min(8 * wave + 2 * i + (ln >> 5), own - 1)];
-      angles[i] = *reinterpret_cast<const u32x4*>(p.rope_table + (size_t)row * D + 4 * (ln & 31));
+      angles[i] = *reinterpret_cast<const table_u32x4*>(p.rope_table + (size_t)row * D + 4 * (ln & 31));
     }
   }
   load_tile(0, 0);
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(NT, 3) void fwd_sorted_bf16_kernel(const Pass p, co
 #pragma unroll
     for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(table + (8 * wave + 2 * i + (ln >> 5)) * TABLE_STR + 4 * (ln & 31)) = angles[i];
     __syncthreads();
-    rope_row_fragments<D>(qf, reinterpret_cast<const float2*>(table + (ln & 31) * TABLE_STR), ln >> 5, p.rope_interleaved);
+    rope_row_fragments<D, f32x4>(qf, reinterpret_cast<const float2*>(table + (ln & 31) * TABLE_STR), ln >> 5, p.rope_interleaved);
   }
 
   float m_ref = 0.f, l_run = 0.f;

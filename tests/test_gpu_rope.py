@@ -255,3 +255,42 @@ def test_bwd_rope_rejects_unsupported():
         sa.sa_bwd_rope(sa.make_desc(1, 1, 1, 8, 64, 4, dtype=sa.SA_F32), xf, xf, xf, None, t, xf, L, xf,
                        *[torch.empty_like(xf) for _ in range(3)], ws)
     assert e.value.status == sa.SA_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("interleaved", [0, 1])
+@pytest.mark.parametrize("B,Hq,Hkv,n,d,w", [(2, 3, 3, 200, 64, 40), (1, 4, 2, 200, 64, 40), (1, 4, 2, 200, 128, 40), (9, 12, 3, 460, 128, 900)])
+def test_tables_aligned_to_one_pair(B, Hq, Hkv, n, d, w, interleaved):
+    """A table is (cos, sin) pairs of 8 bytes and need not be aligned beyond that: the same bits from a table 8 bytes past a 16-byte
+    boundary in sa_rope, both forwards (the last case is the sorted one) and both backwards (the first is the one-pass form)."""
+    from paper_2604_00754_amd import binding as sa
+    gen = torch.Generator(device=U.DEV)
+    gen.manual_seed(n + d)
+    normal = lambda *s: torch.randn(s, device=U.DEV, generator=gen)
+    Q32, K32, V, dY = normal(B, Hq, n, d), normal(B, Hkv, n, d), normal(B, Hkv, n, d).bfloat16(), normal(B, Hq, n, d).bfloat16()
+    Q, K = Q32.bfloat16(), K32.bfloat16()
+    perm = torch.randperm(n, device=U.DEV, generator=gen).to(torch.int32).view(1, 1, n).contiguous()
+    desc, desc32 = sa.make_desc(B, Hq, Hkv, n, d, w), sa.make_desc(B, Hq, Hkv, n, d, w, dtype=sa.SA_F32)
+    if n == 460:
+        assert sa.fwd_kernel(desc, rotated=True) == "fwd_sorted_bf16_kernel"
+    if n == 200:
+        assert (sa.bwd_kernel(desc, rotated=True) == "bwd_strip_bf16_kernel") == (Hq == Hkv)
+    table = gpu_table(n, d, 1e4, 0)
+    store = torch.empty(n * d + 2, device=U.DEV)
+    shifted = store[2:].view(n, d // 2, 2)
+    shifted.copy_(table)
+    assert table.data_ptr() % 16 == 0 and shifted.data_ptr() % 16 == 8
+
+    def everything(table):
+        out = [torch.empty_like(Q32), torch.empty_like(K32), torch.empty_like(K), torch.empty_like(Q), torch.empty((B, Hq, n), device=U.DEV)]
+        Kr, Y, L = out[2:]
+        sa.sa_rope(desc32, Q32, K32, table, out[0], out[1], interleaved=interleaved)
+        sa.sa_rope(desc, None, K, table, None, Kr, interleaved=interleaved)
+        sa.sa_fwd_rope(desc, Q, Kr, V, perm, table, Y, L, interleaved=interleaved)
+        grads = [torch.empty_like(Q), torch.empty_like(K), torch.empty_like(K)]
+        ws = torch.empty(sa.sa_workspace_bytes(desc, sa.SA_OP_BWD_ROPE), device=U.DEV, dtype=torch.uint8)
+        sa.sa_bwd_rope(desc, Q, Kr, V, perm, table, Y, L, dY, *grads, ws, interleaved=interleaved, dk_unrotated=1)
+        torch.cuda.synchronize()
+        return out + grads
+
+    for a, b in zip(everything(table), everything(shifted)):
+        assert torch.equal(a, b)
