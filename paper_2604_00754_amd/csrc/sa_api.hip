@@ -262,6 +262,12 @@ const char* sa_internal_bwd_kernel(const sa_desc* c, int permuted, int rotated) 
   return sa::bwd_strip_serves(p) ? "bwd_strip_bf16_kernel" : "bwd_mfma_bf16_kernel";
 }
 
+int sa_internal_gate_dw_pieces(const sa_desc* c, int dual) {
+  if (validate_desc(c) != SA_OK) return 0;
+  const long tiles = (long)c->Hq * c->d / 128;
+  return tiles < 1 ? 0 : (int)sa::gate_proj_dw_pieces(tiles * tiles * (dual ? 2 : 1), c->B, c->n);
+}
+
 namespace {
 sa_status decode_common(const sa_desc* c, const void* q, const void* K, const void* V, const int32_t* lens,
                         int32_t len, void* Y, float* LSE, void* ws, size_t ws_bytes, void* stream);

@@ -603,10 +603,16 @@ __global__ __launch_bounds__(256) void gate_bwd_setup_kernel(const GateBwd p, co
 // and with two: n = 1100 51.6 / 44.3 us, 2048 65.4 / 48.3, 4096 78.5 / 64.6; with two heads, one tile, n = 8192 28.6 / 56.4.)
 // Longer calls add in no fixed order: equal pieces, as many as fill the chip once, with two workgroups per CU where a piece then has WLONG
 // tokens and one where not (whole backward, 512 / 256 workgroups, us: 16 heads of 64, B4 n = 8192 409 / 431, B1 n = 16384 203 / 217,
-// 9000 145.5 / 144.9, B3 n = 2048 104 / 100; 8 heads, 13 x 476 64 / 55), each of WLEAST at least (3 x 512 of 4 heads 23.8, 256 workgroups 29.3).
-// Half as many pieces again (768 workgroups) 5 % slower and more.  Pieces that end with their batch at 4096 tokens took 13 x 613
+// 9000 145.5 / 144.9, B3 n = 2048 104 / 100; 8 heads, 13 x 476 64 / 55), each of WLEAST at least (3 x 512 of 4 heads 23.8, 256 workgroups 29.3; 13 x 613
+// of two heads in pieces of 256 tokens 21.2, of 88 24.7), less where that leaves few workgroups (40 x 31 tokens of two heads in 4 pieces 22.3, in 19
+// 20.1, in 38 20.3; of four heads in 4 24.6, in 9 22.7).
+// Where tiles do not divide the places, one round stays partly empty and two to four rounds of shorter pieces are taken if they are filled better
+// and a piece keeps WMANY tokens (tiles x tokens, pieces of one round / now, us: 288 x 32768 842 / 800, 338 x 32768 1110 / 1030, 200 x 65536 1202 / 1165, 324 x
+// 32768 897 / 832, 144 x 65536 820 / 786, 288 x 8192 237 / 232; with 2048 tokens a piece 338 x 6144 213 / 221; more tiles than places, 648 x 32768 in one and
+// in three 1710 / 1701, x 6144 340 / 351).
+// Half as many pieces again (768 workgroups) 5 % slower and more where the round is full.  Pieces that end with their batch at 4096 tokens took 13 x 613
 // tokens of 16 heads 190 us, now 139; 8 x 1024 of 12 heads 105, now 90; 16 x 4096 of 16 heads 840, now 798.
-constexpr int WCHUNK = 4096, WLONG = 2048, WLEAST = 256;
+constexpr int WCHUNK = 4096, WLONG = 2048, WMANY = 2560, WLEAST = 256;
 constexpr long WTARGET = 256;
 constexpr int WSTEP = 32;
 constexpr int WSTAGES = 4;
@@ -647,20 +653,23 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
     return (uint32_t)(((size_t)(f / D) * n * D + f % D) * 2);
   };
   const uint32_t zfeat = feature_offset(ot * 128 + ld_feat), yfeat = feature_offset(kt * 128 + ld_feat);
-  int rb = first / steps_b, rt = first % steps_b;  // batch and step of the next request
-  auto request_step = [&](int st) {  // past the call's last step: its rows again, never used
+  int rb = first / steps_b, rrow = first % steps_b * WSTEP;  // batch and first row of the next request
+  const size_t batch = (size_t)H * n * D;
+  const bf16_t *zb = dz + rb * batch, *yb = Yx + rb * batch;
+  auto request_step = [&](int st) {  // past the call's last step: its last row again, never used
     const int buf = st & (WSTAGES - 1);
-    const bf16_t *zb = dz + (size_t)rb * H * n * D, *yb = Yx + (size_t)rb * H * n * D;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int token = min(rt * WSTEP + 16 * j + ld_row, n - 1);
+      const int token = min(rrow + 16 * j + ld_row, n - 1);
       const uint32_t trow = (uint32_t)token * (uint32_t)(D * 2);
       const uint32_t dst = lds0 + buf * WSTAGE_BYTES + (16 * j + wave * 4) * 256;
       load_to_lds_16(zb, zfeat + trow, dst);
       load_to_lds_16(yb, yfeat + trow, dst + WTILE_BYTES);
     }
-    if (rt + 1 < steps_b) ++rt;
-    else if (rb + 1 < B) { rt = 0; ++rb; }
+    rrow += WSTEP;
+  };
+  auto next_batch = [&]() {
+    if (rrow >= n && rb + 1 < B) { rrow = 0; ++rb; zb += batch; yb += batch; }
   };
 
   int troff[4][2];
@@ -674,10 +683,15 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[oi][ki][i] = 0.f;
 
-  request_step(0);
-  request_step(1);
-  request_step(2);
-  int ct = first % steps_b;  // step of the batch
+  for (int st = 0; st < 3; ++st) {
+    request_step(st);
+    next_batch();
+  }
+  // The steps at which something happens beside the products: the request that ends its batch, and a batch's ragged last step.  (Looked for at
+  // every step, the calls of few tiles, whose workgroups have a CU each, took 4 % longer: n = 8192 of two heads 53.2 -> 55.5 us.)
+  constexpr int NEVER = 0x7fffffff;
+  int ends_at = rb + 1 < B ? (n - 1 - rrow) / WSTEP : NEVER, ragged_at = n % WSTEP ? steps_b - 1 - first % steps_b : NEVER;
+  int event = min(ends_at, ragged_at);
   for (int st = 0; st < nsteps; ++st) {
     const int buf = st & (WSTAGES - 1);
     // all but the two youngest steps of this wave have landed; after the barrier step st is visible and
@@ -687,14 +701,22 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
     request_step(st + 3);
     bf16_t* Zt = reinterpret_cast<bf16_t*>(smem + buf * WSTAGE_BYTES);
     const bf16_t* Yt = reinterpret_cast<const bf16_t*>(smem + buf * WSTAGE_BYTES + WTILE_BYTES);
-    if ((ct + 1) * WSTEP > n) {  // a batch's ragged last step: tokens past the end contribute zeros
-      const int row = tid >> 3;
-      if (ct * WSTEP + row >= n) {
-        u32x4* r = reinterpret_cast<u32x4*>(Zt + row * 128 + (tid & 7) * 16);
-        r[0] = u32x4{0u, 0u, 0u, 0u};
-        r[1] = u32x4{0u, 0u, 0u, 0u};
+    if (__builtin_expect(st == event, 0)) {
+      if (st == ends_at) {
+        next_batch();
+        ends_at = rb + 1 < B ? ends_at + steps_b : NEVER;
       }
-      __syncthreads();
+      if (st == ragged_at) {  // tokens past the end contribute zeros
+        const int row = tid >> 3;
+        if (row >= n % WSTEP) {
+          u32x4* r = reinterpret_cast<u32x4*>(Zt + row * 128 + (tid & 7) * 16);
+          r[0] = u32x4{0u, 0u, 0u, 0u};
+          r[1] = u32x4{0u, 0u, 0u, 0u};
+        }
+        ragged_at += steps_b;
+        __syncthreads();
+      }
+      event = min(ends_at, ragged_at);
     }
 #pragma unroll
     for (int ks = 0; ks < WSTEP / 16; ++ks) {
@@ -708,7 +730,6 @@ __global__ __launch_bounds__(GNT, 2) void gate_dw_bf16_kernel(const GateBwd p, c
 #pragma unroll
         for (int ki = 0; ki < 2; ++ki) acc[oi][ki] = mfma_bf16(fa[oi], fb[ki], acc[oi][ki]);
     }
-    ct = ct + 1 < steps_b ? ct + 1 : 0;
   }
   wait_all_loads();  // the surplus steps requested near the end
   // accumulator 4q + x of lane (g2, c32): row o = 64wo + 32oi + 8q + 4g2 + x, column k = 64wk + 32ki + c32
@@ -811,6 +832,27 @@ size_t gate_proj_bwd_workspace_bytes(int B, int Hq, int n, int d, bool dual) {
   return (dual ? 2 : 1) * ((per_branch + 255) / 256 * 256);
 }
 
+// Pieces that the tokens of dW are cut into (see gate_dw_bf16_kernel): tiles = those of 128 x 128 of all branches.
+long gate_proj_dw_pieces(long tiles, int B, int n) {
+  const long tokens = (long)n * B, chunks = (long)((n + WCHUNK - 1) / WCHUNK) * B, places = 2 * WTARGET;
+  if (chunks <= 2) return B == 1 && n > WLEAST && tiles * chunks < places ? 2 : chunks;
+  long pieces = places / tiles;
+  if (pieces * WLONG > tokens) pieces = WTARGET / tiles;
+  if (pieces * WLEAST > tokens) {
+    const long few = 32 / tiles < 16 ? 32 / tiles : 16, few_short = tokens / 64 < few ? tokens / 64 : few;
+    pieces = tokens / WLEAST > few_short ? tokens / WLEAST : few_short;
+  }
+  if (pieces < 1) pieces = 1;
+  // where whole tiles leave places of the one round empty: the rounds, four at most, that are filled best
+  long rounds = 1;
+  for (long r = 2; r <= 4 && tiles <= places; ++r) {
+    const long more = r * places / tiles;
+    if (more * WMANY > tokens) break;
+    if (more * rounds * 100 > pieces * r * 103) { pieces = more; rounds = r; }
+  }
+  return pieces;
+}
+
 // `branches` branches at once: dz, W^T, dy_x = dY * g_x + dz W_x, dW_x = dz^T y_x.
 static hipError_t gate_proj_bwd_branches(int branches, int B, int Hq, int n, int d, const void* const* Y_x, const void* const* W_x,
                                          const void* const* G_x, const void* dY, void* const* dY_x, void* const* dW_x, char* ws,
@@ -844,18 +886,9 @@ static hipError_t gate_proj_bwd_branches(int branches, int B, int Hq, int n, int
   e = launch_gemm<GP_BWD_INPUT>(g, st);
   if (e != hipSuccess) return e;
   const int num_ft = (int)(dm / 128);
-  const long tiles = (long)num_ft * num_ft * branches, steps = (long)((n + WSTEP - 1) / WSTEP) * B, tokens = (long)n * B;
+  const long tiles = (long)num_ft * num_ft * branches, steps = (long)((n + WSTEP - 1) / WSTEP) * B;
   if (steps > 0x7fffffffL) return hipErrorNotSupported;
-  long pieces;
-  if ((long)((n + WCHUNK - 1) / WCHUNK) * B <= 2) {
-    pieces = (n + WCHUNK - 1) / WCHUNK * B;
-    if (B == 1 && n > WLEAST && tiles * pieces < 2 * WTARGET) pieces = 2;
-  } else {
-    pieces = 2 * WTARGET / tiles;
-    if (pieces * WLONG > tokens) pieces = WTARGET / tiles;
-    if (pieces * WLEAST > tokens) pieces = tokens / WLEAST;
-    if (pieces < 1) pieces = 1;
-  }
+  long pieces = gate_proj_dw_pieces(tiles, B, n);
   const int piece_steps = (int)((steps + pieces - 1) / pieces);
   pieces = (steps + piece_steps - 1) / piece_steps;
   const long total = tiles * pieces, blocks = xcd_grid_blocks(total);

@@ -282,3 +282,19 @@ def test_backward_takes_the_faster_kernel(case):
     # grouped heads and d = 128 have the two kernels only
     for other in (sa.make_desc(1, 2 * heads, heads, n, 64, w, window), sa.make_desc(1, heads, heads, n, 128, w, window)):
         assert sa.bwd_kernel(other) == "bwd_mfma_bf16_kernel"
+
+
+@pytest.mark.parametrize("heads", [2, 8, 12, 16, 20, 24, 26, 28, 30, 32, 36, 48, 64])
+@pytest.mark.parametrize("B,n", [(1, 200), (1, 8192), (2, 4096), (3, 2048), (4, 8192), (16, 4096), (13, 613)])
+@pytest.mark.parametrize("dual", [0, 1])
+def test_weight_gradient_pieces(heads, B, n, dual):
+    """Two pieces at most where the additions to dW keep their order; long calls leave few of the places of their rounds of workgroups
+    (two to a CU) empty, in pieces that stay long."""
+    tiles, pieces = (heads * 64 // 128) ** 2 * (1 + dual), sa.gate_dw_pieces(sa.make_desc(B, heads, heads, n, 64, 4), dual)
+    if (n + 4095) // 4096 * B <= 2:
+        assert pieces <= 2
+    else:
+        assert 1 <= pieces <= max(1, B * n // 256, min(16, 32 // tiles, B * n // 64))
+        if B * n >= 32768 and B * n * tiles >= 2048 * 512 and tiles <= 512:
+            assert B * n // pieces >= 2048
+            assert tiles * pieces >= 0.87 * 512 * -(-tiles * pieces // 512)
