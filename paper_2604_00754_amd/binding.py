@@ -89,6 +89,8 @@ def _load():
     lib.sa_internal_fwd_kernel.argtypes = [dp, C.c_int, C.c_int]
     lib.sa_internal_bwd_kernel.restype = C.c_char_p
     lib.sa_internal_bwd_kernel.argtypes = [dp, C.c_int, C.c_int]
+    lib.sa_internal_gate_kernel.restype = C.c_char_p
+    lib.sa_internal_gate_kernel.argtypes = [dp, C.c_int, C.c_int]
     lib.sa_internal_gate_dw_pieces.restype = C.c_int
     lib.sa_internal_gate_dw_pieces.argtypes = [dp, C.c_int]
     lib.swa_fwd.restype = C.c_int
@@ -258,6 +260,11 @@ def fwd_kernel(desc, permuted=True, rotated=False) -> str:
 def bwd_kernel(desc, permuted=True, rotated=False) -> str:
     """Name of the kernel that a branch of sa_bwd (rotated: sa_bwd_rope) runs on for this descriptor."""
     return _lib.sa_internal_bwd_kernel(C.byref(desc), int(permuted), int(rotated)).decode()
+
+
+def gate_kernel(desc, backward=False, dual=True) -> str:
+    """Name of the kernel of the products of sa_gate_proj_fwd (backward: of the input gradients of sa_gate_proj_bwd)."""
+    return _lib.sa_internal_gate_kernel(C.byref(desc), int(backward), int(dual)).decode()
 
 
 def gate_dw_pieces(desc, dual=True) -> int:

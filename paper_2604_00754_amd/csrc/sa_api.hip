@@ -262,6 +262,11 @@ const char* sa_internal_bwd_kernel(const sa_desc* c, int permuted, int rotated) 
   return sa::bwd_strip_serves(p) ? "bwd_strip_bf16_kernel" : "bwd_mfma_bf16_kernel";
 }
 
+const char* sa_internal_gate_kernel(const sa_desc* c, int backward, int dual) {
+  if (validate_desc(c) != SA_OK || (long)c->Hq * c->d % 128 != 0) return "";
+  return sa::gate_proj_wide_serves(c->B, c->Hq, c->n, c->d, backward, dual) ? "gate_proj_wide_bf16_kernel" : "gate_proj_fwd_bf16_kernel";
+}
+
 int sa_internal_gate_dw_pieces(const sa_desc* c, int dual) {
   if (validate_desc(c) != SA_OK) return 0;
   const long tiles = (long)c->Hq * c->d / 128;

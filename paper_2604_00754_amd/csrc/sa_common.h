@@ -82,6 +82,7 @@ hipError_t launch_gate_proj_fwd_bf16(int B, int Hq, int n, int d, const void* Y_
                                      const void* W_sa, const void* W_swa, void* Y, void* G_sa, void* G_swa,
                                      hipStream_t st);
 
+bool gate_proj_wide_serves(int B, int Hq, int n, int d, bool backward, bool dual);  // the tiles of the forward, of the backward's input gradients
 long gate_proj_dw_pieces(long tiles, int B, int n);  // how sa_gate_proj_bwd cuts the tokens of dW
 size_t gate_proj_bwd_workspace_bytes(int B, int Hq, int n, int d, bool dual);
 hipError_t launch_gate_proj_bwd_bf16(int B, int Hq, int n, int d, const void* Y_sa, const void* Y_swa,
@@ -143,6 +144,8 @@ const char* sa_internal_fwd_kernel(const sa_desc* desc, int permuted, int rotate
 // the kernel that a branch of a bf16 backward of this descriptor runs on (sa_bwd, sa_bwd_rope: with an index tensor; with rotations), its
 // outputs apart from its inputs
 const char* sa_internal_bwd_kernel(const sa_desc* desc, int permuted, int rotated);
+// the kernel of the products of sa_gate_proj_fwd (backward: of the input gradients of sa_gate_proj_bwd)
+const char* sa_internal_gate_kernel(const sa_desc* desc, int backward, int dual);
 // pieces of the tokens that add up to a 128 x 128 tile of dW in sa_gate_proj_bwd
 int sa_internal_gate_dw_pieces(const sa_desc* desc, int dual);
 // sa_sample_perm with room for `cap` keys of a bucket

@@ -765,41 +765,51 @@ __global__ __launch_bounds__(256) void gate_dw_round_kernel(const GateBwd p, con
 //   backward of both        112 80.2 / 77.4, 144 88.3 / 95.0, 256 124 / 131, 320 159 / 154, 352 165 / 169, 416 183 / 196, 512 207 / 224, 576 272 / 270
 //   single path             128 29.3 / 26.6, 136 28.7 / 39.3, 256 38.8 / 49.2, 288 63.5 / 61.0, 352 65.1 / 69.2, 448 69.1 / 86.8
 // Short sequences, whose last tile a wide one pads further (batch x tokens, heads of 64): 16 x 300 of 16 38.6 / 40.6, 16 x 513 of 12 54.1 / 34.5,
-// 13 x 1030 of 16 109 / 84, backward 10 x 513 of 16 97 / 107, 16 x 513 of 12 109 / 99; 130 x 40 of 2 13.7 / 9.7.  Below dm = 512 the forward of
-// both has too few steps for its longer start and end (64 x 300 of 4 19.7 / 17.3).
+// 13 x 1030 of 16 109 / 84, backward 10 x 513 of 16 97 / 107, 16 x 513 of 12 109 / 99; 130 x 40 of 2 13.7 / 9.7.
+// A wide tile's longer start and end need steps to pay for them.  Below dm = 1024 the forward of both branches gains only where the second
+// half round of narrow ones is mostly empty (dm = 512, by wide workgroups: 192 35.2 / 38.4, 256 29.8 / 29.3, 512 60.1 / 55.5, 1024 115 / 106; 640:
+// 160 .89 of it, 240 1.01, 480 63.3 / 62.1, 1280 165 / 155; 768: 192 .90, 768 112 / 108), the others only in one round or with half a round to
+// spare (single path, dm = 512: 192 23.3 / 24.5, 256 28.1 / 29.9, 384 46.3 / 42.4; 768: 384 56.6 / 55.6, 576 89.6 / 82.2, 768 95.7 / 115); below dm = 512
+// none (dm = 256, backward of both 256 74.8 / 71.9, 384 102 / 94.5, single path 192 19.0 / 17.3).
 bool wide_is_faster(long wide, long narrow, bool both, long dm) {
   const long rounds = (wide + 255) / 256, halves = (narrow + 255) / 256;
-  return wide > 0 && (both ? halves >= 2 * rounds && dm >= 512 : halves >= 3 * rounds);
+  if (wide < 1 || dm < 512) return false;
+  if (both) return dm >= 1024 ? halves >= 2 * rounds : halves == 2 && wide <= 218;
+  return dm >= 1024 || rounds == 1 ? halves >= 3 * rounds : 2 * halves >= 7 * rounds;
+}
+
+struct Tiles {
+  int wide, num_tt, num_ft;  // token tiles, feature tiles
+  long total;
+};
+Tiles gate_tiles(int B, int Hq, int n, int d, bool backward, bool dual) {
+  const long dm = (long)Hq * d;
+  const int parts = backward && dual ? 2 : 1;  // of the work list
+  const bool both = !backward && dual;
+  const int feats = both ? Wide<true>::FEATS : Wide<false>::FEATS;
+  const int num_tt = (n + TM - 1) / TM, wide_tt = (n + XTM - 1) / XTM;
+  const long total = (long)num_tt * (dm / TN) * B * parts, wide = dm % feats ? 0 : (long)wide_tt * (dm / feats) * B * parts;
+  if ((size_t)n * d * 2 < ((size_t)1 << 32) && wide_is_faster(wide, total, both, dm)) return {1, wide_tt, (int)(dm / feats), wide};  // 32-bit offsets inside a head
+  return {0, num_tt, (int)(dm / TN), total};
 }
 
 template <int MODE>
 hipError_t launch_gemm(const GateProj& p, hipStream_t st) {
-  const long dm = (long)p.Hq * p.d;
-  const int num_ft = (int)(dm / TN);
-  const int parts = MODE == GP_BWD_INPUT && p.Y_x[1] ? 2 : 1;  // of the work list
-  const int num_tt = (p.n + TM - 1) / TM;
-  const long total = (long)num_tt * num_ft * p.B * parts;
-  const bool both = MODE == GP_FORWARD && p.Y_x[1];
-  const int feats = both ? Wide<true>::FEATS : Wide<false>::FEATS;
-  const long wide = dm % feats ? 0 : (long)((p.n + XTM - 1) / XTM) * (dm / feats) * p.B * parts;
-  if ((size_t)p.n * p.d * 2 < ((size_t)1 << 32) && wide_is_faster(wide, total, both, dm)) {  // 32-bit offsets inside a head
-    const int num_tt = (p.n + XTM - 1) / XTM, num_ft = (int)(dm / feats);
-    const long blocks = xcd_grid_blocks(wide);
-    if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks);
-    if (both) {
-      if (p.d == 64) hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<64, GP_FORWARD, true>), grid, dim3(XNT), 0, st, p, num_tt, num_ft, wide);
-      else hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<128, GP_FORWARD, true>), grid, dim3(XNT), 0, st, p, num_tt, num_ft, wide);
-    } else {
-      if (p.d == 64) hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<64, MODE, false>), grid, dim3(XNT), 0, st, p, num_tt, num_ft, wide);
-      else hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<128, MODE, false>), grid, dim3(XNT), 0, st, p, num_tt, num_ft, wide);
-    }
-    return hipGetLastError();
-  }
-  const long blocks = xcd_grid_blocks(total);
+  const bool dual = p.Y_x[1] != nullptr, both = MODE == GP_FORWARD && dual;
+  const Tiles t = gate_tiles(p.B, p.Hq, p.n, p.d, MODE == GP_BWD_INPUT, dual);
+  const long blocks = xcd_grid_blocks(t.total);
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  if (p.d == 64) hipLaunchKernelGGL((gate_proj_fwd_bf16_kernel<64, MODE>), dim3((unsigned)blocks), dim3(GNT), 0, st, p, num_tt, num_ft, total);
-  else hipLaunchKernelGGL((gate_proj_fwd_bf16_kernel<128, MODE>), dim3((unsigned)blocks), dim3(GNT), 0, st, p, num_tt, num_ft, total);
+  const dim3 grid((unsigned)blocks), block(t.wide ? XNT : GNT);
+  if (t.wide && both) {
+    if (p.d == 64) hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<64, GP_FORWARD, true>), grid, block, 0, st, p, t.num_tt, t.num_ft, t.total);
+    else hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<128, GP_FORWARD, true>), grid, block, 0, st, p, t.num_tt, t.num_ft, t.total);
+  } else if (t.wide) {
+    if (p.d == 64) hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<64, MODE, false>), grid, block, 0, st, p, t.num_tt, t.num_ft, t.total);
+    else hipLaunchKernelGGL((gate_proj_wide_bf16_kernel<128, MODE, false>), grid, block, 0, st, p, t.num_tt, t.num_ft, t.total);
+  } else {
+    if (p.d == 64) hipLaunchKernelGGL((gate_proj_fwd_bf16_kernel<64, MODE>), grid, block, 0, st, p, t.num_tt, t.num_ft, t.total);
+    else hipLaunchKernelGGL((gate_proj_fwd_bf16_kernel<128, MODE>), grid, block, 0, st, p, t.num_tt, t.num_ft, t.total);
+  }
   return hipGetLastError();
 }
 
@@ -809,6 +819,8 @@ unsigned capped_blocks(size_t items, size_t per_block) {
 }
 
 }  // namespace
+
+bool gate_proj_wide_serves(int B, int Hq, int n, int d, bool backward, bool dual) { return gate_tiles(B, Hq, n, d, backward, dual).wide; }
 
 hipError_t launch_gate_proj_fwd_bf16(int B, int Hq, int n, int d, const void* Y_sa, const void* Y_swa, const void* W_sa,
                                      const void* W_swa, void* Y, void* G_sa, void* G_swa, hipStream_t st) {

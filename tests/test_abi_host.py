@@ -298,3 +298,30 @@ def test_weight_gradient_pieces(heads, B, n, dual):
         if B * n >= 32768 and B * n * tiles >= 2048 * 512 and tiles <= 512:
             assert B * n // pieces >= 2048
             assert tiles * pieces >= 0.87 * 512 * -(-tiles * pieces // 512)
+
+
+# B, heads of 64, n, backward, dual, wide; microseconds of a call (the whole one, backward) with (narrow, wide) tiles on one MI355X
+GATE_ROUTES = [
+    (4, 8, 8192, 0, 1, False),   # 55.5, 60.1
+    (16, 8, 4096, 0, 1, False),  # 106, 115
+    (8, 10, 8192, 0, 1, False),  # 155, 165
+    (6, 8, 8192, 0, 0, False),   # 42.4, 46.3: one round and a half
+    (6, 12, 8192, 0, 0, False),  # 82.2, 89.6
+    (4, 4, 8192, 1, 1, False),   # 71.9, 74.8
+    (6, 4, 8192, 0, 0, False),   # 17.3, 19.0
+    (3, 8, 4096, 0, 1, True),    # 38.4, 35.2
+    (4, 8, 8192, 0, 0, True),    # 29.9, 28.1
+    (8, 12, 8192, 0, 0, True),   # 115, 95.7
+    (4, 16, 8192, 0, 1, True),   # 180, 171
+    (4, 16, 8192, 1, 1, True),   # 436, 403
+    (6, 16, 8192, 0, 0, True),   # 141, 113
+    (1, 32, 4096, 1, 1, True),   # 207, 186
+    (16, 12, 513, 0, 1, False),  # 34.5, 54.1: a wide tile pads further
+]
+
+
+@pytest.mark.parametrize("case", GATE_ROUTES, ids=lambda c: "-".join(map(str, c)))
+def test_gate_products_take_the_faster_tiles(case):
+    B, heads, n, backward, dual, wide = case
+    for H, d in ((heads, 64), (heads // 2, 128)):
+        assert sa.gate_kernel(sa.make_desc(B, H, H, n, d, 4), backward, dual) == f"gate_proj_{'wide' if wide else 'fwd'}_bf16_kernel"

@@ -190,15 +190,25 @@ def test_weight_gradients_of_short_calls_repeat_themselves(B, H, d, n, dual):
         assert (first[x].double() - ref).norm() <= 5e-3 * ref.norm()
 
 
-@pytest.mark.parametrize("B,H,n,d,dual", [(22, 8, 257, 64, True), (13, 4, 600, 128, True), (86, 4, 300, 64, False), (129, 2, 129, 128, False)])
-def test_wide_tiles_forward(B, H, n, d, dual):
+def products_on(B, H, n, d, dual, backward):
+    from paper_2604_00754_amd import binding as sa
+    return sa.gate_kernel(sa.make_desc(B, H, H, n, d, 4), backward, dual)
+
+
+@pytest.mark.parametrize("B,H,n,d,dual,wide", [(22, 8, 257, 64, True, True), (13, 4, 600, 128, True, True), (43, 8, 300, 64, False, True),
+                                               (65, 4, 129, 128, False, True), (86, 4, 300, 64, False, False), (129, 2, 129, 128, False, False)])
+def test_wide_tiles_forward(B, H, n, d, dual, wide):
     """Batches that fill a round of 256 CUs with tiles of 256 tokens x 128 (both branches) or 256 (single path) features better than
-    with tiles of 128 x 128; ragged token tiles, with and without gate outputs."""
+    with tiles of 128 x 128 (256 features: narrow ones); ragged token tiles, with and without gate outputs."""
+    assert products_on(B, H, n, d, dual, False) == f"gate_proj_{'wide' if wide else 'fwd'}_bf16_kernel"
     run_case(B, H, n, d, seed=B + n, dual=dual, want_gates=n != 600)
 
 
-@pytest.mark.parametrize("B,H,n,d,dual", [(65, 4, 129, 64, True), (43, 2, 300, 128, True), (22, 8, 257, 64, True), (52, 4, 600, 64, False)])
-def test_wide_tiles_backward(B, H, n, d, dual):
+@pytest.mark.parametrize("B,H,n,d,dual,wide", [(22, 8, 257, 64, True, True), (33, 4, 129, 128, True, True), (43, 8, 300, 64, False, True),
+                                               (65, 4, 129, 128, False, True), (65, 4, 129, 64, True, False), (43, 2, 300, 128, True, False),
+                                               (52, 4, 600, 64, False, False)])
+def test_wide_tiles_backward(B, H, n, d, dual, wide):
+    assert products_on(B, H, n, d, dual, True) == f"gate_proj_{'wide' if wide else 'fwd'}_bf16_kernel"
     run_bwd_case(B, H, n, d, seed=B + n, dual=dual)
 
 
