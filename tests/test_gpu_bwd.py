@@ -16,7 +16,7 @@ def grad_close(got, ref, dtype, what):
 
 
 def run_bwd(B, Hq, Hkv, n, d, w, window, causal, dtype, perm_B=1, perm_H=1, seed=0, identity=False,
-            k_growth=0.0):
+            k_growth=0.0, scale=0.0):
     from oracle import binding as orc
     from paper_2604_00754_amd import binding as sa
     wl, x = U.make_case(B, Hq, Hkv, n, d, w, dtype, perm_B, perm_H, seed, grads=True, identity=identity)
@@ -29,10 +29,12 @@ def run_bwd(B, Hq, Hkv, n, d, w, window, causal, dtype, perm_B=1, perm_H=1, seed
     print(f"case bwd B{B} Hq{Hq} Hkv{Hkv} n{n} d{d} w{w} win{window} causal{causal} {dtype} "
           f"perm[{perm_B},{perm_H}] identity={identity}", flush=True)
     oc = U.orc_desc(wl, window, causal)
+    oc.scale = scale
     dQr, dKr, dVr = orc.sa_bwd(oc, x["Q"], x["K"], x["V"], x["perm"], x["dY"])
     Q, K, V, dY = (U.to_dev(x[k], dtype) for k in ("Q", "K", "V", "dY"))
     perm = None if identity else torch.from_numpy(x["perm"]).to(U.DEV)
     desc = U.sa_desc(wl, window, causal)
+    desc.scale = scale
     Y = torch.empty_like(Q)
     L = torch.empty((B, Hq, n), device=U.DEV, dtype=torch.float32)
     sa.sa_fwd(desc, Q, K, V, perm, Y, L)
@@ -47,7 +49,7 @@ def run_bwd(B, Hq, Hkv, n, d, w, window, causal, dtype, perm_B=1, perm_H=1, seed
     grad_close(U.to_np64(dV), dVr, dtype, "dV")
 
 
-def run_gated_bwd(B, Hq, Hkv, n, d, w, dtype, perm_B=1, perm_H=1, per_dim=0, gate_dtype="f32", seed=0):
+def run_gated_bwd(B, Hq, Hkv, n, d, w, dtype, perm_B=1, perm_H=1, per_dim=0, gate_dtype="f32", seed=0, close_gates=False):
     from oracle import binding as orc
     from paper_2604_00754_amd import binding as sa
     from paper_2604_00754_amd import synth
@@ -59,6 +61,11 @@ def run_gated_bwd(B, Hq, Hkv, n, d, w, dtype, perm_B=1, perm_H=1, per_dim=0, gat
         rng = np.random.default_rng(seed)
         ga = rng.standard_normal((B, Hq, n, d)).astype(np.float32)
         gl = rng.standard_normal((B, Hq, n, d)).astype(np.float32)
+    if close_gates:  # a third of either branch's rows: closed for good, all but closed, wide open
+        ga, gl = ga.copy(), gl.copy()
+        for g, first in ((ga, 0), (gl, 1)):
+            for i, value in enumerate((-np.inf, -90.0, np.inf)):
+                g[:, :, first + i::9] = value
     if gate_dtype == "bf16":
         ga, gl = synth.round_to_bf16(ga), synth.round_to_bf16(gl)
     osa, oswa = U.orc_desc(wl, CIRC, 1), U.orc_desc(wl, ONE, 1)
