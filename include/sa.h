@@ -18,8 +18,9 @@
  *   - All tensor pointers are DEVICE pointers owned by the caller, contiguous row-major, 16-byte
  *     aligned: Q, Y, dY, dQ, Y_sa, Y_swa [B,Hq,n,d]; K, V, dK, dV [B,Hkv,n,d]; LSE [B,Hq,n] float.
  *     Query head hq uses kv head hq / (Hq/Hkv).  Alignment is checked on the host: a tensor, weight or
- *     workspace pointer that is not 16-byte aligned, or an index / LSE / gate array not aligned to its
- *     element, gives SA_ERR_UNSUPPORTED before anything is launched.
+ *     workspace pointer that is not 16-byte aligned, an index / LSE / gate array not aligned to its
+ *     element, or a RoPE table not aligned to its (cos, sin) pairs of 8 bytes, gives SA_ERR_UNSUPPORTED before
+ *     anything is launched.
  *   - Size limits (SA_ERR_SHAPE beyond): n <= 2^30, B*Hq*n < 2^31 rows; the bf16 kernels additionally need one
  *     head's rows to span less than 2 GiB (n*d*2 < 2^31, SA_ERR_UNSUPPORTED beyond).
  *   - perm: int32 [perm_B, perm_H, n]; perm[..., p] is the ORIGINAL index of the token placed at
@@ -184,13 +185,14 @@ sa_status sa_fwd_rope(const sa_desc* desc, const void* Q, const void* K, const v
 /* The backward of sa_fwd_rope (App. B "Attention" item, App. C, Sec. 4.2: RoPE on original positions, then
  * stochastic attention; the gradient of Eq. 1 over the visible set of Eq. 3 / App. B, and the transpose of the
  * rotation of RoFormer Sec. 3.2.2).  Q arrives UNROTATED and K ROTATED, as for sa_fwd_rope; Y, LSE: what
- * sa_fwd_rope returned; dY: gradient w.r.t. Y.  Each query row is rotated while the dQ kernel stages it (the
- * rotated rows, rounded to bf16 as in the forward, are kept in the workspace for the dK/dV kernel, which
- * streams them) and dQ is turned back in that kernel's epilogue: dQ is the gradient w.r.t. the UNROTATED Q.
- * dk_unrotated = 1: dK is turned back in the dK/dV kernel's epilogue as well (gradient w.r.t. the unrotated K,
- * what a caller that rotated K with sa_rope needs); 0: dK is the gradient w.r.t. the rotated K as given.
+ * sa_fwd_rope returned; dY: gradient w.r.t. Y.  Each query row is rotated (and rounded to bf16, as in the
+ * forward) while it is staged, and dQ is turned back on its way out: dQ is the gradient w.r.t. the UNROTATED Q.
+ * dk_unrotated = 1: dK is turned back on its way out as well (gradient w.r.t. the unrotated K, what a caller that
+ * rotated K with sa_rope needs); 0: dK is the gradient w.r.t. the rotated K as given.
  * dV as in sa_bwd.  All of dQ, dK, dV are overwritten.  bf16 only (SA_ERR_UNSUPPORTED otherwise).
- * ws: sa_workspace_bytes(desc, SA_OP_BWD_ROPE) bytes of device memory (SA_ERR_WORKSPACE if smaller). */
+ * ws: sa_workspace_bytes(desc, SA_OP_BWD_ROPE) bytes of device memory (SA_ERR_WORKSPACE if smaller): room for the
+ * rotated query rows and the row sums of dY * Y where two kernels share them; calls that one kernel serves leave it
+ * untouched. */
 sa_status sa_bwd_rope(const sa_desc* desc, const void* Q, const void* K, const void* V, const int32_t* perm,
                       const float* rope_table, int32_t interleaved, int32_t dk_unrotated, const void* Y,
                       const float* LSE, const void* dY, void* dQ, void* dK, void* dV, void* ws, size_t ws_bytes,

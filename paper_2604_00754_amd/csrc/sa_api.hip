@@ -486,7 +486,7 @@ sa_status sa_dual_path_bwd(const sa_desc* sa_d, const sa_desc* swa_d, const void
   for (int x = 0; x < 2; ++x) {
     Pass p = make_pass(dsc[x], Q, K, V, x == 0 ? nullptr : perm);
     p.dO = dO[x]; p.lse_in = lse[x];
-    p.O_rows = Yx[x]; p.Dsum_out = D[x];  // the dQ kernel forms rowsum(dO o O) from the rows it holds
+    p.O_rows = Yx[x]; p.Dsum_out = D[x];  // rowsum(dO o O) is formed from the rows that the kernels hold
     p.dQ = dQ; p.dK = dK; p.dV = dV; p.accumulate = x;
     e = run_bwd(dsc[x], p, st);
     if (e != hipSuccess) return hip_status(e);
@@ -565,7 +565,7 @@ sa_status sa_bwd(const sa_desc* sa_d, const sa_desc* swa_d, const void* Q, const
   char* base = reinterpret_cast<char*>(ws);
 
   float* D_a = reinterpret_cast<float*>(base + w.off_Da);
-  // ungated: the dQ kernel forms rowsum(dY o Y) from the rows it holds and leaves it in D_a
+  // ungated: rowsum(dY o Y) is formed from the rows that the kernels hold (two-kernel form: left in D_a by the first)
   Pass b = make_pass(sa_d, Q, K, V, perm);
   b.dO = dY;
   b.lse_in = LSE_sa;
@@ -632,7 +632,7 @@ sa_status sa_bwd_rope(const sa_desc* c, const void* Q, const void* K, const void
   b.Q_rot = base + w.total;
   b.dO = dY;
   b.lse_in = LSE;
-  b.O_rows = Y;  // the dQ kernel forms rowsum(dY o Y) from the rows it holds
+  b.O_rows = Y;  // rowsum(dY o Y) is formed from the rows that the kernels hold
   b.Dsum_out = reinterpret_cast<float*>(base + w.off_Da);
   b.dQ = dQ; b.dK = dK; b.dV = dV; b.accumulate = 0;
   return hip_status(sa::launch_bwd_mfma_bf16(b, st));

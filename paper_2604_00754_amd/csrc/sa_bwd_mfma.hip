@@ -5,6 +5,7 @@
 // permuted order, with rows gathered from and scattered to their original positions:
 //   P = exp(S - LSE),  dV = P^T dO,  dP = dO V^T,  dS = P * (dP - D),  dQ = scale dS K,
 //   dK = scale dS^T Q,  D = rowsum(dO * O).
+// (d = 64 with one query head per KV head goes through sa_bwd_strip.hip where that is faster.)
 // Two kernels, both recomputing S from Q and K:
 //   dQ kernel    -- a workgroup owns 128 query slots (as in the forward) and walks key tiles;
 //                   S^T and dP^T are produced in the "lane = query" layout, dS^T feeds

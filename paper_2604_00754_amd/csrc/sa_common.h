@@ -27,9 +27,9 @@ struct Pass {
   int causal;
   float scale;          // softmax scale (Eq. 1)
   // bf16 only: rotate the Q rows on their original positions while they are staged (RoPE table [n][d/2][2]
-  // of sa_rope_table; nullptr = Q arrives rotated).  K always arrives rotated.  In the backward the dQ kernel
-  // does the same, leaves the rotated rows in Q_rot for the dK/dV kernel (which streams them) and turns dQ back
-  // in its epilogue; rope_dk: the dK/dV kernel turns dK back as well (gradient w.r.t. the unrotated K).
+  // of sa_rope_table; nullptr = Q arrives rotated).  K always arrives rotated.  The backward does the same and turns dQ back on
+  // its way out; rope_dk: dK as well (gradient w.r.t. the unrotated K).  In the two-kernel form the dQ kernel leaves the rotated rows in
+  // Q_rot for the dK/dV kernel, which streams them; the one-pass form turns them in LDS and leaves Q_rot untouched.
   const float* rope_table;
   int rope_interleaved;
   void* Q_rot;
@@ -48,8 +48,8 @@ struct Pass {
   const void* dO;       // gradient w.r.t. this branch's output [B,Hq,n,d]
   const float* lse_in;  // [B,Hq,n]
   const float* Dsum;    // rowsum(dO * O) [B,Hq,n]
-  const void* O_rows;   // optional: this branch's output rows [B,Hq,n,d]; when given, the dQ kernel forms
-  float* Dsum_out;      // rowsum(dO * O) itself from its stationary rows and leaves it here for the dK/dV kernel
+  const void* O_rows;   // optional: this branch's output rows [B,Hq,n,d]; when given, rowsum(dO * O) is formed from the rows that
+  float* Dsum_out;      // the kernel holds anyway.  Two-kernel form: the dQ kernel leaves it here for the other; one-pass form: untouched
   void* dQ;
   void* dK;
   void* dV;

@@ -14,7 +14,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 // two (cos, sin) pairs of a RoPE table in device memory, which callers align to one pair
-typedef float table_f32x4 __attribute__((ext_vector_type(4), aligned(8)));
+typedef float4 table_float4 __attribute__((aligned(8)));
 typedef uint32_t table_u32x4 __attribute__((ext_vector_type(4), aligned(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));

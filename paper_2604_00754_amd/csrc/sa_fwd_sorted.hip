@@ -284,7 +284,7 @@ __global__ __launch_bounds__(NT, 3) void fwd_sorted_bf16_kernel(const Pass p, co
 #pragma unroll
     for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(table + (8 * wave + 2 * i + (ln >> 5)) * TABLE_STR + 4 * (ln & 31)) = angles[i];
     __syncthreads();
-    rope_row_fragments<D, f32x4>(qf, reinterpret_cast<const float2*>(table + (ln & 31) * TABLE_STR), ln >> 5, p.rope_interleaved);
+    rope_row_fragments<D, true>(qf, reinterpret_cast<const float2*>(table + (ln & 31) * TABLE_STR), ln >> 5, p.rope_interleaved);
   }
 
   float m_ref = 0.f, l_run = 0.f;

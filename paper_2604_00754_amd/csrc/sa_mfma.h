@@ -105,19 +105,19 @@ __device__ __forceinline__ bf16x8 lds_read_transposed_swz(const bf16_t* rows16, 
 // RoPE (RoFormer Sec. 3.2.2) of one row held as MFMA operand fragments: lane group g2 holds elements
 // 16kk + 8*g2 .. +7 of the row in f[kk], so both members of a pair are the lane's own -- (x[i], x[i + D/2]) sit
 // in fragments kk and kk + D/32, (x[2i], x[2i+1]) next to each other.  trow: the (cos, sin) of the row's
-// position, D/2 pairs, read as Pairs: table_f32x4 from a caller's table, f32x4 from a copy on 16-byte boundaries.  The rotated values
-// are rounded to bf16.
-template <int D, typename Pairs = table_f32x4>
+// position, D/2 pairs, COPY: a copy on 16-byte boundaries, not a caller's table.  The rotated values are rounded to bf16.
+template <int D, bool COPY = false>
 __device__ __forceinline__ void rope_row_fragments(bf16x8* f, const float2* trow, int g2, int interleaved) {
+  auto pairs = [](const float2* at) -> float4 { return COPY ? *reinterpret_cast<const float4*>(at) : *reinterpret_cast<const table_float4*>(at); };
   if (!interleaved) {
 #pragma unroll
     for (int kk = 0; kk < D / 32; ++kk) {
-      const Pairs* tp = reinterpret_cast<const Pairs*>(trow + 16 * kk + 8 * g2);
+      const float2* tp = trow + 16 * kk + 8 * g2;
       const u32x4 a = __builtin_bit_cast(u32x4, f[kk]), b = __builtin_bit_cast(u32x4, f[kk + D / 32]);
       u32x4 ra, rb;
 #pragma unroll
       for (int m = 0; m < 4; ++m) {  // dword m = elements 2m, 2m+1 of the fragment
-        const f32x4 t = tp[m];       // (cos, sin) of pairs 2m and 2m+1
+        const float4 t = pairs(tp + 2 * m);  // (cos, sin) of pairs 2m and 2m+1
         const float a0 = bf16lo(a[m]), a1 = bf16hi(a[m]), b0 = bf16lo(b[m]), b1 = bf16hi(b[m]);
         ra[m] = pack_bf16(a0 * t.x - b0 * t.y, a1 * t.z - b1 * t.w);
         rb[m] = pack_bf16(a0 * t.y + b0 * t.x, a1 * t.w + b1 * t.z);
@@ -128,12 +128,12 @@ __device__ __forceinline__ void rope_row_fragments(bf16x8* f, const float2* trow
   } else {
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
-      const Pairs* tp = reinterpret_cast<const Pairs*>(trow + 8 * kk + 4 * g2);
+      const float2* tp = trow + 8 * kk + 4 * g2;
       const u32x4 a = __builtin_bit_cast(u32x4, f[kk]);
       u32x4 ra;
 #pragma unroll
       for (int m = 0; m < 2; ++m) {  // dwords 2m, 2m+1 = pairs 2m, 2m+1 of the fragment
-        const f32x4 t = tp[m];
+        const float4 t = pairs(tp + 2 * m);
         const float x0 = bf16lo(a[2 * m]), y0 = bf16hi(a[2 * m]);
         const float x1 = bf16lo(a[2 * m + 1]), y1 = bf16hi(a[2 * m + 1]);
         ra[2 * m] = pack_bf16(x0 * t.x - y0 * t.y, x0 * t.y + y0 * t.x);
@@ -155,8 +155,8 @@ __device__ __forceinline__ void rope_transpose_accumulators(f32x16* acc, const f
     for (int db = 0; db < D / 64; ++db)
 #pragma unroll
       for (int mq = 0; mq < 4; ++mq) {
-        const table_f32x4* tp = reinterpret_cast<const table_f32x4*>(trow + 32 * db + 8 * mq + 4 * g2);
-        const f32x4 t01 = tp[0], t23 = tp[1];  // (cos, sin) of pairs x = 0, 1 and x = 2, 3
+        const table_float4* tp = reinterpret_cast<const table_float4*>(trow + 32 * db + 8 * mq + 4 * g2);
+        const float4 t01 = tp[0], t23 = tp[1];  // (cos, sin) of pairs x = 0, 1 and x = 2, 3
         const float c[4] = {t01.x, t01.z, t23.x, t23.z}, sn[4] = {t01.y, t01.w, t23.y, t23.w};
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
@@ -170,7 +170,7 @@ __device__ __forceinline__ void rope_transpose_accumulators(f32x16* acc, const f
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
       for (int mq = 0; mq < 4; ++mq) {
-        const f32x4 t = *reinterpret_cast<const table_f32x4*>(trow + 16 * db + 4 * mq + 2 * g2);  // pairs of x = 0,1 and 2,3
+        const float4 t = *reinterpret_cast<const table_float4*>(trow + 16 * db + 4 * mq + 2 * g2);  // pairs of x = 0,1 and 2,3
         const float a0 = acc[db][4 * mq + 0], b0 = acc[db][4 * mq + 1], a1 = acc[db][4 * mq + 2], b1 = acc[db][4 * mq + 3];
         acc[db][4 * mq + 0] = a0 * t.x + b0 * t.y;
         acc[db][4 * mq + 1] = b0 * t.x - a0 * t.y;

@@ -91,10 +91,10 @@ __global__ __launch_bounds__(ROPE_THREADS) void rope_apply_kernel(const T* __res
   const bool second = !INTERLEAVED && !BOTH && c >= cpr / 2;  // holds the second members of its pairs
   float cs[NPAIR], sn[NPAIR];
   {
-    const table_f32x4* tp = reinterpret_cast<const table_f32x4*>(table + (size_t)m * (d / 2) + NPAIR * (second ? c - cpr / 2 : c));
+    const table_float4* tp = reinterpret_cast<const table_float4*>(table + (size_t)m * (d / 2) + NPAIR * (second ? c - cpr / 2 : c));
 #pragma unroll
     for (int j = 0; j < NPAIR / 2; ++j) {
-      const f32x4 v = tp[j];
+      const float4 v = tp[j];
       cs[2 * j] = v.x; sn[2 * j] = v.y;
       cs[2 * j + 1] = v.z; sn[2 * j + 1] = v.w;
     }
