@@ -16,9 +16,10 @@
 //
 // Bound: the issue of vector instructions (per SIMD and interval about 3000 cycles of 4500 at NB = 9: 150 instructions and 16
 // exponentials for a block of 32 x 32, 2.25 blocks a SIMD, 1000 instructions for the three other roles), then the LDS latencies of the
-// slowest role.  Measured against the two kernels (us): 64 heads, 8192 slots, d = 64, w = 256, one call alone 242 -> 159, the
-// one-sided branch 223 -> 150; 256 heads, 4096 slots with rotations 590 -> 345 (430 while dK's table rows went through LDS to the accumulators).  NB + 3 waves of 168 registers at NB = 9 fill a
-// CU; its LDS (155 KB) holds query tiles three intervals ahead and one K tile a wave.  The strip is as long as one round of 256
+// slowest role.  Measured against the two kernels (us): 64 heads, 8192 slots, d = 64, w = 256, one call alone 242 -> 158, calls in a row
+// 238 -> 146, the one-sided branch 223 -> 150; 256 heads, 4096 slots with rotations 590 -> 342 (430 while dK's table rows went through LDS to the
+// accumulators); other sizes at strips_are_faster().  NB + 3 waves of 168 registers at NB = 9 fill a CU; its LDS (155 136 bytes, with rotations
+// 163 328 of the 163 840) holds query tiles three intervals ahead and one K tile a wave.  The strip is as long as one round of 256
 // workgroups allows (2048 slots there): every strip walks its windows' reach on top of its own slots.
 #include "sa_common.h"
 #include "sa_mfma.h"

@@ -289,10 +289,11 @@ __global__ __launch_bounds__(GNT, 2) void gate_proj_fwd_bf16_kernel(const GatePr
 //            half of Y.
 //   else     256 x 256, steps of 64 (whole lines), two buffers: input gradients (the branches are independent parts of the work
 //            list) and the forward of a single path.
-// Measured at B4, n = 8192, 16 heads of 64 (us): forward of both branches 180 -> 171 (124 without the loads: half lines, 64 bytes of a row
-// a step, cost 12 of the rest; two buffers of whole lines do not fit beside either branch's tiles), single path 94 -> 78 = 0.88
-// PFLOP/s, backward of both 460 -> 427.  A step's loads go out with the first two operand groups, not all behind the barrier:
-// 173 -> 170, 80 -> 78.  Wave priorities around the products: no change.
+// Measured at B4, n = 8192, 16 heads of 64, both forms in turn in one process (us): forward of both branches 180 -> 171 (124 without the
+// loads: half lines, 64 bytes of a row a step, cost 12 of the rest; two buffers of whole lines do not fit beside either branch's tiles), single
+// path 94 -> 78 = 0.88 PFLOP/s, backward of both 460 -> 427 (now 403 with the rest of the call).  bench.py, which times each call by itself,
+// reads 189 to 192 for the forward (0.72 PFLOP/s) and 413 to 437 for the backward.  A step's loads go out with the first two operand groups, not all
+// behind the barrier: 173 -> 170, 80 -> 78.  Wave priorities around the products: no change.
 constexpr int XTM = 256;
 constexpr int XNT = 512;
 constexpr int XSTR = 64 + 8;                     // bf16 per staged row
