@@ -24,6 +24,9 @@
 #include "sa_common.h"
 #include "sa_mfma.h"
 
+#include <algorithm>
+#include <cmath>
+
 namespace sa {
 namespace {
 
@@ -733,9 +736,25 @@ int key_blocks(const Pass& p) { return p.win.L + p.win.R <= 128 ? 5 : 9; }
 // plain causal SWA: the window already leaves out every later key
 bool masks_positions(const Pass& p) { return p.causal && !(!p.perm && !p.win.circular && p.win.R == 0); }
 
-// Microseconds of a call with either form, as far as the choice needs them: workgroups of 128 slots fill the CUs in small pieces,
-// strips in rounds of 256, each with the intervals of its start, of its windows' reach and of its own slots.  Both lines go through what was
-// measured with both forms on 1608 calls (1 to 2048 heads, 40 to 65535 slots, w = 1 to 257; plain, one-sided, gated and with rotations).
+// Intervals with pairs of the strip that has most of them (the kernel's block grids).
+int intervals(const Pass& p, const Strips& s) {
+  const int L = p.win.L, R = p.win.R;
+  int most = 0;
+  for (const int strip : {0, s.per_head / 2, s.per_head - 1}) {
+    const int k0 = strip * s.slots, k1 = std::min(k0 + s.slots, p.n);
+    const int q_lo = p.win.circular ? k0 - R : std::max(k0 - R, 0), q_hi = p.win.circular ? k1 - 1 + L : std::min(k1 - 1 + L, p.n - 1);
+    const int Q0 = k0 - (k0 - q_lo + RB - 1) / RB * RB;
+    most = std::max({most, (q_hi - Q0) / RB + 1, (k1 - 1 - Q0 + L) / RB + 1});
+  }
+  return most;
+}
+
+// Microseconds of a call with either form, as far as the choice needs them.  Strips come in rounds of 256 workgroups, each with the intervals of
+// its longest strip, and are slowed down by HBM where there are many rows.  The two kernels' workgroups of 128 slots go up in steps: a second one to a
+// CU costs little, a third is a second round of the dK/dV kernel.  The constants are those for which fewest of 4200 calls measured with both forms take
+// the slower one (1 to 1200 heads, 40 to 65535 slots, w = 1 to 257, circular and one-sided, with rotations and without; a third of them at the
+// heads and lengths of training steps, a quarter at edges of rounds): both estimates are within 7 % of their times (standard deviation), 18 calls take
+// a form that is more than a tenth slower than the other, against 94 with strips for all, and the calls as a whole 0.2 % longer than with the faster form each.
 // Two kernels / strips (us), no rotations, circular, by heads x slots, w = 33 | 129 | 257:
 //   1 x 300     14.5 / 9.1  | 18.1 / 11.6 | 23.4 / 18.3      64 x 512    15.9 / 13.0 | 19.5 / 16.8 | 24.5 / 25.2
 //   12 x 16384  65.9 / 39.9 | 79.1 / 46.8 | 94.1 / 63.8      64 x 8192   161 / 115   | 196 / 122   | 238 / 146
@@ -745,25 +764,26 @@ bool masks_positions(const Pass& p) { return p.causal && !(!p.perm && !p.win.cir
 // One-sided without a permutation, w = 257: 256 x 256 24.8 / 28.6, 257 x 256 33.6 / 53.7, 192 x 512 48.5 / 40.8; rotations, w = 257: 64 x 512
 // 28.7 / 30.9, 480 x 300 87 / 76.
 bool strips_are_faster(const Pass& p) {
-  const int nb = key_blocks(p);
-  const Strips s = plan(p, nb);
+  const Strips s = plan(p, key_blocks(p));
   const long heads = (long)p.B * p.Hq;
-  const double reach = p.win.L + p.win.R;
-  const double rounds = (double)((heads * s.per_head + kCUs - 1) / kCUs), blocks = (double)s.slots / RB;
-  double strips = 0.92 * (nb + 2 + reach / RB) + (1.2 + 0.0025 * reach) * blocks;
-  if (!masks_positions(p)) strips *= 0.92;
-  if (p.rope_table) strips += 2.5 + 0.65 * blocks;
-  // what 128 neighbouring slots see beyond themselves, on average over a sequence with ends
+  const int reach = p.win.L + p.win.R, turned = p.rope_table ? 1 : 0;
+  // what neighbouring slots see beyond themselves, on average over a sequence with ends
   double seen = reach;
   if (!p.win.circular)
     for (const double side : {(double)p.win.L, (double)p.win.R}) seen -= side * (side + 128) / (2. * p.n);
   if (seen < 0) seen = 0;
-  // Workgroups per CU, one that is not whole counting as more than its slots.  A second one on the CUs: 1.4 times; a third, for which the dK/dV
-  // kernel has no place: 1.8.
-  const double fills = (double)heads * ((p.n + 127) / 128 + p.n / 128.) / 2 / kCUs;
-  double two = (reach > 0 ? 14.5 + 0.039 * seen : 11.) * (fills <= 1 ? 1. : (fills <= 2 ? 1.38 : 0.7 + 0.53 * fills));
-  if (p.rope_table) two += 2.5 + 1.8 * fills;
-  return rounds * strips <= two;
+
+  const double rounds = (double)((heads * s.per_head + kCUs - 1) / kCUs);
+  const double walk = rounds * (6.8 + intervals(p, s) * (1.0 + 0.062 * seen / RB + 0.48 * turned)) + 1.5 * turned;
+  const double rows = (0.13 + 0.08 * turned) * 1e-3 * (double)heads * p.n;
+  const double strips = std::sqrt(walk * walk + rows * rows);
+
+  const long tiles = (p.n + 127) / 128;
+  const double per_cu = (double)heads * tiles / kCUs, filled = p.n / (128. * tiles);
+  const double one = 21 + (masks_positions(p) ? 7.2 : 6.0) * seen / 128 - (reach ? 0 : 2.4);
+  const double steps = per_cu <= 1 ? 1 : (per_cu <= 2 ? 1.05 + 0.09 * per_cu : 0.71 + 0.41 * per_cu);
+  const double two = one * steps * (0.73 + 0.27 * filled) - 5.2 + turned * (1.8 + 2.6 * filled * per_cu);
+  return strips <= two;
 }
 
 template <int NB, int CAUSAL>

@@ -268,6 +268,15 @@ BWD_ROUTES = [
     (192, 512, 257, sa.SA_WIN_ONE_SIDED, 0, "strip"),    # 48.5, 40.8
     (64, 8192, 256, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 238, 146
     (256, 4096, 256, sa.SA_WIN_SYM_CIRCULAR, 1, "strip"),  # 590, 345
+    (108, 566, 225, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 44.2, 30.5: a third workgroup of the two kernels to a CU
+    (48, 1291, 229, sa.SA_WIN_SYM_CIRCULAR, 1, "strip"),  # 54.3, 41.5
+    (132, 992, 35, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 58.5, 45.0
+    (144, 903, 142, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 70.4, 56.3
+    (176, 1093, 148, sa.SA_WIN_SYM_CIRCULAR, 1, "strip"),  # 102.5, 86.0
+    (133, 921, 131, sa.SA_WIN_ONE_SIDED, 0, "strip"),    # 64.9, 50.0
+    (320, 512, 65, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 62.5, 52.2
+    (153, 1797, 1, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),  # 71.9, 54.6
+    (96, 575, 205, sa.SA_WIN_ONE_SIDED, 1, "mfma"),      # 34.3, 39.4
     (64, 65535, 257, sa.SA_WIN_SYM_CIRCULAR, 0, "strip"),
     (64, 65536, 257, sa.SA_WIN_SYM_CIRCULAR, 0, "mfma"),  # positions no longer fit 16 bits
     (64, 8192, 258, sa.SA_WIN_ONE_SIDED, 0, "mfma"),     # a window past what the waves of a workgroup hold

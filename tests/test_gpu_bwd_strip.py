@@ -27,11 +27,11 @@ def test_windows_around_the_key_blocks_of_a_workgroup(w, window, identity):
 
 
 @pytest.mark.parametrize("B,H,n,w,served", [(1, 64, 511, 100, "both"), (2, 70, 97, 40, "both"), (1, 130, 256, 256, "circular"), (1, 5, 32, 31, "both"),
-                                            (1, 1, 40, 8, "both"), (3, 100, 300, 64, ""), (1, 200, 512, 100, "both"), (1, 250, 700, 256, "both"),
+                                            (1, 1, 40, 8, "both"), (3, 100, 300, 64, "both"), (1, 257, 256, 33, ""), (1, 200, 512, 100, "both"), (1, 250, 700, 256, "both"),
                                             (2, 240, 300, 64, "both")])
 def test_strip_lengths(B, H, n, w, served):
     """64 heads: four strips each; 140 and 200: one each, of four and of sixteen blocks (more key blocks than a workgroup's waves); 250: of 22,
-    nine key blocks in reach; 480: two full rounds of workgroups (300: two kernels); 32 slots: one block."""
+    nine key blocks in reach; 300 and 480: two rounds of workgroups (257 over 256 slots: two kernels); 32 slots: one block."""
     assert on_strips(B, H, n, w, CIRC) == (served != "") and on_strips(B, H, n, w, ONE) == (served == "both")
     run_bwd(B, H, H, n, 64, w, CIRC, 1, "bf16", seed=400 + n)
     run_bwd(B, H, H, n, 64, w, ONE, 0, "bf16", seed=401 + n)
