@@ -767,16 +767,24 @@ __global__ __launch_bounds__(256) void gate_dw_round_kernel(const GateBwd p, con
 //   single path             128 29.3 / 26.6, 136 28.7 / 39.3, 256 38.8 / 49.2, 288 63.5 / 61.0, 352 65.1 / 69.2, 448 69.1 / 86.8
 // Short sequences, whose last tile a wide one pads further (batch x tokens, heads of 64): 16 x 300 of 16 38.6 / 40.6, 16 x 513 of 12 54.1 / 34.5,
 // 13 x 1030 of 16 109 / 84, backward 10 x 513 of 16 97 / 107, 16 x 513 of 12 109 / 99; 130 x 40 of 2 13.7 / 9.7.
-// A wide tile's longer start and end need steps to pay for them.  Below dm = 1024 the forward of both branches gains only where the second
-// half round of narrow ones is mostly empty (dm = 512, by wide workgroups: 192 35.2 / 38.4, 256 29.8 / 29.3, 512 60.1 / 55.5, 1024 115 / 106; 640:
-// 160 .89 of it, 240 1.01, 480 63.3 / 62.1, 1280 165 / 155; 768: 192 .90, 768 112 / 108), the others only in one round or with half a round to
-// spare (single path, dm = 512: 192 23.3 / 24.5, 256 28.1 / 29.9, 384 46.3 / 42.4; 768: 384 56.6 / 55.6, 576 89.6 / 82.2, 768 95.7 / 115); below dm = 512
-// none (dm = 256, backward of both 256 74.8 / 71.9, 384 102 / 94.5, single path 192 19.0 / 17.3).
-bool wide_is_faster(long wide, long narrow, bool both, long dm) {
+// A wide tile's longer start and end need steps to pay for them.  What that comes to depends on whether the call's inputs are still in the last
+// level cache (hot: the same buffers again and again; else 600 MB of buffers in turn, as a program's layers use them).  Wide / narrow:
+//   forward of both, dm < 1024: up to 8 % faster hot and as much slower in turn (dm = 768: 4 x 8192 112 / 118 hot, 123 / 124; 2 x 8474 66.9 / 69.5, 76.7 / 70.7; 6 x 8400
+//     179 / 188, 200 / 198; 13 x 2774 139 / 133, 152 / 142; dm = 512: 3 x 4096 24.9 / 26.1, 28.8 / 27.7; 2 x 16384 62.5 / 58.4, 67.9 / 63.6; 4 x 14579 112 / 109, 122 /
+//     117).  Behind the attention, in sa_dual_path_fwd with buffers in turn, the layer is 1 to 3 % slower with wide tiles in 66 of 71 such calls; at dm = 1024 to 1536 level
+//     where the tokens are whole tiles and up to 4 % slower where not, at 2048 2 to 4 % faster
+//   the others at dm = 768 as from 1024 on (in turn: single path 6 x 8192 93.6 / 94.8, 9 x 3454 58.7 / 61.8, 8 x 8192 106 / 132; backward of both 4 x 6077 218 / 219,
+//     9 x 2845 223 / 229, 2 x 8192 160 / 157; single path's 11 x 4096 of 3 whole half rounds a wide one 85.8 / 89.6)
+//   at dm = 512 in one round or with half a round to spare (single path 6 x 8192 52.4 / 48.0, 10 x 4427 45.7 / 44.7, 7 x 8192 53.7 / 55.4; backward of both 6 x 3504
+//     117 / 117, 14 x 2048 137 / 141)
+//   below that the single path's forward in one round (dm = 256: 3 x 16384 18.6 / 21.2, 12 x 2721 15.3 / 18.2, 13 x 4096 20.5 / 23.6; the exception 6 x 8192 21.9 / 20.8;
+//     backward of both 17 x 2729 104 / 100, 12 x 4096 107 / 104)
+bool wide_is_faster(long wide, long narrow, bool backward, bool dual, long dm) {
   const long rounds = (wide + 255) / 256, halves = (narrow + 255) / 256;
-  if (wide < 1 || dm < 512) return false;
-  if (both) return dm >= 1024 ? halves >= 2 * rounds : halves == 2 && wide <= 218;
-  return dm >= 1024 || rounds == 1 ? halves >= 3 * rounds : 2 * halves >= 7 * rounds;
+  if (wide < 1) return false;
+  if (!backward && dual) return dm >= 1024 && halves >= 2 * rounds;
+  if (dm < 512) return !backward && rounds == 1 && halves >= 3;
+  return dm >= 768 || rounds == 1 ? halves >= 3 * rounds : 2 * halves >= 7 * rounds;
 }
 
 struct Tiles {
@@ -790,7 +798,7 @@ Tiles gate_tiles(int B, int Hq, int n, int d, bool backward, bool dual) {
   const int feats = both ? Wide<true>::FEATS : Wide<false>::FEATS;
   const int num_tt = (n + TM - 1) / TM, wide_tt = (n + XTM - 1) / XTM;
   const long total = (long)num_tt * (dm / TN) * B * parts, wide = dm % feats ? 0 : (long)wide_tt * (dm / feats) * B * parts;
-  if ((size_t)n * d * 2 < ((size_t)1 << 32) && wide_is_faster(wide, total, both, dm)) return {1, wide_tt, (int)(dm / feats), wide};  // 32-bit offsets inside a head
+  if ((size_t)n * d * 2 < ((size_t)1 << 32) && wide_is_faster(wide, total, backward, dual, dm)) return {1, wide_tt, (int)(dm / feats), wide};  // 32-bit offsets inside a head
   return {0, num_tt, (int)(dm / TN), total};
 }
 

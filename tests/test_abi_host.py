@@ -314,11 +314,17 @@ GATE_ROUTES = [
     (4, 8, 8192, 0, 1, False),   # 55.5, 60.1
     (16, 8, 4096, 0, 1, False),  # 106, 115
     (8, 10, 8192, 0, 1, False),  # 155, 165
-    (6, 8, 8192, 0, 0, False),   # 42.4, 46.3: one round and a half
-    (6, 12, 8192, 0, 0, False),  # 82.2, 89.6
+    (6, 8, 8192, 0, 0, False),   # 48.0, 52.4: one round and a half
     (4, 4, 8192, 1, 1, False),   # 71.9, 74.8
-    (6, 4, 8192, 0, 0, False),   # 17.3, 19.0
-    (3, 8, 4096, 0, 1, True),    # 38.4, 35.2
+    (2, 12, 8474, 0, 1, False),  # 70.7, 76.7
+    (13, 12, 2774, 0, 1, False),  # 142, 152
+    (11, 12, 4039, 1, 1, True),  # 390, 370
+    (3, 12, 14481, 1, 1, True),  # 382, 363
+    (16, 12, 3338, 1, 0, True),  # 251, 240
+    (6, 12, 5316, 0, 0, True),   # 60.8, 56.4
+    (3, 4, 16789, 0, 0, True),   # 21.0, 17.7
+    (13, 4, 4096, 0, 0, True),   # 23.6, 20.5
+    (3, 8, 4096, 0, 1, False),   # 27.7, 28.8
     (4, 8, 8192, 0, 0, True),    # 29.9, 28.1
     (8, 12, 8192, 0, 0, True),   # 115, 95.7
     (4, 16, 8192, 0, 1, True),   # 180, 171

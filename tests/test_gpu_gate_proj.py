@@ -195,11 +195,13 @@ def products_on(B, H, n, d, dual, backward):
     return sa.gate_kernel(sa.make_desc(B, H, H, n, d, 4), backward, dual)
 
 
-@pytest.mark.parametrize("B,H,n,d,dual,wide", [(22, 8, 257, 64, True, True), (13, 4, 600, 128, True, True), (43, 8, 300, 64, False, True),
-                                               (65, 4, 129, 128, False, True), (86, 4, 300, 64, False, False), (129, 2, 129, 128, False, False)])
+@pytest.mark.parametrize("B,H,n,d,dual,wide", [(11, 16, 257, 64, True, True), (7, 8, 600, 128, True, True), (22, 8, 257, 64, True, False),
+                                               (43, 8, 300, 64, False, True),
+                                               (65, 4, 129, 128, False, True), (86, 4, 300, 64, False, True), (129, 2, 129, 128, False, True),
+                                               (130, 4, 60, 64, False, False)])
 def test_wide_tiles_forward(B, H, n, d, dual, wide):
     """Batches that fill a round of 256 CUs with tiles of 256 tokens x 128 (both branches) or 256 (single path) features better than
-    with tiles of 128 x 128 (256 features: narrow ones); ragged token tiles, with and without gate outputs."""
+    with tiles of 128 x 128 (too few features, or too few tiles: narrow ones); ragged token tiles, with and without gate outputs."""
     assert products_on(B, H, n, d, dual, False) == f"gate_proj_{'wide' if wide else 'fwd'}_bf16_kernel"
     run_case(B, H, n, d, seed=B + n, dual=dual, want_gates=n != 600)
 
