@@ -771,7 +771,7 @@ __global__ __launch_bounds__(256) void gate_dw_round_kernel(const GateBwd p, con
 // level cache (hot: the same buffers again and again; else 600 MB of buffers in turn, as a program's layers use them).  Wide / narrow:
 //   forward of both, dm < 1024: up to 8 % faster hot and as much slower in turn (dm = 768: 4 x 8192 112 / 118 hot, 123 / 124; 2 x 8474 66.9 / 69.5, 76.7 / 70.7; 6 x 8400
 //     179 / 188, 200 / 198; 13 x 2774 139 / 133, 152 / 142; dm = 512: 3 x 4096 24.9 / 26.1, 28.8 / 27.7; 2 x 16384 62.5 / 58.4, 67.9 / 63.6; 4 x 14579 112 / 109, 122 /
-//     117).  Behind the attention, in sa_dual_path_fwd with buffers in turn, the layer is 1 to 3 % slower with wide tiles in 66 of 71 such calls; at dm = 1024 to 1536 level
+//     117).  Behind the attention, in sa_dual_path_fwd with buffers in turn, its forward is slower with wide tiles in 66 of 70 such calls, mostly by 1 to 3 %; at dm = 1024 to 1536 level
 //     where the tokens are whole tiles and up to 4 % slower where not, at 2048 2 to 4 % faster
 //   the others at dm = 768 as from 1024 on (in turn: single path 6 x 8192 93.6 / 94.8, 9 x 3454 58.7 / 61.8, 8 x 8192 106 / 132; backward of both 4 x 6077 218 / 219,
 //     9 x 2845 223 / 229, 2 x 8192 160 / 157; single path's 11 x 4096 of 3 whole half rounds a wide one 85.8 / 89.6)
